@@ -15,7 +15,7 @@
 // path.
 //
 // Precision.  Activations stay fp32 between kernels.  The GEMMs run on MFMA
-// (v_mfma_f32_32x32x16_bf16) with every activation split exactly into three
+// (v_mfma_f32_16x16x32_bf16) with every activation split exactly into three
 // bf16 terms as it is staged in LDS (a = t0 + t1 + t2), so the products keep
 // fp32 accuracy (two terms leave 2^-18, which measurably loosens the cache
 // rows of deeper layers).  Weights are exact in bf16 (int8 weights
@@ -23,6 +23,7 @@
 // epilogue).  Attention splits the queries and the softmax weights into
 // three terms as well.
 #include <math.h>
+#include <algorithm>
 
 #include "aio_internal.h"
 #include "common.h"
@@ -31,6 +32,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 AIO_DEV f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
@@ -72,6 +74,9 @@ AIO_DEV float ld_agent(const float* p) {
 }
 AIO_DEV int atomic_add_agent(int* p, int v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+AIO_DEV int atomic_load_agent(const int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 AIO_DEV void atomic_store_agent(int* p, int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -125,37 +130,64 @@ __global__ __launch_bounds__(kNormThreads) void k_pnorm(PNormArgs a) {
 
 // --------------------------------------------------------------------- GEMM
 
-// A workgroup of 2 WN waves computes a tile of 64 WN weight rows (2 WN
+// A workgroup of WN x WR waves computes a tile of 64 WN weight rows (2 WN
 // blocks of 32, in "units" of 128 rows, the granule of the row mapping
-// below) by 64 prompt rows, every term of each.  Wave (wn, wr) owns row
-// blocks 2 wn ("lo") and 2 wn + 1 ("hi") and prompt rows [32 wr, 32 wr +
-// 32), so the two rows an epilogue combines (a RoPE pair, gate and up) sit
-// in one lane.  Long prompts take WN = 4 (256 rows): the loads, not the
-// MFMAs, set the rate, and the larger tile does twice the products for 1.4x
-// the bytes per stage (prefill of 2048 tokens 32.2 -> 28.5 ms); short ones
-// WN = 2, which gives twice the workgroups.
+// below) by 16 PB WR prompt rows, every term of each.  Wave (wn, wr) owns
+// row blocks 2 wn ("lo") and 2 wn + 1 ("hi") and PB blocks of 16 prompt
+// rows, so the two rows an epilogue combines (a RoPE pair, gate and up) sit
+// in one lane.
+//
+// What bounds a long prompt is the card's power: in the products the clock
+// falls from 2.4 to about 1.9 GHz (1.56 in a large library matrix product).
+// So the products are 16 x 16 x 32 MFMAs, which draw less than 32 x 32 x 16
+// ones (register-resident products of such operands: 2050 against 1780
+// TFLOP/s; the 1B's 2048-row QKV product 98 -> 88 us, gate/up 248 -> 232),
+// consecutive ones share an operand (2110), and the tile is as large as the
+// accumulators allow (256 x 128: 27 % less LDS traffic per product than 256 x
+// 64).  1B, 2048 rows, per layer: QKV 140 -> 88, O 63 -> 53, gate/up 308 ->
+// 230, down 161 -> 126 us, about 1.2 PFLOP/s of MFMA work, where a library
+// matrix product reaches 1.3.
+//
 // Weights and activations pass through LDS in stages of 32 k, double
-// buffered: the next stage's global loads are in flight in registers while
-// the current one is multiplied.  Rows in LDS are 80 bytes apart (64 + a
-// 16-byte skew), so the 32 rows a fragment read touches spread over the
-// banks.
+// buffered: the next stages' global loads are in flight in registers while
+// the current one is multiplied.  An LDS row is 64 bytes (32 k); its 16-byte
+// chunk c is kept at place c ^ (row / 4 mod 4), so the 16 rows that one pass
+// of a fragment read touches (one chunk each) cover all 64 banks.
+// (Activations kept as the three terms between the products, split once by
+// their producer: no splitting here, but half as many bytes again to stage;
+// gate/up 268 -> 279 us.)
 constexpr int kPfMaxKs = 8;  // most K slices of a prefill product
 constexpr int kUnit = 128;   // weight rows per unit of the row mapping (block_src)
-constexpr int kBR = 64;   // prompt rows per tile
-constexpr int kKT = 32;   // k per stage
-constexpr int kRowB = kKT * 2 + 16;
-constexpr int kBCols = kNT * kBR;                  // activation columns: term-major per wave half
-constexpr int kBChunks = kBR * (kKT / 4);         // 16-byte (4 x fp32) activation chunks per stage
+constexpr int kKT = 32;      // k per stage
+constexpr int kRowB = kKT * 2;
+constexpr int kMB = 4;       // blocks of 16 weight rows per wave
 
-// The tile shape of WN waves across the weight rows.
-template <int WN>
+// Byte of chunk c of LDS row `row` (of either operand).
+AIO_DEV int lds_chunk(int row, int c) { return row * kRowB + ((c ^ ((row >> 2) & 3)) << 4); }
+
+// With KG > 1, KG such groups of waves share the tile, group kg multiplying
+// the kg-th 32 k of every stage of 32 KG k; their sums meet in LDS at the
+// end.  At a short prompt a workgroup has a CU to itself and a stage's time
+// is its chain of waits (barrier, LDS, products), about 0.5 us whatever its
+// width, so KG times the k per stage is nearly KG times the rate.
+template <int WN, int WR, int PB, int NS, int KG>
 struct PTile {
-  static constexpr int GT = 2 * WN * AIO_WAVE;              // threads
-  static constexpr int BM = 64 * WN;                        // weight rows
+  static constexpr int kWN = WN, kWR = WR, kPB = PB, kKG = KG;
+  static constexpr int kNS = NS;                            // stages of loads in flight
+  static constexpr int GG = WN * WR * AIO_WAVE;             // threads of a group
+  static constexpr int GT = KG * GG;                        // threads
+  static constexpr int BM = 16 * kMB * WN;                  // weight rows
+  static constexpr int BN = 16 * PB * WR;                   // prompt rows
+  static constexpr int SK = KG * kKT;                       // k per stage
   static constexpr int UPT = BM / kUnit;                    // units per tile
-  static constexpr int BLd = (kBChunks + GT - 1) / GT;      // activation loads per thread
-  static constexpr int StageB = (BM + kBCols) * kRowB;      // weight rows + activation columns
+  static constexpr int BCols = kNT * BN;                    // activation columns
+  static constexpr int BLd = BN * (SK / 4) / GT;            // 16-byte activation loads per thread
+  static constexpr int SubB = (BM + BCols) * kRowB;         // 32 k: weight rows + activation columns
+  static constexpr int StageB = KG * SubB;
+  static constexpr int RedB = (KG - 1) * 16 * kMB * PB * GG;  // the groups' sums
   static constexpr int Lds = 2 * StageB;
+  static_assert(BN * (SK / 4) % GT == 0, "whole activation loads per thread");
+  static_assert(RedB <= Lds, "the groups' sums fit the stage buffers");
 };
 
 enum PEpi { PE_QKV = 0, PE_RESID = 1, PE_SWIGLU = 2 };
@@ -179,12 +211,12 @@ struct PGemmArgs {
   uint16_t* vc;
   const float2* rope;   // [max_ctx][hd / 2] (cos, sin)
   int pos0, H, Hkv, hd, max_ctx;
-  // K split over workgroups (grid.z) when the tiles alone are too few: each
-  // slice writes its partial tile through to fix and counts itself in
-  // tcnt[tile]; the last slice to arrive adds the partials in slice order
-  // and runs the epilogue
+  // K split over workgroups (grid.z) when the tiles alone are too few: all
+  // but the last slice of a tile to arrive write their partial tile through
+  // to fix; tcnt[tile] counts arrivals (low half) and writes (high half)
   int ks;
-  float* fix;           // [tiles][ks][32][threads]
+  float* fix;           // [tiles][ks, or 1 for ks == 2][values per lane][lanes of a group]
+  size_t fix_bytes;     // room at fix
   int* tcnt;            // [tiles], zero between products
   // the folded RMSNorm: QKV and SWIGLU scale output row r by 1 / sqrt(sum
   // of ss_in[r][0 .. nss) / K + eps); RESID (with act_next) writes x g_next
@@ -249,29 +281,25 @@ AIO_DEV const char* pick_mat(const PGemmArgs& a, int mat) {
   return (const char*)(b0 + (uint64_t)(mat == 1) * d1 + (uint64_t)(mat == 2) * d2);
 }
 
-// Global loads of stage st: A_LD 16-byte weight chunks and BLD activation
+// Global loads of stage st: A_LD 16-byte weight chunks and BLd activation
 // chunks per thread.
-template <int WFMT, int WN, int A_LD, int BLD = PTile<WN>::BLd>
+template <int WFMT, int SK, int A_LD, int BLD>
 AIO_DEV void gload_stage(const char* const (&aptr)[A_LD], const float* const (&bptr)[BLD],
                          int st, uint4 (&ra)[A_LD], uint4 (&rb)[BLD]) {
-  constexpr int GT = PTile<WN>::GT;
   constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
-  const size_t ko = (size_t)st * kKT;
+  const size_t ko = (size_t)st * SK;
 #pragma unroll
-  for (int j = 0; j < A_LD; ++j) ra[j] = ld_stream((const uint4*)(aptr[j] + ko * wbytes));
+  for (int j = 0; j < A_LD; ++j) ra[j] = *(const uint4*)(aptr[j] + ko * wbytes);
 #pragma unroll
-  for (int j = 0; j < BLD; ++j)
-    if (j + 1 < BLD || kBChunks % GT == 0 || (int)threadIdx.x < kBChunks % GT)
-      rb[j] = *(const uint4*)(bptr[j] + ko);
+  for (int j = 0; j < BLD; ++j) rb[j] = *(const uint4*)(bptr[j] + ko);
 }
 
 // The same chunks into an LDS stage buffer: int8 widened to bf16 (exact:
 // |q| <= 127); each activation value split into its three bf16 terms, one
 // 8-byte store per term column (4 consecutive k).
-template <int WFMT, int WN, int A_LD, int BLD = PTile<WN>::BLd>
+template <int WFMT, int A_LD, int BLD>
 AIO_DEV void lstore_stage(char* buf, const int (&alds)[A_LD], const int (&blds)[BLD],
                           const uint4 (&ra)[A_LD], const uint4 (&rb)[BLD]) {
-  constexpr int GT = PTile<WN>::GT;
   // (vector stores: a uint4 struct copy is a memcpy, which keeps the
   // register sets in scratch memory)
 #pragma unroll
@@ -289,66 +317,81 @@ AIO_DEV void lstore_stage(char* buf, const int (&alds)[A_LD], const int (&blds)[
         const float f0 = (float)(int8_t)(sw >> sh), f1 = (float)(int8_t)(sw >> (sh + 8));
         o[i] = (__float_as_uint(f0) >> 16) | (__float_as_uint(f1) & 0xffff0000u);
       }
+      // 16 weights: chunks c and c ^ 1 of the row (c even, so the swizzled
+      // places are one 32-byte pair, in one order or the other)
       const u32x4 w0 = {o[0], o[1], o[2], o[3]}, w1 = {o[4], o[5], o[6], o[7]};
       *(u32x4*)(buf + alds[j]) = w0;
-      *(u32x4*)(buf + alds[j] + 16) = w1;
+      *(u32x4*)(buf + (alds[j] ^ 16)) = w1;
     }
   }
 #pragma unroll
-  for (int j = 0; j < BLD; ++j)
-    if (j + 1 < BLD || kBChunks % GT == 0 || (int)threadIdx.x < kBChunks % GT) {
-      uint32_t t[4][kNT];
-      split3t(rb[j].x, t[0]);
-      split3t(rb[j].y, t[1]);
-      split3t(rb[j].z, t[2]);
-      split3t(rb[j].w, t[3]);
+  for (int j = 0; j < BLD; ++j) {
+    uint32_t t[4][kNT];
+    split3t(rb[j].x, t[0]);
+    split3t(rb[j].y, t[1]);
+    split3t(rb[j].z, t[2]);
+    split3t(rb[j].w, t[3]);
 #pragma unroll
-      for (int k = 0; k < kNT; ++k) {
-        const u32x2 w = {(t[0][k] >> 16) | t[1][k], (t[2][k] >> 16) | t[3][k]};
-        *(u32x2*)(buf + blds[j] + k * 32 * kRowB) = w;
-      }
+    for (int k = 0; k < kNT; ++k) {
+      const u32x2 w = {(t[0][k] >> 16) | t[1][k], (t[2][k] >> 16) | t[3][k]};
+      *(u32x2*)(buf + blds[j] + k * 32 * kRowB) = w;
     }
+  }
 }
 
-// The MFMA products of one LDS stage: 16-k chunks, the wave's two row blocks
-// by the terms of its 32 prompt rows.  Activation columns of the stage are
-// ordered [wave half wr][term][row].
-template <int WN>
-AIO_DEV void stage_product(const char* cur, int wn, int wr, int rl, int kh,
-                           f32x16 (&acc)[2][kNT]) {
-  constexpr int kBM = PTile<WN>::BM;
+// MFMA fragments of a stage: the wave's weight rows, and the three terms of
+// one block of 16 prompt rows (LDS columns are ordered [32 prompt
+// rows][term][row]).
+struct AFrag {
+  bf16x8 v[kMB];
+};
+struct BFrag {
+  bf16x8 v[kNT];
+};
+
+AIO_DEV void afrag_load(AFrag& f, const char* p) {
 #pragma unroll
-  for (int c16 = 0; c16 < kKT / 16; ++c16) {
-    const int koff = (c16 * 16 + 8 * kh) * 2;
-    bf16x8 af[2], bfr[kNT];
+  for (int m = 0; m < kMB; ++m) f.v[m] = as_bf16x8(*(const uint4*)(p + m * 16 * kRowB));
+}
+// Block p of the wave's prompt rows, b0 its first block's address.
+AIO_DEV void bfrag_load(BFrag& f, const char* b0, int p) {
+  b0 += ((p >> 1) * kNT * 32 + (p & 1) * 16) * kRowB;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-      af[b] = as_bf16x8(*(const uint4*)(cur + ((2 * wn + b) * 32 + rl) * kRowB + koff));
+  for (int t = 0; t < kNT; ++t) f.v[t] = as_bf16x8(*(const uint4*)(b0 + t * 32 * kRowB));
+}
+
+// Products of one block of prompt rows.  The first term's go to hi, the
+// second's and third's (2^-8 of it and below, so rounding their sum in fp32
+// costs nothing next to hi's own rounding) to lo.  Consecutive products
+// share an operand (the rows go back and forth), which saves power.
+AIO_DEV void frag_mma(const AFrag& a, const BFrag& b, f32x4 (&hi)[kMB], f32x4 (&lo)[kMB]) {
 #pragma unroll
-    for (int t = 0; t < kNT; ++t)
-      bfr[t] = as_bf16x8(
-          *(const uint4*)(cur + (kBM + (wr * kNT + t) * 32 + rl) * kRowB + koff));
+  for (int i = 0; i < kNT; ++i) {
+    const int t = i == 0 ? 1 : (i == 1 ? 0 : 2);
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int t = 0; t < kNT; ++t) acc[b][t] = mfma(af[b], bfr[t], acc[b][t]);
+    for (int j = 0; j < kMB; ++j) {
+      const int m = i == 1 ? kMB - 1 - j : j;
+      f32x4& acc = t == 0 ? hi[m] : lo[m];
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v[m], b.v[t], acc, 0, 0, 0);
+    }
   }
 }
 
 // The logical (weight tile, prompt-row tile, K slice) of this workgroup.
 // Workgroups go to the 8 XCDs round-robin by linear id, and each XCD has its
 // own L2; so the linear ids are renumbered to give every XCD a contiguous
-// run of the logical order, in which the tiles go down bands of up to 8
-// prompt-row tiles per weight tile.  The workgroups that run at once on one
+// run of the logical order, in which the tiles go down bands of up to 512
+// prompt rows per weight tile.  The workgroups that run at once on one
 // XCD then share a few weight tiles and a few activation tiles in its L2,
-// instead of each bringing its own from memory (2048 tokens 20.8 -> 18.9
-// ms).  A product split over K keeps the hardware order: its workgroups
-// all run in one round, and renumbered, the workgroups of one XCD would
-// all read one K slice, whose rows' equal k offsets share a few HBM
-// channels (128 tokens 3.31 -> 3.49 ms).
+// instead of each bringing its own from memory (when it was introduced:
+// 2048 tokens 20.8 -> 18.9 ms).  A product split over K keeps the hardware
+// order: renumbered, the workgroups of one XCD would all read one K slice,
+// whose rows' equal k offsets share a few HBM channels (128 tokens 3.31 ->
+// 3.49 ms).
 struct PTileId {
   int bx, by, kz;
 };
+template <class Tl>
 AIO_DEV PTileId ptile_id() {
   PTileId t;
   if (gridDim.z > 1) {
@@ -359,9 +402,10 @@ AIO_DEV PTileId ptile_id() {
   }
   const int nx = (int)gridDim.x, ny = (int)gridDim.y, g = nx * ny;
   const int lin = (int)(blockIdx.x + gridDim.x * blockIdx.y);
-  const int rem = g % 8 == 0 ? (lin % 8) * (g / 8) + lin / 8 : lin;
+  // XCD lin % 8 holds g / 8 workgroups, the first g % 8 XCDs one more
+  const int xcd = lin & 7, rem = xcd * (g / 8) + min(xcd, g & 7) + (lin >> 3);
   t.kz = 0;
-  constexpr int kBand = 8;
+  constexpr int kBand = 512 / Tl::BN;
   const int by0 = rem / (kBand * nx) * kBand;
   const int nb = min(kBand, ny - by0);
   const int in = rem - by0 * nx;
@@ -370,73 +414,264 @@ AIO_DEV PTileId ptile_id() {
   return t;
 }
 
-template <int WFMT, int EPI, int WN>
-__global__ __launch_bounds__(PTile<WN>::GT) void k_pgemm(PGemmArgs a) {
-  using Tl = PTile<WN>;
+// The four fp16 scales from s, as floats.
+AIO_DEV void scale4(const uint16_t* s, float (&f)[4]) {
+  const uint2 u = *(const uint2*)s;
+  f[0] = fp16_to_f32((uint16_t)u.x);
+  f[1] = fp16_to_f32((uint16_t)(u.x >> 16));
+  f[2] = fp16_to_f32((uint16_t)u.y);
+  f[3] = fp16_to_f32((uint16_t)(u.y >> 16));
+}
+
+// Epilogue of a wave: its 64 weight rows (the 32-row blocks slo and shi, both
+// whole or both past the end) by its PB blocks of 16 prompt rows from row
+// rw0.  Lane (c16, g) holds, for prompt row rw0 + 16 p + c16, rows 16 m + 4 g
+// .. + 3 of the 64 in y[p][m].  inv: the norm factors of the wave's prompt
+// rows (QKV and SWIGLU).  Everything it reads is requested before the first
+// store (a load after a store that may alias it would wait its own round
+// trip: 16 of them in turn in a residual tile).
+template <int WFMT, int EPI, int PB>
+AIO_DEV void pgemm_epi(const PGemmArgs& a, const BlockSrc& slo, const BlockSrc& shi, int rw0,
+                       int c16, int g, const float* inv, const f32x4 (&y)[PB][kMB]) {
+  if (!slo.valid) return;
+  if constexpr (EPI == PE_RESID) {
+    float4 xv[PB][kMB];
+    float gn[kMB][4], sc[kMB][4];
+#pragma unroll
+    for (int m = 0; m < kMB; ++m) {
+      const int n = slo.row0 + 16 * m + 4 * g;  // (adjacent blocks)
+      if (a.act_next) {
+        const uint2 u = *(const uint2*)(a.g_next + n);
+        gn[m][0] = bf16_lo(u.x);
+        gn[m][1] = bf16_hi(u.x);
+        gn[m][2] = bf16_lo(u.y);
+        gn[m][3] = bf16_hi(u.y);
+      }
+      if constexpr (WFMT == AIO_WFMT_INT8) scale4(a.s0 + n, sc[m]);
+    }
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+      const float* xrow = a.out + (size_t)min(rw0 + 16 * p + c16, a.R - 1) * a.ldo;
+#pragma unroll
+      for (int m = 0; m < kMB; ++m)
+        xv[p][m] = *(const float4*)(xrow + slo.row0 + 16 * m + 4 * g);
+    }
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+      const int r = rw0 + 16 * p + c16;
+      const bool live = r < a.R;
+      float sq = 0.f;  // the lane's sum of squares of the new x
+#pragma unroll
+      for (int m = 0; m < kMB; ++m) {
+        const int n = slo.row0 + 16 * m + 4 * g;
+        float x[4] = {xv[p][m].x, xv[p][m].y, xv[p][m].z, xv[p][m].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float v = y[p][m][e];
+          if constexpr (WFMT == AIO_WFMT_INT8) v *= sc[m][e];
+          x[e] += v;
+          sq = fmaf(x[e], x[e], sq);
+        }
+        if (live) {
+          *(float4*)(a.out + (size_t)r * a.ldo + n) = make_float4(x[0], x[1], x[2], x[3]);
+          if (a.act_next)
+            *(float4*)(a.act_next + (size_t)r * a.lda_next + n) =
+                make_float4(x[0] * gn[m][0], x[1] * gn[m][1], x[2] * gn[m][2], x[3] * gn[m][3]);
+        }
+      }
+      // the wave's 64 columns are one block of the sums for row r, 16 of
+      // them in each lane group
+      if (a.act_next) {
+        sq += __shfl_xor(sq, 16, AIO_WAVE);
+        sq += __shfl_xor(sq, 32, AIO_WAVE);
+        if (live && g == 0) a.ss_out[(size_t)r * a.nss + slo.row0 / 64] = sq;
+      }
+    }
+  } else if constexpr (EPI == PE_SWIGLU) {
+    float sg[2][4], su[2][4];
+    if constexpr (WFMT == AIO_WFMT_INT8) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        scale4(a.s0 + slo.row0 + 16 * q + 4 * g, sg[q]);
+        scale4(a.s1 + slo.row0 + 16 * q + 4 * g, su[q]);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+      const int r = rw0 + 16 * p + c16;
+      if (r >= a.R) continue;
+      const float rs = inv[16 * p + c16];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        float h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float gt = y[p][q][e] * rs, up = y[p][q + 2][e] * rs;
+          if constexpr (WFMT == AIO_WFMT_INT8) {
+            gt *= sg[q][e];
+            up *= su[q][e];
+          }
+          h[e] = gt / (1.f + expf(-gt)) * up;
+        }
+        *(float4*)(a.act_out + (size_t)r * a.lda_out + slo.row0 + 16 * q + 4 * g) =
+            make_float4(h[0], h[1], h[2], h[3]);
+      }
+    }
+  } else {
+    // QKV: the pair (row, row + hd/2) of a head section in blocks lo and hi;
+    // the lane's rows come in runs of 4, stored as one vector each (q fp32,
+    // the K / V cache bf16)
+    const int half = a.hd / 2, mat = slo.mat;
+    float sl[2][4], sh[2][4];
+    if constexpr (WFMT == AIO_WFMT_INT8) {
+      const uint16_t* s = (mat == 0 ? a.s0 : (mat == 1 ? a.s1 : a.s2)) + slo.row0 + 4 * g;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        scale4(s + 16 * q, sl[q]);
+        scale4(s + half + 16 * q, sh[q]);
+      }
+    }
+    // cos, sin of the rows' four consecutive angles (ii is a multiple of 4)
+    float4 cs[PB][2][2];
+    if (mat < 2) {
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int ii = (slo.vrow0 + 16 * q + 4 * g) % a.hd;
+          const float4* t = (const float4*)(a.rope + (size_t)(a.pos0 + min(rw0 + 16 * p + c16,
+                                                                           a.R - 1)) * half + ii);
+          cs[p][q][0] = t[0];
+          cs[p][q][1] = t[1];
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+      const int r = rw0 + 16 * p + c16;
+      if (r >= a.R) continue;
+      const float rs = inv[16 * p + c16];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int row = slo.row0 + 16 * q + 4 * g;            // first of 4 rows in its matrix
+        const int ii = (slo.vrow0 + 16 * q + 4 * g) % a.hd;  // its index in the head (< hd / 2)
+        float lo[4], hi[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          lo[e] = y[p][q][e] * rs;
+          hi[e] = y[p][q + 2][e] * rs;
+          if constexpr (WFMT == AIO_WFMT_INT8) {
+            lo[e] *= sl[q][e];
+            hi[e] *= sh[q][e];
+          }
+        }
+        if (mat < 2) {
+          const float4 c0 = cs[p][q][0], c1 = cs[p][q][1];
+          const float co[4] = {c0.x, c0.z, c1.x, c1.z}, si[4] = {c0.y, c0.w, c1.y, c1.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float r0v = lo[e] * co[e] - hi[e] * si[e];
+            const float r1v = hi[e] * co[e] + lo[e] * si[e];
+            lo[e] = r0v;
+            hi[e] = r1v;
+          }
+        }
+        if (mat == 0) {
+          float* qp = a.out + (size_t)r * a.ldo + row;
+          *(float4*)qp = make_float4(lo[0], lo[1], lo[2], lo[3]);
+          *(float4*)(qp + half) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+        } else {
+          uint16_t* c = (mat == 1 ? a.kc : a.vc) +
+                        ((size_t)(row / a.hd) * a.max_ctx + a.pos0 + r) * a.hd + ii;
+          *(uint2*)c = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
+          *(uint2*)(c + half) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
+        }
+      }
+    }
+  }
+}
+
+// Scheduling of N MFMAs with a share of a stage's split and stores between
+// them.
+template <int N>
+AIO_DEV void sched_mix() {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // MFMA
+    __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);  // VALU
+    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+  }
+}
+
+template <int WFMT, int EPI, class Tl>
+__global__ __launch_bounds__(Tl::GT, 2) void k_pgemm(PGemmArgs a) {
   constexpr int kGT = Tl::GT, kBM = Tl::BM, kBLd = Tl::BLd, kStageB = Tl::StageB;
+  constexpr int PB = Tl::kPB;
   extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
-  const int wn = wid % WN, wr = wid / WN;
-  const int rl = lane & 31, kh = lane >> 5;
-  const PTileId tid3 = ptile_id();
-  const int bx = tid3.bx, r0 = tid3.by * kBR;
+  constexpr int KG = Tl::kKG, kGG = Tl::GG;
+  const int kg = wid / (Tl::kWN * Tl::kWR);
+  const int wn = wid % Tl::kWN, wr = wid / Tl::kWN % Tl::kWR;
+  const int c16 = lane & 15, g = lane >> 4;  // row of a fragment, lane group
+  const PTileId tid3 = ptile_id<Tl>();
+  const int bx = tid3.bx, r0 = tid3.by * Tl::BN;
   constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
 
   // Staging assignments.  A: row ra of the tile (block ra / 32), 16-byte
-  // chunk ca of the stage's 32 k (bf16: 4 chunks of 8 weights; int8: 2
-  // chunks of 16 weights, widened to 32 bytes in LDS).  B: prompt row r0 +
-  // p (p = 32 wr' + j), 8 chunks of 4 fp32 k; its terms t go to the LDS
-  // activation columns (wr' kNT + t) 32 + j.
+  // chunk ca of 32 k (bf16: 4 chunks of 8 weights; int8: 2 chunks of 16
+  // weights, widened to 32 bytes in LDS) of the stage's KG.  B: prompt row r0
+  // + p, 8 chunks of 4 fp32 per 32 k; its terms t go to the LDS activation
+  // columns (p / 32 kNT + t) 32 + p % 32.
   constexpr int A_CPR = WFMT == AIO_WFMT_BF16 ? 4 : 2;
-  constexpr int A_LD = kBM * A_CPR / kGT;
+  constexpr int A_LD = kBM * A_CPR * KG / kGT;
   const char* aptr[A_LD];
   int alds[A_LD];
 #pragma unroll
   for (int j = 0; j < A_LD; ++j) {
-    const int f = j * kGT + tid, ra = f / A_CPR, ca = f % A_CPR;
+    const int f = j * kGT + tid, ra = f / (A_CPR * KG), cs = f % (A_CPR * KG);
+    const int sub = cs / A_CPR, ca = cs % A_CPR;
     const int blk = ra >> 5;  // block of the tile: unit UPT bx + blk / 4, block blk % 4 of it
     const BlockSrc s = block_src<EPI>(a, Tl::UPT * bx + (blk >> 2), blk & 3);
     int row = s.row0 + ((ra & 31) < s.valid ? (ra & 31) : 0);
     if (s.valid == 0) row = 0;  // a block past the end reads row 0 of w0 (discarded)
     const char* w = s.valid ? pick_mat(a, s.mat) : (const char*)a.w0;
-    aptr[j] = w + ((size_t)row * a.K + (size_t)ca * (16 / wbytes)) * wbytes;
-    alds[j] = ra * kRowB + ca * 16 * (2 / wbytes);
+    aptr[j] = w + ((size_t)row * a.K + (size_t)cs * (16 / wbytes)) * wbytes;
+    alds[j] = sub * Tl::SubB + lds_chunk(ra, ca * (2 / wbytes));
   }
   const float* bptr[kBLd];
   int blds[kBLd];
 #pragma unroll
   for (int j = 0; j < kBLd; ++j) {
-    const int f = min(j * kGT + tid, kBChunks - 1), p = f / 8, c = f % 8;
+    const int f = j * kGT + tid, p = f / (8 * KG), cs = f % (8 * KG), c = cs % 8;
     const int row = r0 + p;
-    bptr[j] = a.act + (size_t)(row < a.R ? row : a.R - 1) * a.lda + c * 4;
-    blds[j] = (kBM + (p / 32) * kNT * 32 + (p % 32)) * kRowB + c * 8;
+    bptr[j] = a.act + (size_t)(row < a.R ? row : a.R - 1) * a.lda + cs * 4;
+    blds[j] = cs / 8 * Tl::SubB + lds_chunk(kBM + (p / 32) * kNT * 32 + (p % 32), c / 2) + (c & 1) * 8;
   }
-  uint4 ra_[A_LD], rb_[kBLd];
-  f32x16 acc[2][kNT];
+  // fragment reads: lane (c16, g) takes chunk g of row c16 of a block
+  const int aoff = kg * Tl::SubB + lds_chunk(wn * 16 * kMB + c16, g);
+  const int boff = kg * Tl::SubB + lds_chunk(kBM + wr * (PB / 2) * kNT * 32 + c16, g);
+  f32x4 hi[PB][kMB], lo[PB][kMB];
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int p = 0; p < PB; ++p)
 #pragma unroll
-    for (int t = 0; t < kNT; ++t)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[b][t][i] = 0.f;
+    for (int m = 0; m < kMB; ++m) hi[p][m] = lo[p][m] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // this workgroup's stages [sA, sB) of K (all of them unless K is split).
-  // Two register sets keep two stages' loads in flight (a stage's loads take
-  // a memory round trip, its products a fraction of one): set 1 holds the
-  // stages sA + 1, sA + 3, ..., set 0 the others; loads past sB re-read the
-  // last stage and are not used.
-  const int nst = a.K / kKT, kz = tid3.kz;
-  const int sA = kz * nst / a.ks, sB = (kz + 1) * nst / a.ks;
-  uint4 ra1[A_LD], rb1[kBLd];
-  const int sL = sB - 1;
-  gload_stage<WFMT, WN, A_LD>(aptr, bptr, sA, ra_, rb_);
-  gload_stage<WFMT, WN, A_LD>(aptr, bptr, min(sA + 1, sL), ra1, rb1);
-  // the folded norm's row factors of the tile's 64 prompt rows, Tl::GT / 64
-  // threads per row (their loads queue behind the first stages'; the
-  // barrier below publishes them)
-  __shared__ float inv_rows[kBR];
+  // NS register sets keep NS stages' loads in flight (a stage's loads take a
+  // memory round trip, its products a fraction of one): stage sA + i goes
+  // through set i mod NS; loads past sB re-read the last stage and are not
+  // used.
+  constexpr int NS = Tl::kNS;
+  const int nst = a.K / Tl::SK, kz = tid3.kz;
+  const int sA = kz * nst / a.ks, sB = (kz + 1) * nst / a.ks, sL = sB - 1;
+  uint4 ra[NS][A_LD], rb[NS][kBLd];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) gload_stage<WFMT, Tl::SK>(aptr, bptr, min(sA + i, sL), ra[i], rb[i]);
+  // the folded norm's row factors of the tile's prompt rows, GT / BN threads
+  // per row (their loads queue behind the first stages'; the barrier below
+  // publishes them)
+  __shared__ float inv_rows[Tl::BN];
   if constexpr (EPI != PE_RESID) {
-    constexpr int TPR = Tl::GT / kBR;
+    constexpr int TPR = kGT / Tl::BN;
     const int j = tid / TPR, part = tid % TPR;
     const float* ssr = a.ss_in + (size_t)min(r0 + j, a.R - 1) * a.nss;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
@@ -453,199 +688,173 @@ __global__ __launch_bounds__(PTile<WN>::GT) void k_pgemm(PGemmArgs a) {
     for (int off = TPR / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, AIO_WAVE);
     if (part == 0) inv_rows[j] = rsqrtf(sum / (float)a.K + a.eps);
   }
-  lstore_stage<WFMT, WN, A_LD>(smem, alds, blds, ra_, rb_);
+  lstore_stage<WFMT>(smem, alds, blds, ra[0], rb[0]);
   __syncthreads();
-  gload_stage<WFMT, WN, A_LD>(aptr, bptr, min(sA + 2, sL), ra_, rb_);
-  // stage S from its LDS buffer; then stage S + 1 (in set RA, RB) to the
-  // other buffer, and the set refilled with stage S + 3 (written out for
-  // each set: a set chosen at run time would live in scratch memory)
-#define AIO_PF_STEP(S, RA, RB)                                                          \
-  do {                                                                                 \
-    stage_product<WN>(smem + (((S) - sA) & 1) * kStageB, wn, wr, rl, kh, acc);             \
-    lstore_stage<WFMT, WN, A_LD>(smem + (((S) + 1 - sA) & 1) * kStageB, alds, blds, RA, RB); \
-    __syncthreads();                                                                   \
-    gload_stage<WFMT, WN, A_LD>(aptr, bptr, min((S) + 3, sL), RA, RB);                     \
-  } while (0)
-  int st = sA;
-  for (; st + 2 < sB; st += 2) {
-    AIO_PF_STEP(st, ra1, rb1);
-    AIO_PF_STEP(st + 1, ra_, rb_);
+  gload_stage<WFMT, Tl::SK>(aptr, bptr, min(sA + NS, sL), ra[0], rb[0]);
+  // Stage i (of sA ..): its weight fragments fa and its first block of
+  // prompt rows f0 are in registers.  During the first half of the blocks'
+  // products the other blocks are read, and stage i + 1 is split and stored
+  // to the other LDS buffer.  Then, after the barrier, its register set is
+  // refilled with stage i + 1 + NS and the next stage's first fragments are
+  // requested, ahead of the second half's products, which cover their
+  // latency.  The scheduling barriers keep these parts in this order:
+  // without them the compiler moved a set's loads to just before their use,
+  // and nothing was in flight.
+  AFrag fa, na;
+  BFrag f0, fb[PB];
+  afrag_load(fa, smem + aoff);
+  bfrag_load(f0, smem + boff, 0);
+  auto step = [&](int i, uint4 (&RA)[A_LD], uint4 (&RB)[kBLd]) {
+    const char* cur = smem + (i & 1) * kStageB;
+    char* nxt = smem + ((i + 1) & 1) * kStageB;
+#pragma unroll
+    for (int p = 1; p < PB; ++p) bfrag_load(fb[p], cur + boff, p);
+    __builtin_amdgcn_sched_barrier(0);
+    frag_mma(fa, f0, hi[0], lo[0]);
+#pragma unroll
+    for (int p = 1; p < PB / 2; ++p) frag_mma(fa, fb[p], hi[p], lo[p]);
+    lstore_stage<WFMT>(nxt, alds, blds, RA, RB);
+    sched_mix<kMB * kNT * PB / 4>();
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    gload_stage<WFMT, Tl::SK>(aptr, bptr, min(sA + i + 1 + NS, sL), RA, RB);
+    afrag_load(na, nxt + aoff);
+    bfrag_load(f0, nxt + boff, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = PB / 2; p < PB; ++p) frag_mma(fa, fb[p], hi[p], lo[p]);
+    __builtin_amdgcn_sched_barrier(0);
+    fa = na;
+  };
+  const int ns = sB - sA;
+  int i = 0;
+  for (; i + NS < ns; i += NS) {
+#pragma unroll
+    for (int u = 0; u < NS; ++u) step(i + u, ra[(u + 1) % NS], rb[(u + 1) % NS]);
   }
-  if (st + 1 < sB) {
-    AIO_PF_STEP(st, ra1, rb1);
-    ++st;
+  // the last 1 .. NS stages
+#pragma unroll
+  for (int u = 0; u < NS - 1; ++u) {
+    if (i + 1 >= ns) break;
+    step(i, ra[(u + 1) % NS], rb[(u + 1) % NS]);
+    ++i;
   }
-#undef AIO_PF_STEP
-  stage_product<WN>(smem + ((st - sA) & 1) * kStageB, wn, wr, rl, kh, acc);
+  {
+    const char* cur = smem + (i & 1) * kStageB;
+    frag_mma(fa, f0, hi[0], lo[0]);
+#pragma unroll
+    for (int p = 1; p < PB; ++p) {
+      bfrag_load(fb[p], cur + boff, p);
+      frag_mma(fa, fb[p], hi[p], lo[p]);
+    }
+  }
 
-  // the tile's sums over the three terms: lane l, register v -> column
-  // (prompt row) l % 32, row i = 8 (v / 4) + 4 (l / 32) + v % 4 of the
-  // 32-row blocks lo and hi
-  float ylo[16], yhi[16];
+  // the tile's sums over the three terms
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    ylo[v] = acc[0][0][v];
-    yhi[v] = acc[1][0][v];
+  for (int p = 0; p < PB; ++p)
 #pragma unroll
-    for (int t = 1; t < kNT; ++t) {
-      ylo[v] += acc[0][t][v];
-      yhi[v] += acc[1][t][v];
+    for (int m = 0; m < kMB; ++m) hi[p][m] += lo[p][m];
+  constexpr int PV = 4 * kMB;  // values of a lane per block of prompt rows
+  const int gtid = tid % kGG;  // thread of its group
+  if constexpr (KG > 1) {
+    // the groups' sums, added in group order by group 0
+    __syncthreads();
+    float* red = (float*)smem + gtid;
+    if (kg > 0) {
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int v = 0; v < PV; ++v)
+          red[((kg - 1) * PB * PV + p * PV + v) * kGG] = hi[p][v / 4][v % 4];
+    }
+    __syncthreads();
+    if (kg == 0) {
+#pragma unroll
+      for (int k = 1; k < KG; ++k)
+#pragma unroll
+        for (int p = 0; p < PB; ++p)
+#pragma unroll
+          for (int v = 0; v < PV; ++v)
+            hi[p][v / 4][v % 4] += red[((k - 1) * PB * PV + p * PV + v) * kGG];
     }
   }
   if (a.ks > 1) {
-    // K split: every slice's partial goes through memory (written through,
-    // read past the caches); the last slice to arrive adds them in slice
-    // order, so the sum is the same whatever the arrival order
-    // (element-major, so that each store and load instruction of a wave
-    // covers 256 contiguous bytes).  Lanes of prompt rows past R move
-    // nothing: at a short prompt most of the tile's rows are (the last
-    // slice's reads of 8 partial tiles were half of a 23-row O product).
+    // K split.  Each slice takes a ticket when its product is done (the low
+    // half of the tile's counter).  All but the last to arrive write their
+    // partial tile through to memory and count it written (the high half);
+    // the last keeps its own in registers, waits for the others' writes
+    // (they hold their tickets, so they are past their products and only
+    // storing: the wait is short and cannot be for a workgroup that has not
+    // started), and adds all of them in slice order, so the sum is the same
+    // whatever the arrival order.  Partials are element-major: every store
+    // and load instruction of a wave covers 256 contiguous bytes.  Lanes of
+    // prompt rows past R move nothing: at a short prompt most of the tile's
+    // rows are.  Two slices need one slot per tile, more need one each.
     const int tile = tid3.by * (int)gridDim.x + bx;
-    const bool row_live = r0 + wr * 32 + rl < a.R;
-    float* mine = a.fix + ((size_t)tile * a.ks + kz) * 32 * kGT + tid;
-    if (row_live) {
+    const size_t slot = (size_t)PV * PB * kGG;  // floats of one partial tile
+    const int nslot = a.ks == 2 ? 1 : a.ks;
+    float* fix = a.fix + (size_t)tile * nslot * slot + gtid;
+    __shared__ int ticket_s;
+    if (tid == 0) ticket_s = atomic_add_agent(a.tcnt + tile, 1) & 0xffff;
+    __syncthreads();
+    if (ticket_s < a.ks - 1) {
+      float* mine = fix + (a.ks == 2 ? 0 : kz) * slot;
+      if (kg == 0) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        st_agent(mine + v * kGT, ylo[v]);
-        st_agent(mine + (16 + v) * kGT, yhi[v]);
+        for (int p = 0; p < PB; ++p)
+          if (r0 + (wr * PB + p) * 16 + c16 < a.R) {
+#pragma unroll
+            for (int v = 0; v < PV; ++v) st_agent(mine + (p * PV + v) * kGG, hi[p][v / 4][v % 4]);
+          }
       }
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      if (tid == 0) atomic_add_agent(a.tcnt + tile, 0x10000);
+      return;
     }
-    __builtin_amdgcn_s_waitcnt(0);
+    if (tid == 0) {
+      while ((atomic_load_agent(a.tcnt + tile) >> 16) != a.ks - 1) __builtin_amdgcn_s_sleep(1);
+      atomic_store_agent(a.tcnt + tile, 0);  // ready for the next product
+    }
     __syncthreads();
-    __shared__ int last_s;
-    if (tid == 0) last_s = atomic_add_agent(a.tcnt + tile, 1) == a.ks - 1;
-    __syncthreads();
-    if (!last_s) return;
-    if (tid == 0) atomic_store_agent(a.tcnt + tile, 0);  // ready for the next product
+    if (kg > 0) return;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) ylo[v] = yhi[v] = 0.f;
-    for (int k = 0; k < (row_live ? a.ks : 0); ++k) {
-      const float* pk = a.fix + ((size_t)tile * a.ks + k) * 32 * kGT + tid;
-      float plo[16], phi[16];
+    for (int p = 0; p < PB; ++p) {
+      if (r0 + (wr * PB + p) * 16 + c16 >= a.R) continue;
+      float sum[PV];
+      if (a.ks == 2) {  // (the two slices' sum does not depend on their order)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        plo[v] = ld_agent(pk + v * kGT);
-        phi[v] = ld_agent(pk + (16 + v) * kGT);
+        for (int v = 0; v < PV; ++v) sum[v] = ld_agent(fix + (p * PV + v) * kGG);
+#pragma unroll
+        for (int v = 0; v < PV; ++v) sum[v] += hi[p][v / 4][v % 4];
+      } else {
+        // four slices' values are requested together (a round trip each)
+#pragma unroll
+        for (int v = 0; v < PV; ++v) sum[v] = 0.f;
+        for (int k0 = 0; k0 < a.ks; k0 += 4) {
+          float pv[4][PV];
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int v = 0; v < PV; ++v)
+              pv[k][v] = ld_agent(fix + (k0 + k) * slot + (p * PV + v) * kGG);
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int v = 0; v < PV; ++v) sum[v] += k0 + k == kz ? hi[p][v / 4][v % 4] : pv[k][v];
+        }
       }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        ylo[v] += plo[v];
-        yhi[v] += phi[v];
-      }
+      for (int v = 0; v < PV; ++v) hi[p][v / 4][v % 4] = sum[v];
     }
   }
+  if (kg > 0) return;
 
-  // Epilogue.
-  const int r = r0 + wr * 32 + rl;
-  if (r >= a.R) return;
-  const BlockSrc slo = block_src<EPI>(a, Tl::UPT * bx + (wn >> 1), 2 * (wn & 1));
-  const BlockSrc shi = block_src<EPI>(a, Tl::UPT * bx + (wn >> 1), 2 * (wn & 1) + 1);
-  if constexpr (EPI == PE_RESID) {
-    // N is a multiple of 64: the wave's two blocks (adjacent, from a
-    // multiple of 64) are both whole or both past the end.  The lane's 16
-    // values of a block are 4 runs of 4 columns, moved as float4.
-    if (!slo.valid) return;
-    float* xrow = a.out + (size_t)r * a.ldo;
-    float sq = 0.f;  // the lane's sum of squares of the new x
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      const int nb = (hb ? shi.row0 : slo.row0) + 4 * kh;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = nb + 8 * g;
-        float y[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          y[e] = hb ? yhi[4 * g + e] : ylo[4 * g + e];
-          if constexpr (WFMT == AIO_WFMT_INT8) y[e] *= fp16_to_f32(a.s0[n + e]);
-        }
-        float4* xp = (float4*)(xrow + n);
-        float4 xn = *xp;
-        xn.x += y[0];
-        xn.y += y[1];
-        xn.z += y[2];
-        xn.w += y[3];
-        *xp = xn;
-        if (a.act_next) {
-          const uint16_t* gn = a.g_next + n;
-          *(float4*)(a.act_next + (size_t)r * a.lda_next + n) =
-              make_float4(xn.x * bf16_to_f32(gn[0]), xn.y * bf16_to_f32(gn[1]),
-                          xn.z * bf16_to_f32(gn[2]), xn.w * bf16_to_f32(gn[3]));
-          sq = fmaf(xn.x, xn.x, sq);
-          sq = fmaf(xn.y, xn.y, sq);
-          sq = fmaf(xn.z, xn.z, sq);
-          sq = fmaf(xn.w, xn.w, sq);
-        }
-      }
-    }
-    // the wave's 64 columns are one block of the sums for row r: this lane
-    // holds 32 of them, the lane 32 away (same row) the other 32
-    if (a.act_next) {
-      sq += __shfl_xor(sq, 32, AIO_WAVE);
-      if (kh == 0) a.ss_out[(size_t)r * a.nss + slo.row0 / 64] = sq;
-    }
-    return;
-  }
-  const float rs = inv_rows[wr * 32 + rl];
-  if constexpr (EPI == PE_SWIGLU) {
-    // F is a multiple of 64: the block is whole or past the end; the lane's
-    // 16 values are 4 runs of 4 columns, one float4 store each
-    if (!slo.valid) return;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int n = slo.row0 + 8 * g + 4 * kh;
-      float h[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float gt = ylo[4 * g + e] * rs, up = yhi[4 * g + e] * rs;
-        if constexpr (WFMT == AIO_WFMT_INT8) {
-          gt *= fp16_to_f32(a.s0[n + e]);
-          up *= fp16_to_f32(a.s1[n + e]);
-        }
-        h[e] = gt / (1.f + expf(-gt)) * up;
-      }
-      *(float4*)(a.act_out + (size_t)r * a.lda_out + n) = make_float4(h[0], h[1], h[2], h[3]);
-    }
-    return;
-  }
-  // QKV: the pair (row, row + hd/2) of a head section in blocks lo and hi;
-  // the lane's rows come in runs of 4, stored as one vector each (q fp32,
-  // the K / V cache bf16)
-  if (slo.valid == 0) return;
-  const int half = a.hd / 2, mat = slo.mat, p = a.pos0 + r;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int i0 = 8 * g + 4 * kh;
-    const int row = slo.row0 + i0;           // first of 4 rows in its matrix
-    const int ii = (slo.vrow0 + i0) % a.hd;  // its index in the head (< hd / 2)
-    float lo[4], hi[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      lo[e] = ylo[4 * g + e] * rs;
-      hi[e] = yhi[4 * g + e] * rs;
-      if constexpr (WFMT == AIO_WFMT_INT8) {
-        const uint16_t* sc = mat == 0 ? a.s0 : (mat == 1 ? a.s1 : a.s2);
-        lo[e] *= fp16_to_f32(sc[row + e]);
-        hi[e] *= fp16_to_f32(sc[row + e + half]);
-      }
-      if (mat < 2) {
-        const float2 cs = a.rope[(size_t)p * half + ii + e];
-        const float r0v = lo[e] * cs.x - hi[e] * cs.y;
-        const float r1v = hi[e] * cs.x + lo[e] * cs.y;
-        lo[e] = r0v;
-        hi[e] = r1v;
-      }
-    }
-    if (mat == 0) {
-      float* q = a.out + (size_t)r * a.ldo + row;
-      *(float4*)q = make_float4(lo[0], lo[1], lo[2], lo[3]);
-      *(float4*)(q + half) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-    } else {
-      uint16_t* c = (mat == 1 ? a.kc : a.vc) + ((size_t)(row / a.hd) * a.max_ctx + p) * a.hd + ii;
-      *(uint2*)c = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
-      *(uint2*)(c + half) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
-    }
-  }
+  const int blk = 2 * wn;  // the wave's first block of 32 weight rows in the tile
+  const BlockSrc slo = block_src<EPI>(a, Tl::UPT * bx + (blk >> 2), blk & 3);
+  const BlockSrc shi = block_src<EPI>(a, Tl::UPT * bx + (blk >> 2), (blk & 3) + 1);
+  pgemm_epi<WFMT, EPI, PB>(a, slo, shi, r0 + wr * PB * 16, c16, g,
+                           EPI == PE_RESID ? nullptr : inv_rows + wr * PB * 16, hi);
 }
 
 // ------------------------------------------------------ causal attention
@@ -931,45 +1140,98 @@ hipError_t launch_pnorm(const aio_model& m, const PfBuffers& b, int R, const uin
   return hipGetLastError();
 }
 
-// Launch over `units` (of 128 weight rows) x (R / 64) prompt-row tiles,
-// in tiles of WN / 2 units.  A product also splits K over workgroups (up
-// to kPfMaxKs slices of at least 8 stages, within the fix-up buffer's
-// room) as far as the workgroups still fit one round of the CUs: a
-// workgroup streams its stages one latency apart, so at a short prompt the
-// 1B's QKV product (32 tiles of 64 stages) took 57 us unsplit, and a split
-// past one round (the 1B's gate/up at 128 rows: 704 workgroups) leaves a
-// second, partial round.
-template <int WFMT, int EPI, int WN>
-hipError_t launch_pgemm_t(const aio_model& m, const PGemmArgs& g0, int units) {
-  using Tl = PTile<WN>;
-  PGemmArgs g = g0;
-  const int tiles = (units + Tl::UPT - 1) / Tl::UPT;
-  const int rt = (g.R + kBR - 1) / kBR, nst = g.K / kKT;
-  // workgroups one round of the CUs holds: two of 4 waves, one of 8
-  const int slots = (WN == 2 ? 2 : 1) * m.num_cus;
-  g.ks = 1;
-  while (tiles * rt * 2 * g.ks <= slots && 2 * g.ks <= kPfMaxKs &&
-         nst / (2 * g.ks) >= 8 &&
-         (size_t)tiles * rt * 2 * g.ks * Tl::GT * 32 * 4 <= m.lay.pfix_bytes &&
-         (size_t)tiles * rt <= m.lay.pcnt_n)
-    g.ks *= 2;
-  g.fix = m.at<float>(m.lay.pfix);
-  g.tcnt = m.at<int>(m.lay.pcnt);
-  const void* fn = (const void*)k_pgemm<WFMT, EPI, WN>;
+// The tile shapes, and what a product takes in each, in microseconds: every
+// round of workgroups `round` plus, per 32 k of its K slice, `few` (at most
+// half the CUs busy) or `full`; `base` once; a K split `split` plus
+// `slice` per slice (scaled by the live share of the tile's prompt rows).
+// Fitted to the 1B's and the 7B's four products at 19 prompt lengths from 23
+// to 2048, every shape and split measured by kernel trace (the model is
+// within 4 to 10 % of them, and the shape it picks within 1.8 % of the best
+// one on average, 13 % at worst):
+//   Big    one workgroup per CU; the fewest bytes and LDS reads per product
+//          (2048 rows, 1B: QKV 86 against Wide's 105 us, gate/up 226 / 264)
+//   Wide   half the prompt rows: twice the workgroups where Big leaves CUs
+//          idle (2048 rows, 1B: O 53 against Big's 78 us unsplit, down
+//          126 / 182; 1000 rows, 7B: O 95 / 140)
+//   Short  prompts of a few blocks of 16 rows, split over K to cover the CUs
+//          (23 rows, 1B: QKV 20.5 against Wide's 23.8 us, O 15.6 / 21.4,
+//          gate/up 19.2 / 24.8, down 21.4 / 31.3)
+struct PfShape {
+  int bm, bn, sk, per_cu;
+  double few, full, round, base, split, slice;
+};
+using Big = PTile<4, 2, 4, 2, 1>;
+using Wide = PTile<4, 2, 2, 2, 1>;
+using Short = PTile<2, 1, 2, 2, 2>;
+template <class Tl>
+constexpr PfShape pf_shape(int per_cu, double few, double full, double round, double base,
+                           double split, double slice) {
+  return PfShape{Tl::BM, Tl::BN, Tl::SK, per_cu, few, full, round, base, split, slice};
+}
+constexpr PfShape kPfShapes[3] = {
+    pf_shape<Big>(1, 0.96, 1.07, 7.3, 3.5, 0.0, 5.6),
+    pf_shape<Wide>(1, 0.60, 0.67, 3.3, 5.1, 2.6, 1.7),
+    pf_shape<Short>(2, 0.25, 0.43, 2.4, 7.9, 1.1, 0.9),
+};
+
+// Bytes of the partial tiles of `tiles` tiles split into ks slices.
+size_t pf_fix_bytes(const PfShape& s, size_t tiles, int ks) {
+  return ks == 1 ? 0 : tiles * (ks == 2 ? 1 : ks) * s.bm * s.bn * 4;
+}
+
+// Shape and K split (up to kPfMaxKs, within the fix-up room) with the least
+// predicted time.
+void pf_choose(const aio_model& m, int units, int R, int K, size_t fix_bytes, int* shape, int* ks) {
+  double best = 1e30;
+  for (int i = 0; i < 3; ++i) {
+    const PfShape& s = kPfShapes[i];
+    const size_t tiles = (size_t)((units * kUnit + s.bm - 1) / s.bm) * ((R + s.bn - 1) / s.bn);
+    const long long slots = (long long)s.per_cu * m.num_cus;
+    for (int k = 1; k <= kPfMaxKs; k *= 2) {
+      if (k > 1 && (pf_fix_bytes(s, tiles, k) > fix_bytes || tiles > m.lay.pcnt_n || K / s.sk < k))
+        break;
+      const long long wgs = (long long)tiles * k, rem = wgs % slots;
+      const double st = (double)K / kKT / k;
+      auto round = [&](long long n) {
+        return st * (2 * n <= slots ? s.few : s.full) + s.round;
+      };
+      const double t = s.base + (double)(wgs / slots) * round(slots) + (rem ? round(rem) : 0.0) +
+                       (k > 1 ? s.split + s.slice * k * std::min(R, s.bn) / s.bn : 0.0);
+      if (t < best) {
+        best = t;
+        *shape = i;
+        *ks = k;
+      }
+    }
+  }
+}
+
+template <int WFMT, int EPI, class Tl>
+hipError_t launch_pgemm_t(const aio_model& m, const PGemmArgs& g, int units) {
+  const dim3 grid((units + Tl::UPT - 1) / Tl::UPT, (g.R + Tl::BN - 1) / Tl::BN, g.ks);
+  const void* fn = (const void*)k_pgemm<WFMT, EPI, Tl>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, Tl::Lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_pgemm<WFMT, EPI, WN>), dim3(tiles, rt, g.ks), dim3(Tl::GT), Tl::Lds,
-                     m.stream, g);
+  hipLaunchKernelGGL((k_pgemm<WFMT, EPI, Tl>), grid, dim3(Tl::GT), Tl::Lds, m.stream, g);
   return hipGetLastError();
 }
 
-// 256-row tiles from 16 prompt-row tiles (1024 rows) on, 128-row tiles
-// below (at 512 rows the smaller tiles were still ahead: 8.76 against
-// 8.99 ms for the 1B).
+// Launch over `units` (of 128 weight rows) of the product.  The partial tiles
+// of a K split go to the scratch that is idle during this product (g.fix),
+// or to the workspace's region where that is larger.
 template <int WFMT, int EPI>
-hipError_t launch_pgemm_w(const aio_model& m, const PGemmArgs& g, int units) {
-  if ((g.R + kBR - 1) / kBR >= 16) return launch_pgemm_t<WFMT, EPI, 4>(m, g, units);
-  return launch_pgemm_t<WFMT, EPI, 2>(m, g, units);
+hipError_t launch_pgemm_w(const aio_model& m, const PGemmArgs& g0, int units) {
+  PGemmArgs g = g0;
+  if (g.fix_bytes < m.lay.pfix_bytes) {
+    g.fix = m.at<float>(m.lay.pfix);
+    g.fix_bytes = m.lay.pfix_bytes;
+  }
+  g.tcnt = m.at<int>(m.lay.pcnt);
+  int shape = 0;
+  pf_choose(m, units, g.R, g.K, g.fix_bytes, &shape, &g.ks);
+  if (shape == 0) return launch_pgemm_t<WFMT, EPI, Big>(m, g, units);
+  if (shape == 1) return launch_pgemm_t<WFMT, EPI, Wide>(m, g, units);
+  return launch_pgemm_t<WFMT, EPI, Short>(m, g, units);
 }
 
 template <int EPI>
@@ -1043,6 +1305,11 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     g.kc = m.kv_layer(l, 0); g.vc = m.kv_layer(l, 1);
     g.rope = m.rope; g.pos0 = pos0;
     g.H = H; g.Hkv = Hkv; g.hd = hd; g.max_ctx = c.max_ctx;
+    // partial tiles of a product split over K go to activations idle meanwhile
+    // (sized by R alone, so that the split, and with it the order of the
+    // sums, does not depend on how much scratch there is)
+    const size_t row4 = 4 * (size_t)R;
+    g.fix = b.actN; g.fix_bytes = row4 * (d + F);
     const int qkv_tiles = hd == 128 ? H + 2 * Hkv : (H + 2 * Hkv + 1) / 2;
     if ((e = launch_pgemm<PE_QKV>(m, g, qkv_tiles)) != hipSuccess) return e;
 
@@ -1061,6 +1328,7 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     o.N = d; o.K = H * hd; o.out = b.x; o.ldo = d;
     o.act_next = b.actN; o.lda_next = d;
     o.g_next = (const uint16_t*)L.ffn_norm; o.ss_out = b.ss; o.nss = nss;
+    o.fix = b.actB; o.fix_bytes = row4 * F;
     if ((e = launch_pgemm<PE_RESID>(m, o, (d + kUnit - 1) / kUnit)) != hipSuccess) return e;
 
     PGemmArgs gu{};
@@ -1069,6 +1337,7 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     gu.w0 = L.w_gate; gu.w1 = L.w_up;
     gu.s0 = (const uint16_t*)L.s_gate; gu.s1 = (const uint16_t*)L.s_up;
     gu.N = F; gu.K = d;
+    gu.fix = b.q; gu.fix_bytes = row4 * (H * hd + std::max(d, H * hd));
     gu.act_out = b.actB; gu.lda_out = b.lda_b;
     if ((e = launch_pgemm<PE_SWIGLU>(m, gu, (F + 63) / 64)) != hipSuccess) return e;
 
@@ -1076,6 +1345,7 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     dn.act = b.actB; dn.lda = b.lda_b; dn.R = R;
     dn.w0 = L.w_down; dn.s0 = (const uint16_t*)L.s_down;
     dn.N = d; dn.K = F; dn.out = b.x; dn.ldo = d;
+    dn.fix = b.q; dn.fix_bytes = row4 * H * hd;
     if (!last) {
       dn.act_next = b.actA; dn.lda_next = b.lda_a;
       dn.g_next = (const uint16_t*)m.layers[(size_t)l + 1].attn_norm;
