@@ -891,22 +891,21 @@ struct AttnLds {
   static constexpr int BYTES = QBYTES + TAIL;
 };
 
-// Key of element e (0..7) of lane half kh's softmax weights in 16-key chunk
-// c2.  The weights reach the P V product as the B operand straight from the
-// score tile's registers: score register v = 8 c2 + e holds key
-// 8 (v / 4) + 4 kh + v % 4, so the A fragment (V^T) gathers the value rows
-// of those keys.
-AIO_DEV int pkey(int c2, int kh, int e) { return 16 * c2 + 8 * (e >> 2) + 4 * kh + (e & 3); }
-
 // One workgroup per (32 query rows, head): wave w takes key blocks w, w + 4,
 // ... of 32 keys.  Per block: S^T = K Q^T on MFMA (A = 32 key rows from the
 // cache, B = the queries' three bf16 terms from LDS), the online softmax per
-// query (one query per lane pair), then O^T += V^T P^T (A = the value tile,
-// staged in LDS row by row and read back one bf16 per key and dimension; B =
-// the softmax weights' three terms from registers).  Transposing the value
-// tile on its way into LDS, one 16-bit store per element, put 16 lanes on
-// one bank.  The waves' (max, sum, output) states are merged through LDS at
+// query (one query per lane pair), then O^T += V^T P^T (B = the softmax
+// weights' three terms straight from the score tile's registers: register v
+// = 8 c2 + e of lane half kh holds key 8 (v / 4) + 4 kh + v % 4; A = the value
+// rows of those keys, staged in LDS row by row and read with the transposing
+// LDS read).  The waves' (max, sum, output) states are merged through LDS at
 // the end.
+// Vector instructions bound it (MFMAs do not hide them): the value tile
+// gathered by 16-bit reads, 64 and 32 packs per block, the output rescaled
+// and the mask applied at every block took 79 us at 2048 rows of the 1B (16
+// heads); the transposing reads, and both of the others only where needed,
+// 69.5 (7B, 1000 rows: 53 -> 44).  The first block requested ahead of the
+// query split, and no merge for a single block: 23 rows 12.3 -> 5.2 us.
 template <int HD>
 __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
   using Lds = AttnLds<HD>;
@@ -934,34 +933,18 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
   const int n_keys = a.pos0 + q0 + rows;  // keys the block's last row sees
   const int nkb = (n_keys + 31) / 32;
 
-  // queries, scaled to log2 units and split into three bf16 terms
-  for (int e = tid; e < 32 * HD; e += kAW * AIO_WAVE) {
-    const int qq = e / HD, dim = e % HD;
-    const float v = qq < rows ? a.q[(size_t)(q0 + qq) * a.ldq + (size_t)h * HD + dim] * a.scale_log2
-                              : 0.f;
-    const uint16_t t0 = f32_to_bf16(v);
-    const float r1 = v - bf16_to_f32(t0);
-    const uint16_t t1 = f32_to_bf16(r1);
-    const uint16_t t2 = f32_to_bf16(r1 - bf16_to_f32(t1));
-    *(uint16_t*)(qs + (0 * 32 + qq) * Lds::QROW + dim * 2) = t0;
-    *(uint16_t*)(qs + (1 * 32 + qq) * Lds::QROW + dim * 2) = t1;
-    *(uint16_t*)(qs + (2 * 32 + qq) * Lds::QROW + dim * 2) = t2;
+  // queries, scaled to log2 units and split into three bf16 terms, four
+  // consecutive dims per thread and pass
+  float4 qv[32 * HD / 4 / (kAW * AIO_WAVE)];
+#pragma unroll
+  for (int i = 0; i < 32 * HD / 4 / (kAW * AIO_WAVE); ++i) {
+    const int e = i * kAW * AIO_WAVE + tid, qq = e / (HD / 4), dim = e % (HD / 4) * 4;
+    qv[i] = *(const float4*)(a.q + (size_t)(q0 + min(qq, rows - 1)) * a.ldq + (size_t)h * HD + dim);
   }
-  __syncthreads();
-
-  // this lane's query: row q0 + rl sees keys [0, lim]
-  const int lim = a.pos0 + q0 + (rl < rows ? rl : rows - 1);
-  char* vt = tail + wid * Lds::VBYTES;
+  // (the first block's keys and values follow the queries: loads complete in
+  // order, so waiting for the queries leaves them in flight)
   const uint16_t* kbase = a.kc + (size_t)kvh * a.max_ctx * HD;
   const uint16_t* vbase = a.vc + (size_t)kvh * a.max_ctx * HD;
-  constexpr int NHB = HD / 32;
-  f32x16 o[NHB];
-#pragma unroll
-  for (int hb = 0; hb < NHB; ++hb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[hb][i] = 0.f;
-  float m = -INFINITY, lsum = 0.f;
-
   // Block kb's key fragments (A operand: key row rl, dims 16 c + 8 kh ..) and
   // value chunks (16 bytes of 8 dims, row-major) into registers; keys past
   // n_keys read key 0.  The next block of the wave is requested while the
@@ -981,7 +964,38 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
       vr[it] = *(const uint4*)(vbase + (size_t)vkey * HD + d0);
     }
   };
-  if (wid < nkb) load_block(wid);
+  load_block(min(wid, nkb - 1));
+#pragma unroll
+  for (int i = 0; i < 32 * HD / 4 / (kAW * AIO_WAVE); ++i) {
+    const int e = i * kAW * AIO_WAVE + tid, qq = e / (HD / 4), dim = e % (HD / 4) * 4;
+    uint32_t t[4][kNT];
+    split3t(__float_as_uint(qv[i].x * a.scale_log2), t[0]);
+    split3t(__float_as_uint(qv[i].y * a.scale_log2), t[1]);
+    split3t(__float_as_uint(qv[i].z * a.scale_log2), t[2]);
+    split3t(__float_as_uint(qv[i].w * a.scale_log2), t[3]);
+#pragma unroll
+    for (int k = 0; k < kNT; ++k) {
+      const u32x2 w = {(t[0][k] >> 16) | t[1][k], (t[2][k] >> 16) | t[3][k]};
+      *(u32x2*)(qs + (k * 32 + qq) * Lds::QROW + dim * 2) = w;
+    }
+  }
+  __syncthreads();
+
+  // this lane's query: row q0 + rl sees keys [0, lim]
+  const int lim = a.pos0 + q0 + (rl < rows ? rl : rows - 1);
+  char* vt = tail + wid * Lds::VBYTES;
+  constexpr int NHB = HD / 32;
+  f32x16 o[NHB];
+#pragma unroll
+  for (int hb = 0; hb < NHB; ++hb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[hb][i] = 0.f;
+  float m = -INFINITY, lsum = 0.f;
+
+  // transposing reads of the value tile: this lane's address serves key e of
+  // four and dims 4 q .. + 3 of its group's 16
+  const char* vtr = vt + (4 * kh + (lane & 15) / 4) * Lds::VROW +
+                    ((lane >> 4 & 1) * 16 + (lane & 3) * 4) * 2;
 
   for (int kb = wid; kb < nkb; kb += kAW) {
     const int j0 = kb * 32;
@@ -1011,18 +1025,24 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
     // the fragments stay in registers)
     load_block(kb + kAW < nkb ? kb + kAW : kb);
     // causal mask and online softmax for this lane's query (column rl)
-    float mx = -INFINITY;
+    // (only a block with keys past the first row's own needs the mask)
+    if (j0 + 31 > a.pos0 + q0) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int key = j0 + 8 * (v / 4) + 4 * kh + (v % 4);
-      if (key > lim) s[v] = -INFINITY;
-      mx = fmaxf(mx, s[v]);
+      for (int v = 0; v < 16; ++v) {
+        const int key = j0 + 8 * (v / 4) + 4 * kh + (v % 4);
+        if (key > lim) s[v] = -INFINITY;
+      }
     }
+    float mx = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, AIO_WAVE));
     const float mnew = fmaxf(m, mx);
-    // (the hardware exp2: every argument is <= 0, and exp2(-inf) = 0)
-    const float c =
-        (m == -INFINITY) ? (mnew == -INFINITY ? 1.f : 0.f) : __builtin_amdgcn_exp2f(m - mnew);
+    // (the hardware exp2: every argument is <= 0, and exp2(-inf) = 0; a block
+    // that raises no query's maximum, as most after the first few, leaves the
+    // output as it is: c would be 1)
+    const bool raised = __any(mnew > m);
+    const float c = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mnew);
     const float mref = mnew == -INFINITY ? 0.f : mnew;
     float p[16];
     float ps = 0.f;
@@ -1031,12 +1051,15 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
       p[v] = __builtin_amdgcn_exp2f(s[v] - mref);
       ps += p[v];
     }
-    lsum = lsum * c + ps;
+    if (raised) {
+      lsum *= c;
+#pragma unroll
+      for (int hb = 0; hb < NHB; ++hb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[hb][i] *= c;
+    }
+    lsum += ps;
     m = mnew;
-#pragma unroll
-    for (int hb = 0; hb < NHB; ++hb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o[hb][i] *= c;
     wave_lds_sync();  // the value tile is in LDS
     // O^T += V^T P^T, two chunks of 16 keys, three terms of the weights
 #pragma unroll
@@ -1063,13 +1086,9 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
 #pragma unroll
       for (int hb = 0; hb < NHB; ++hb) {
         // V^T fragment: dimension hb 32 + rl at this lane's eight keys
-        const char* vcol = vt + (hb * 32 + rl) * 2;
-        uint32_t w[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          w[j] = (uint32_t)*(const uint16_t*)(vcol + pkey(c2, kh, 2 * j) * Lds::VROW) |
-                 ((uint32_t)*(const uint16_t*)(vcol + pkey(c2, kh, 2 * j + 1) * Lds::VROW) << 16);
-        const bf16x8 av = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+        const uint2 v0 = lds_read_tr16(vtr + 16 * c2 * Lds::VROW + hb * 64);
+        const uint2 v1 = lds_read_tr16(vtr + (16 * c2 + 8) * Lds::VROW + hb * 64);
+        const bf16x8 av = as_bf16x8(make_uint4(v0.x, v0.y, v1.x, v1.y));
 #pragma unroll
         for (int t = 0; t < 3; ++t) o[hb] = mfma(av, bp[t], o[hb]);
       }
@@ -1108,14 +1127,16 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
     lsum = lsum * c1 + l2 * c2;
     m = M;
   };
-  if (wid >= 2) put(wid - 2);
-  __syncthreads();
-  if (wid < 2) take(wid);
-  __syncthreads();
-  if (wid == 1) put(0);
-  __syncthreads();
+  if (nkb > 1) {  // (one block: it was wave 0's)
+    if (wid >= 2) put(wid - 2);
+    __syncthreads();
+    if (wid < 2) take(wid);
+    __syncthreads();
+    if (wid == 1) put(0);
+    __syncthreads();
+  }
   if (wid != 0) return;
-  take(0);
+  if (nkb > 1) take(0);
   if (rl >= rows) return;
   const int r = q0 + rl;
   const float inv = 1.f / lsum;

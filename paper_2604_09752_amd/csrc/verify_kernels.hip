@@ -1091,6 +1091,9 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   // columns past the M rows read the zero row: their columns of S^T are zero
   const char* qrow = qs + (live ? col : kMaxRows) * Lds::QROW;
   char* vt = tail + wid * Lds::VBYTES;
+  // transposing reads of the value tile: this lane's address serves key 4 g +
+  // e (and 16 + ..) and dims 4 q .. + 3 of a 16-dim tile
+  const char* vtr = vt + (4 * g + col / 4) * Lds::VROW + (col & 3) * 8;
   f32x4 o[NDT];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
@@ -1204,13 +1207,9 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) {
       // V^T fragment: dimension 16 dt + col at this lane group's eight keys
-      const char* vcol = vt + (dt * 16 + col) * 2;
-      uint32_t w[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        w[j] = (uint32_t)*(const uint16_t*)(vcol + vattn_key(g, 2 * j) * Lds::VROW) |
-               ((uint32_t)*(const uint16_t*)(vcol + vattn_key(g, 2 * j + 1) * Lds::VROW) << 16);
-      const bf16x8 av = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+      const uint2 v0 = lds_read_tr16(vtr + dt * 32);
+      const uint2 v1 = lds_read_tr16(vtr + 16 * Lds::VROW + dt * 32);
+      const bf16x8 av = as_bf16x8(make_uint4(v0.x, v0.y, v1.x, v1.y));
 #pragma unroll
       for (int t = 0; t < 3; ++t)
         o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bp[t], o[dt], 0, 0, 0);
