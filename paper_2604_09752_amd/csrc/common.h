@@ -96,14 +96,3 @@ AIO_DEV float group_sum_dpp(float v) {
   if (WIDTH == 16) v += dpp_mov<0x140>(v);  // row_mirror
   return v;
 }
-
-// Transposing LDS read of 16-bit values.  In each group of 16 lanes, lanes 4 e
-// .. 4 e + 3 give the addresses of the four quarters (4 values, 8 bytes each)
-// of row e, and lane i receives column i of the four rows: {row 0, .., row
-// 3}[i].  `p` points into LDS.
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-AIO_DEV uint2 lds_read_tr16(const void* p) {
-  const i16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) i16x4*)p);
-  return __builtin_bit_cast(uint2, v);
-}

@@ -27,6 +27,7 @@
 
 #include "aio_internal.h"
 #include "common.h"
+#include "lanes.h"
 
 namespace {
 

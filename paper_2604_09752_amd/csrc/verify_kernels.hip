@@ -31,6 +31,7 @@
 
 #include "aio_internal.h"
 #include "common.h"
+#include "lanes.h"
 
 namespace {
 
@@ -147,7 +148,6 @@ struct VGemmArgs {
   uint16_t* kc;
   uint16_t* vc;
   const float2* rope;
-  const aio_state* st;
   int H, Hkv, hd, max_ctx;
   int ks;                   // K splits across workgroups (grid.y); > 1 only for EPI_RESID
   float* part;              // RESID with ks > 1: [ks][M][ldo], slice y's product
@@ -162,12 +162,8 @@ struct VGemmArgs {
   const uint16_t* g_next;
   uint16_t* act_next;
   float* ss_out;
-  // stream-K form (SWIGLU): tile pairs of the product, and the
-  // partial sums [tiles][kSkMaxC][kMaxRows * 64] and arrival counters
-  // [tiles] of tile pairs that several workgroups share
-  int tiles;
-  float* skpart;
-  int* skcnt;
+  int pairs, np;            // QKV, SWIGLU: row pairs of the product and per workgroup
+  int pos;                  // QKV: position of the first row
 };
 
 // The k of the two MFMA fragments a lane holds in a block of 32 k (lane
@@ -255,67 +251,134 @@ AIO_DEV void vmma(const VFrag<WFMT, T>& f, bool col_live, f32x16 (&acc)[T]) {
   }
 }
 
-// LDS of a skinny-GEMM workgroup: the weight stage during the product, then
-// the partial tiles of the waves and a residual tile [M][64].
-constexpr int kVRedBytes = (int)sizeof(float) * (kGWaves / 2) * 2 * 32 * 33;
-constexpr int kVFinBytes = (int)sizeof(float) * kMaxRows * 64;
-template <int WFMT>
-constexpr int vgemm_lds() {
-  return VStage<WFMT>::BYTES > kVRedBytes + kVFinBytes ? VStage<WFMT>::BYTES
-                                                       : kVRedBytes + kVFinBytes;
+// LDS of a skinny-GEMM workgroup (the eight waves' sums meet in one step there,
+// and the epilogue's operands are requested before the loop.  Two steps, half
+// of the waves adding to the other half's, and late requests took 0.5 to 1.0
+// us more per product: O 7B 12.2 -> 11.6, int8 11.0 -> 10.0, 1B 7.6 -> 6.9;
+// down 22.0 -> 21.3, 18.3 -> 17.4, 10.6 -> 10.1): the weight stage during the product, then
+// the waves' partial tiles [waves][T] of [32][33] (with four tiles each 16
+// floats longer, so that the two rows of a pair, two tiles apart, lie in
+// different halves of the banks, as they do with two tiles).
+template <int T>
+constexpr int kVRedTile = 32 * 33 + (T == 4 ? 16 : 0);
+template <int WFMT, int T>
+constexpr int vgemm_lds(int stage_rows) {
+  constexpr int red = (int)sizeof(float) * kGWaves * T * kVRedTile<T>;
+  return stage_rows * VStage<WFMT>::RS > red ? stage_rows * VStage<WFMT>::RS : red;
 }
 
-// Epilogue of one output element of a QKV or gate/up tile pair tp (tile
-// row i, verify row r) from the pair's two norm-scaled sums y0, y1:
-//   QKV: rows (n, n + hd/2) of a head section, rotated at position pos + r,
-//     to q or to the K / V cache;
-//   SWIGLU: the same row n of gate and up, silu(g) u split into act_out.
+// The waves' partial tiles to LDS (D layout: lane l, register v -> column j =
+// l % 32, row i = 8 * (v / 4) + 4 * (l / 32) + (v % 4); only columns with a
+// term of a row).
+template <int T>
+AIO_DEV void vred_put(float* red, int wid, int rl, int kh, bool col_live,
+                      const f32x16 (&acc)[T]) {
+  if (!col_live) return;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      red[(wid * T + t) * kVRedTile<T> + (8 * (v / 4) + 4 * kh + (v % 4)) * 33 + rl] = acc[t][v];
+}
+// Row r of output i of tile t: every wave's sums of the three split terms.
+template <int T>
+AIO_DEV float vred_sum(const float* red, int t, int i, int r, int M) {
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < kGWaves; ++w) {
+    const float* p = red + (w * T + t) * kVRedTile<T> + i * 33 + r;
+    s += p[0] + p[M] + p[2 * M];
+  }
+  return s;
+}
+
+// What the epilogue of verify row r of pair p reads besides the sums: cos and
+// sin of the pair's angle (QKV: q and k), the int8 scales.
+struct PairIn {
+  float2 cs;
+  float s0, s1;
+};
 template <int WFMT, int EPI>
-AIO_DEV void vgemm_epi(const VGemmArgs& a, int tp, int r, int i, float y0, float y1, int pos) {
+AIO_DEV PairIn vpair_in(const VGemmArgs& a, int p, int r) {
+  PairIn in{make_float2(1.f, 0.f), 1.f, 1.f};
   if constexpr (EPI == EPI_QKV) {
-    const int qrows = a.H * a.hd, krows = a.Hkv * a.hd;
-    const int per_head = a.hd / 64;
-    const int head = tp / per_head, sub = tp % per_head;
-    const int ii = sub * 32 + i;  // index within the first half of the head
-    const int n_lo = head * a.hd + ii;
-    const int half = a.hd / 2;
-    float lo = y0, hi = y1;
+    const int qrows = a.H * a.hd, krows = a.Hkv * a.hd, half = a.hd / 2;
+    const int head = p / half, ii = p - head * half, n = head * a.hd + ii;
+    if (n < qrows + krows) in.cs = a.rope[(size_t)(a.pos + r) * half + ii];
     if constexpr (WFMT == AIO_WFMT_INT8) {
       // both rows of the pair lie in the same (q, k or v) section
-      const uint16_t* sc = a.s0;
-      int m_lo = n_lo;
-      if (n_lo >= qrows + krows) { sc = a.s2; m_lo -= qrows + krows; }
-      else if (n_lo >= qrows) { sc = a.s1; m_lo -= qrows; }
-      lo *= fp16_to_f32(sc[m_lo]);
-      hi *= fp16_to_f32(sc[m_lo + half]);
+      const uint16_t* sc = n >= qrows + krows ? a.s2 + (n - qrows - krows)
+                                              : (n >= qrows ? a.s1 + (n - qrows) : a.s0 + n);
+      in.s0 = fp16_to_f32(sc[0]);
+      in.s1 = fp16_to_f32(sc[half]);
     }
-    const int p = pos + r;
-    if (n_lo < qrows + krows) {
-      const float2 cs = a.rope[(size_t)p * half + ii];
-      const float r0 = lo * cs.x - hi * cs.y;
-      const float r1 = hi * cs.x + lo * cs.y;
-      lo = r0;
-      hi = r1;
+  } else if constexpr (WFMT == AIO_WFMT_INT8) {
+    in.s0 = fp16_to_f32(a.s0[p]);
+    in.s1 = fp16_to_f32(a.s1[p]);
+  }
+  return in;
+}
+
+// Epilogue of verify row r of pair p of a QKV or gate/up product, from the
+// pair's two norm-scaled sums y0, y1:
+//   QKV: pair p = rows ii and ii + hd / 2 of a head section, rotated at
+//     position pos + r, to q or to the K / V cache;
+//   SWIGLU: row p of gate and of up, silu(g) u split into act_out.
+template <int WFMT, int EPI>
+AIO_DEV void vpair_epi(const VGemmArgs& a, const PairIn& in, int p, int r, float y0, float y1) {
+  if constexpr (WFMT == AIO_WFMT_INT8) {
+    y0 *= in.s0;
+    y1 *= in.s1;
+  }
+  if constexpr (EPI == EPI_QKV) {
+    const int qrows = a.H * a.hd, krows = a.Hkv * a.hd, half = a.hd / 2;
+    const int head = p / half, ii = p - head * half, n = head * a.hd + ii;
+    float lo = y0, hi = y1;
+    if (n < qrows + krows) {
+      lo = y0 * in.cs.x - y1 * in.cs.y;
+      hi = y1 * in.cs.x + y0 * in.cs.y;
     }
-    if (n_lo < qrows) {
-      a.out[(size_t)r * a.ldo + n_lo] = lo;
-      a.out[(size_t)r * a.ldo + n_lo + half] = hi;
+    if (n < qrows) {
+      a.out[(size_t)r * a.ldo + n] = lo;
+      a.out[(size_t)r * a.ldo + n + half] = hi;
     } else {
-      const bool is_k = n_lo < qrows + krows;
-      const int g = (n_lo - (is_k ? qrows : qrows + krows)) / a.hd;
-      uint16_t* c = (is_k ? a.kc : a.vc) + ((size_t)g * a.max_ctx + p) * a.hd;
+      const bool is_k = n < qrows + krows;
+      const int g = (n - (is_k ? qrows : qrows + krows)) / a.hd;
+      uint16_t* c = (is_k ? a.kc : a.vc) + ((size_t)g * a.max_ctx + a.pos + r) * a.hd;
       c[ii] = f32_to_bf16(lo);
       c[ii + half] = f32_to_bf16(hi);
     }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    const int n = tp * 32 + i;
-    if (n < a.N) {
-      float g = y0, u = y1;
-      if constexpr (WFMT == AIO_WFMT_INT8) {
-        g *= fp16_to_f32(a.s0[n]);
-        u *= fp16_to_f32(a.s1[n]);
-      }
-      store_split(a.act_out, a.lda_out, a.M, r, n, g / (1.f + expf(-g)) * u);
+  } else {
+    store_split(a.act_out, a.lda_out, a.M, r, p, y0 / (1.f + expf(-y0)) * y1);
+  }
+}
+
+// Norm factors of rows: wave w sums the chunk sums of rows w and w + 8, lane
+// l taking chunks l, l + 64, ...; ssp holds the first two of each, requested
+// earlier.
+AIO_DEV void vnorm_request(const VGemmArgs& a, int wid, int lane, float (&ssp)[2][2]) {
+  static_assert(kMaxRows <= 2 * kGWaves, "two rows per wave");
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = wid + kGWaves * h;
+    ssp[h][0] = ssp[h][1] = 0.f;
+    if (r < a.M) {
+      const float* ssr = a.ss_in + (size_t)r * a.nt;
+      if (lane < a.nt) ssp[h][0] = ssr[lane];
+      if (lane + 64 < a.nt) ssp[h][1] = ssr[lane + 64];
+    }
+  }
+}
+AIO_DEV void vnorm_finish(const VGemmArgs& a, int wid, int lane, const float (&ssp)[2][2],
+                          float* inv_s) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = wid + kGWaves * h;
+    if (r < a.M) {
+      float p = ssp[h][0] + ssp[h][1];
+      for (int c = lane + 128; c < a.nt; c += 64) p += a.ss_in[(size_t)r * a.nt + c];
+      const float sum = wave_sum(p);
+      if (lane == 0) inv_s[r] = rsqrtf(sum / (float)a.K + a.eps);
     }
   }
 }
@@ -325,57 +388,19 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
   constexpr int T = 2;
   using St = VStage<WFMT>;
   extern __shared__ __align__(16) char smem[];
-  float (*red)[T][32][33] = (float (*)[T][32][33])smem;
-  float (*fin)[64] = (float (*)[64])(smem + kVRedBytes);
+  float* red = (float*)smem;
   __shared__ float inv_s[kMaxRows];
   __shared__ int last_s;
   const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
   const int rl = lane & 31, kh = lane >> 5;
   const size_t wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
 
-  // tile rows: QKV pairs (rows, rows + hd/2) of one head section, SWIGLU the
-  // same rows of gate and up, otherwise two consecutive tiles.
-  int tile_row[T];
-  const void* tile_w[T];
-  if constexpr (EPI == EPI_QKV) {
-    const int per_head = a.hd / 64;  // tile pairs per head (hd/2 rows / 32)
-    const int head = blockIdx.x / per_head, sub = blockIdx.x % per_head;
-    const int qrows = a.H * a.hd, krows = a.Hkv * a.hd;
-    int n0 = head * a.hd + sub * 32;
-    const void* w = a.w0;
-    if (n0 >= qrows + krows) { w = a.w2; n0 -= qrows + krows; }
-    else if (n0 >= qrows) { w = a.w1; n0 -= qrows; }
-    tile_row[0] = n0;
-    tile_row[1] = n0 + a.hd / 2;
-    tile_w[0] = tile_w[1] = w;
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    tile_row[0] = tile_row[1] = blockIdx.x * 32;
-    tile_w[0] = a.w0;
-    tile_w[1] = a.w1;
-  } else {
-    tile_row[0] = blockIdx.x * 64;
-    tile_row[1] = blockIdx.x * 64 + 32;
-    tile_w[0] = tile_w[1] = a.w0;
-  }
-  const int n_rows_w = (EPI == EPI_QKV) ? 0 : a.N;  // clamp bound for plain tiles
+  const int tile_row[T] = {(int)blockIdx.x * 64, (int)blockIdx.x * 64 + 32};
   const bool col_live = rl < 3 * a.M;
-  // Norm scales: wave w sums the chunk sums of rows w and w + 8, lane l
-  // taking chunks l and l + 64 (written by an earlier kernel).  They are
-  // requested here and added only in the epilogue, so no wait in the
-  // product is spent on them.
-  static_assert(kMaxRows <= 2 * kGWaves, "two rows per wave");
-  float ssp[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
-  if (EPI != EPI_RESID) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = wid + kGWaves * h;
-      if (r < a.M) {
-        const float* ssr = a.ss_in + (size_t)r * a.nt;
-        if (lane < a.nt) ssp[h][0] = ssr[lane];
-        if (lane + 64 < a.nt) ssp[h][1] = ssr[lane + 64];
-      }
-    }
-  }
+  // (requested here and added only in the epilogue, so no wait in the
+  // product is spent on them)
+  float ssp[2][2];
+  if (EPI != EPI_RESID) vnorm_request(a, wid, lane, ssp);
   // dead columns read row 0 (in bounds) and are zeroed before the product
   const uint16_t* actp = a.act + (size_t)(col_live ? rl : 0) * a.lda;
 
@@ -410,8 +435,8 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
   for (int j = 0; j < St::NLD; ++j) {
     const int f = j * kGBlock + tid, r = f / St::CPR, c = f % St::CPR;
     int n = tile_row[r / 32] + r % 32;
-    if (n_rows_w && n >= n_rows_w) n = n_rows_w - 1;
-    lrow[j] = (const char*)tile_w[r / 32] + (size_t)n * a.K * wbytes;
+    if (n >= a.N) n = a.N - 1;
+    lrow[j] = (const char*)a.w0 + (size_t)n * a.K * wbytes;
     lds_off[j] = r * St::RS + c * 16;
     lchunk[j] = c;
   }
@@ -505,75 +530,44 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
     }
   }
   __syncthreads();  // the stage buffer becomes the partial-tile buffer
-  // D layout: lane l, register v -> column j = l % 32,
-  // row i = 8 * (v / 4) + 4 * (l / 32) + (v % 4).  The upper four waves
-  // hand their tiles to the lower four, which then write the sums.
-  if (wid >= kGWaves / 2) {
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        red[wid - kGWaves / 2][t][8 * (v / 4) + 4 * kh + (v % 4)][rl] = acc[t][v];
-  }
-  __syncthreads();
-  if (wid < kGWaves / 2) {
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float& r = red[wid][t][8 * (v / 4) + 4 * kh + (v % 4)][rl];
-        r += acc[t][v];
-      }
-  }
-  if (EPI != EPI_RESID) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = wid + kGWaves * h;
-      if (r < a.M) {
-        float p = ssp[h][0] + ssp[h][1];
-        for (int c = lane + 128; c < a.nt; c += 64) p += a.ss_in[(size_t)r * a.nt + c];
-        const float sum = wave_sum(p);
-        if (lane == 0) inv_s[r] = rsqrtf(sum / (float)a.K + a.eps);
-      }
-    }
-  }
-  __syncthreads();
+  vred_put<T>(red, wid, rl, kh, col_live, acc);
+  if (EPI != EPI_RESID) vnorm_finish(a, wid, lane, ssp, inv_s);
 
-  // Sum the four wave pairs and the three split terms: y[r][i] for the tile.
+  // Thread -> verify row r, output column n (one row per wave and pass).  The
+  // inputs of the residual epilogue are requested before the sums.
   const int M = a.M;
-  const int pos = a.st->pos;
-  for (int e = tid; e < 32 * M; e += kGBlock) {
-    const int i = e % 32, r = e / 32;
-    float y[T];
+  constexpr int NI = (64 * kMaxRows + kGBlock - 1) / kGBlock;
+  float v[NI], xn[NI], gn[NI], sc[NI];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < kGWaves / 2; ++w)
-        s += red[w][t][i][r] + red[w][t][i][M + r] + red[w][t][i][2 * M + r];
-      y[t] = EPI == EPI_RESID ? s : s * inv_s[r];
+  for (int it = 0; it < NI; ++it) {
+    if (it * kGBlock >= 64 * M) break;
+    const int e = min(tid + it * kGBlock, 64 * M - 1), r = e / 64;
+    const int n = min((int)blockIdx.x * 64 + e % 64, a.N - 1);
+    if constexpr (EPI == EPI_RESID) {
+      xn[it] = a.out[(size_t)r * a.ldo + n];
+      gn[it] = bf16_to_f32(a.g_next[n]);
     }
-    if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
-      vgemm_epi<WFMT, EPI>(a, (int)blockIdx.x, r, i, y[0], y[1], pos);
-    } else {
+    if constexpr (WFMT == AIO_WFMT_INT8) sc[it] = fp16_to_f32(a.s0[n]);
+  }
+  __syncthreads();
 #pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const int n = tile_row[t] + i;
-        if (n >= a.N) continue;
-        float v = y[t];
-        if constexpr (WFMT == AIO_WFMT_INT8) v *= fp16_to_f32(a.s0[n]);
-        if constexpr (EPI == EPI_RESID) {
-          // K split over workgroups: each slice stores its part of the
-          // product; the slice that arrives last adds them in slice order
-          if (a.ks > 1) st_agent(a.part + ((size_t)blockIdx.y * M + r) * a.ldo + n, v);
-          else fin[r][t * 32 + i] = v;
-        } else {
-          a.out[(size_t)r * a.ldo + n] = v;
-        }
-      }
+  for (int it = 0; it < NI; ++it) {
+    const int e = tid + it * kGBlock, r = e / 64, c = e % 64, n = (int)blockIdx.x * 64 + c;
+    if (e >= 64 * M || n >= a.N) break;
+    v[it] = vred_sum<T>(red, c / 32, c % 32, r, M);
+    if constexpr (EPI != EPI_RESID) v[it] *= inv_s[r];
+    if constexpr (WFMT == AIO_WFMT_INT8) v[it] *= sc[it];
+    if constexpr (EPI == EPI_RESID) {
+      // K split over workgroups: each slice stores its part of the product;
+      // the slice that arrives last adds them in slice order
+      if (a.ks > 1) st_agent(a.part + ((size_t)blockIdx.y * M + r) * a.ldo + n, v[it]);
+    } else {
+      a.out[(size_t)r * a.ldo + n] = v[it];
     }
   }
   if constexpr (EPI == EPI_RESID) {
+    const int nt = a.N / 64;
+    float pv[NI][kVerifyMaxKs];
     if (a.ks > 1) {
       // every wave's part stores have completed (written through) before
       // the slice is counted; the last slice to arrive (in whatever order)
@@ -584,314 +578,206 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
       __syncthreads();
       if (!last_s) return;
       if (tid == 0) atomic_store_agent(a.cnt + blockIdx.x, 0);  // ready for the next product
-    } else {
-      __syncthreads();
-    }
-    // columns c0 .. c0 + 63 of the M rows, one row per wave pass; every
-    // slot is requested before the first is added (slots past ks read
-    // slot 0 and add nothing)
-    const int c0 = blockIdx.x * 64, nt = a.N / 64;
-    for (int e = tid; e < 64 * M; e += kGBlock) {
-      const int r = e / 64, c = e % 64, n = c0 + c;
-      float* xp = a.out + (size_t)r * a.ldo + n;
-      float xn = *xp;
-      if (a.ks > 1) {
-        float pv[kVerifyMaxKs];
+      // every slot is requested before the first is added (slots past ks
+      // read slot 0 and add nothing)
+#pragma unroll
+      for (int it = 0; it < NI; ++it) {
+        if (it * kGBlock >= 64 * M) break;
+        const int e = min(tid + it * kGBlock, 64 * M - 1), r = e / 64;
+        const int n = (int)blockIdx.x * 64 + e % 64;
 #pragma unroll
         for (int k = 0; k < kVerifyMaxKs; ++k)
-          pv[k] = ld_agent(a.part + ((size_t)(k < a.ks ? k : 0) * M + r) * a.ldo + n);
-#pragma unroll
-        for (int k = 0; k < kVerifyMaxKs; ++k)
-          if (k < a.ks) xn += pv[k];
-      } else {
-        xn += fin[r][c];
+          pv[it][k] = ld_agent(a.part + ((size_t)(k < a.ks ? k : 0) * M + r) * a.ldo + n);
       }
-      *xp = xn;
-      store_split(a.act_next, a.lda, M, r, n, xn * bf16_to_f32(a.g_next[n]));
-      const float sq = wave_sum(xn * xn);
+    }
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      const int e = tid + it * kGBlock, r = e / 64, n = (int)blockIdx.x * 64 + e % 64;
+      if (e >= 64 * M) break;  // (whole waves)
+      float x = xn[it];
+      if (a.ks > 1) {
+#pragma unroll
+        for (int k = 0; k < kVerifyMaxKs; ++k)
+          if (k < a.ks) x += pv[it][k];
+      } else {
+        x += v[it];
+      }
+      a.out[(size_t)r * a.ldo + n] = x;
+      store_split(a.act_next, a.lda, M, r, n, x * gn[it]);
+      const float sq = wave_sum(x * x);
       if (lane == 0) a.ss_out[(size_t)r * nt + blockIdx.x] = sq;
     }
   }
 }
 
-// Stream-K form of the gate/up product.  The product's units, a
-// tile pair (64 weight rows) times a stage of 256 k, are dealt out in equal
-// contiguous ranges in (tile pair, stage) order, one range per workgroup and
-// one workgroup per CU: every CU streams the same number of bytes, and its
-// register pipeline (two stages in flight, as in k_vgemm) runs on across
-// tile-pair boundaries.  (With one whole tile pair per workgroup the gate /
-// up product has 344 workgroups for 256 CUs, and the CUs that hold two of
-// them set its length.)  A tile pair inside the range gets its epilogue as
-// soon as its last stage is multiplied; a pair the range shares with its
-// neighbours (at most one at each end) keeps its sums in registers until
-// the range is done, then writes them through to skpart at its slot (its
-// rank among the pair's workgroups) and counts itself in skcnt; the last to
-// arrive adds the slots in slot order, so the result does not depend on the
-// arrival order, and runs the epilogue.  (The QKV product keeps one tile
-// pair per workgroup: its 192 pairs on 256 CUs are all shared in this form,
-// and the end-of-range hand-over made it slower.)
-constexpr int kSkMaxC = kVerifySkMaxC;  // most workgroups sharing one tile pair
+// The QKV and gate/up products: outputs in pairs of weight rows (QKV: rows ii
+// and ii + hd / 2 of a head section, SWIGLU: the same row of gate and up).
+// Workgroup b owns the np pairs from np b: as many as spread the product
+// evenly over the CUs, up to 64, so every CU streams the same bytes in one
+// workgroup.  Measured with 2-3 or 8 rows at 2K, in us, against workgroups of
+// whole 32-row tile pairs (QKV) and tile pairs dealt out over the CUs whose
+// shares then met through memory (SWIGLU): gate/up 7B bf16 (43 pairs) 38.2 ->
+// 34.0, int8 27.0 -> 23.3, 1B (22 pairs) 15.3 -> 11.1; QKV 1B (5 pairs) 10.8
+// -> 7.7, 7B int8 (24 pairs) 16.6 -> 16.2.  The 7B's bf16 QKV does not gain
+// (22.3 -> 23.2): its 192 workgroups of 32 pairs already streamed at the rate
+// HBM gives.  Other np (22 to 64) were within 3 % or slower.
+//
+// As in k_vgemm, the weights pass through LDS in stages of 256 k, with NS
+// stages in flight in registers, and wave w multiplies 32-k block w of every
+// stage; NB blocks of 32 pairs (rows past np hold whatever the buffer held:
+// each row of the result depends on its own weight row only), NLD 16-byte
+// loads per thread and stage.
+template <int WFMT, int NB, int NLD, int NS>
+struct VPair {
+  static constexpr int T = 2 * NB;                              // 32-row tiles
+  static constexpr int Lds = vgemm_lds<WFMT, T>(32 * T);
+  static constexpr int RPL = kGBlock / VStage<WFMT>::CPR;       // rows a load slot covers
+  static constexpr int Pairs = NLD * RPL / 2;                   // most pairs
+  static constexpr int NI = (2 * Pairs * kMaxRows + kGBlock - 1) / kGBlock;  // sums per thread
+};
 
-template <int WFMT, int EPI>
-__global__ __launch_bounds__(kGBlock, 1) void k_vgemm_sk(VGemmArgs a) {
-  static_assert(EPI == EPI_SWIGLU, "the stream-K form serves the gate/up product");
-  constexpr int T = 2;
+template <int WFMT, int EPI, int NB, int NLD, int NS>
+__global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
+  static_assert(EPI == EPI_QKV || EPI == EPI_SWIGLU, "products of row pairs");
   using St = VStage<WFMT>;
+  using Vp = VPair<WFMT, NB, NLD, NS>;
+  constexpr int T = Vp::T, BPW = St::BPW;
+  static_assert(BPW == 1, "one block per wave and stage");
   extern __shared__ __align__(16) char smem[];
-  float (*red)[T][32][33] = (float (*)[T][32][33])smem;
+  float* red = (float*)smem;
   __shared__ float inv_s[kMaxRows];
-  __shared__ int last_s[2];
   const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
   const int rl = lane & 31, kh = lane >> 5;
-  const size_t wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
+  constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
   const int M = a.M;
   const bool col_live = rl < 3 * M;
-  constexpr int BPS = St::BPS, BPW = St::BPW;
-  const int nkb = a.K / 32;
-  const int nst = (nkb + BPS - 1) / BPS;
-  const long long U = (long long)a.tiles * nst, G = gridDim.x, gb = blockIdx.x;
-  const int u0 = (int)(gb * U / G), u1 = (int)((gb + 1) * U / G);
-  // workgroup whose range holds unit u
-  auto owner = [&](long long u) { return (int)(((u + 1) * G - 1) / U); };
+  const int p0 = (int)blockIdx.x * a.np, np = min(a.np, a.pairs - p0);
 
-  // norm scales: requested first, reduced once the first stages are in flight
-  static_assert(kMaxRows <= 2 * kGWaves, "two rows per wave");
-  float ssp[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+  // staging: load j of this thread is chunk lchunk of the row in slot j
+  // (slot s < np: the lo row of pair p0 + s, then the hi rows; slots past
+  // them repeat the last row)
+  const char* lrow[NLD];
+  int lds_off[NLD];
+  const int lchunk = tid % St::CPR;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int r = wid + kGWaves * h;
-    if (r < M) {
-      const float* ssr = a.ss_in + (size_t)r * a.nt;
-      if (lane < a.nt) ssp[h][0] = ssr[lane];
-      if (lane + 64 < a.nt) ssp[h][1] = ssr[lane + 64];
+  for (int j = 0; j < NLD; ++j) {
+    const int s = min(j * Vp::RPL + tid / St::CPR, 2 * np - 1);
+    const bool hi = s >= np;
+    const int p = p0 + (hi ? s - np : s);
+    const char* w;
+    int n;
+    if constexpr (EPI == EPI_QKV) {
+      const int half = a.hd / 2, head = p / half;
+      const int qrows = a.H * a.hd, krows = a.Hkv * a.hd;
+      n = head * a.hd + p - head * half + (hi ? half : 0);
+      w = (const char*)a.w0;
+      if (n >= qrows + krows) { w = (const char*)a.w2; n -= qrows + krows; }
+      else if (n >= qrows) { w = (const char*)a.w1; n -= qrows; }
+    } else {
+      n = p;
+      w = (const char*)(hi ? a.w1 : a.w0);
     }
+    lrow[j] = w + (size_t)n * a.K * wbytes;
+    lds_off[j] = ((hi ? 32 * NB : 0) + p - p0) * St::RS + lchunk * 16;
   }
   const uint16_t* actp = a.act + (size_t)(col_live ? rl : 0) * a.lda;
-
-  // staging: load j of this thread is chunk lchunk[j] of stage row lrow[j]
-  // (row < 32: tile 0, else tile 1, of whichever pair the unit belongs to)
-  int lrow[St::NLD], lds_off[St::NLD], lchunk[St::NLD];
-#pragma unroll
-  for (int j = 0; j < St::NLD; ++j) {
-    const int f = j * kGBlock + tid;
-    lrow[j] = f / St::CPR;
-    lchunk[j] = f % St::CPR;
-    lds_off[j] = lrow[j] * St::RS + lchunk[j] * 16;
-  }
-  const int kend = nkb * 32 * (int)wbytes - 16;  // last 16-byte chunk of a row
-  // first byte of weight row rr (0..63) of tile pair tp: rows tp 32 ..
-  // tp 32 + 31 of gate (rr < 32), then the same rows of up
-  auto row_ptr = [&](int tp, int rr) -> const char* {
-    const void* w = rr >= 32 ? a.w1 : a.w0;
-    int n = tp * 32 + (rr & 31);
-    if (n >= a.N) n = a.N - 1;
-    return (const char*)w + (size_t)n * a.K * wbytes;
+  const int nkb = a.K / 32, nst = (nkb + St::BPS - 1) / St::BPS;
+  // workgroup b starts at stage b mod nst and wraps (see k_vgemm)
+  const int rot = (int)(blockIdx.x % (unsigned)nst);
+  auto kb0 = [&](int st) {  // first 32-k block of stage st (st < 2 nst)
+    const int q = st + rot;
+    return (q >= nst ? q - nst : q) * St::BPS;
   };
-  // loads past the range re-read its last unit (and are not multiplied)
-  auto gload_w = [&](uint4 (&R)[St::NLD], int u) {
-    const int uu = u < u1 ? u : u1 - 1;
-    const int tp = uu / nst, s = uu - tp * nst;
+  const int kend = a.K * wbytes - 16;  // last 16-byte chunk of a row
+  auto gload_w = [&](uint4 (&R)[NLD], int st) {
+    const int off = min(kb0(min(st, nst - 1)) * 32 * wbytes + lchunk * 16, kend);
 #pragma unroll
-    for (int j = 0; j < St::NLD; ++j) {
-      int off = s * St::KC * (int)wbytes + lchunk[j] * 16;
-      off = off < kend ? off : kend;
-      R[j] = ldg_nt(row_ptr(tp, lrow[j]) + off);
-    }
+    for (int j = 0; j < NLD; ++j) R[j] = ldg_nt(lrow[j] + off);
   };
-  auto gload_a = [&](uint4 (&A)[BPW][2], int u) {
-    const int uu = u < u1 ? u : u1 - 1;
-    const int s = uu % nst;
-#pragma unroll
-    for (int j = 0; j < BPW; ++j) {
-      const int block = min(s * BPS + wid + kGWaves * j, nkb - 1);
-      A[j][0] = ldg(actp + vk_lo<WFMT>(block * 32, kh));
-      A[j][1] = ldg(actp + vk_hi<WFMT>(block * 32, kh));
-    }
+  auto gload_a = [&](uint4 (&A)[2], int st) {
+    const int block = min(kb0(min(st, nst - 1)) + wid, nkb - 1);
+    A[0] = ldg(actp + vk_lo<WFMT>(block * 32, kh));
+    A[1] = ldg(actp + vk_hi<WFMT>(block * 32, kh));
   };
-  auto stage = [&](const uint4 (&R)[St::NLD]) {
+  auto stage = [&](const uint4 (&R)[NLD]) {
     __syncthreads();  // every wave is done with the previous stage
 #pragma unroll
-    for (int j = 0; j < St::NLD; ++j) {
+    for (int j = 0; j < NLD; ++j) {
       const u32x4 w = {R[j].x, R[j].y, R[j].z, R[j].w};
       *(u32x4*)(smem + lds_off[j]) = w;
     }
     __syncthreads();
   };
   f32x16 acc[T];
-  auto product = [&](int u, const uint4 (&A)[BPW][2]) {
-    const int s = u % nst;
 #pragma unroll
-    for (int j = 0; j < BPW; ++j) {
-      const int wb = wid + kGWaves * j;
-      const bool live = col_live && s * BPS + wb < nkb;
-      VFrag<WFMT, T> f;
+  for (int t = 0; t < T; ++t)
 #pragma unroll
-      for (int t = 0; t < T; ++t)
-        frag_lds<WFMT>(smem + (t * 32 + rl) * St::RS, wb, kh, f.wa[t], f.wb[t]);
-      f.ba = __builtin_bit_cast(bf16x8, A[j][0]);
-      f.bb = __builtin_bit_cast(bf16x8, A[j][1]);
-      vmma(f, live, acc);
-    }
-  };
-  auto zero_acc = [&]() {
+    for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+  // branch-free: a block past the end multiplies zeros
+  auto product = [&](int st, const uint4 (&A)[2]) {
+    const bool live = col_live && kb0(st) + wid < nkb;
+    VFrag<WFMT, T> f;
 #pragma unroll
     for (int t = 0; t < T; ++t)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+      frag_lds<WFMT>(smem + (t * 32 + rl) * St::RS, wid, kh, f.wa[t], f.wb[t]);
+    f.ba = __builtin_bit_cast(bf16x8, A[0]);
+    f.bb = __builtin_bit_cast(bf16x8, A[1]);
+    vmma(f, live, acc);
   };
-  // The eight waves' sums of the current tile pair: element e = 32 r + i of
-  // this thread (e < 32 M), both tiles, three split terms added; raw (the
-  // norm scale comes later).
-  auto reduce = [&](float (&y)[T]) {
-    __syncthreads();  // the stage buffer becomes the partial-tile buffer
-    if (wid >= kGWaves / 2) {
+  uint4 R[NS][NLD], A[NS][2];
 #pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          red[wid - kGWaves / 2][t][8 * (v / 4) + 4 * kh + (v % 4)][rl] = acc[t][v];
-    }
-    __syncthreads();
-    if (wid < kGWaves / 2) {
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float& r = red[wid][t][8 * (v / 4) + 4 * kh + (v % 4)][rl];
-          r += acc[t][v];
-        }
-    }
-    __syncthreads();
-    const int i = tid % 32, r = tid / 32;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      float s = 0.f;
-      if (tid < 32 * M) {
-#pragma unroll
-        for (int w = 0; w < kGWaves / 2; ++w)
-          s += red[w][t][i][r] + red[w][t][i][M + r] + red[w][t][i][2 * M + r];
-      }
-      y[t] = s;
-    }
-    // the next stage() starts with a barrier: every read of red is done
-    // before the buffer is written again
+  for (int i = 0; i < NS; ++i) {
+    gload_w(R[i], i);
+    gload_a(A[i], i);
+  }
+  float ssp[2][2];
+  vnorm_request(a, wid, lane, ssp);
+  // One stage: its weights go to LDS, its register set is refilled with the
+  // weights NS stages ahead before the product (so NS stages stay in flight
+  // through it), and the activation fragments after it.  Loads past the end
+  // re-read the last stage.
+  auto step = [&](uint4 (&Rs)[NLD], uint4 (&As)[2], int st) {
+    stage(Rs);
+    __builtin_amdgcn_sched_barrier(0);
+    gload_w(Rs, st + NS);
+    __builtin_amdgcn_sched_barrier(0);
+    product(st, As);
+    __builtin_amdgcn_sched_barrier(0);
+    gload_a(As, st + NS);
+    __builtin_amdgcn_sched_barrier(0);
   };
-
-  uint4 R0[St::NLD], R1[St::NLD];
-  uint4 A0[BPW][2], A1[BPW][2];
-  gload_w(R0, u0);
-  gload_a(A0, u0);
-  gload_w(R1, u0 + 1);
-  gload_a(A1, u0 + 1);
+  int st = 0;
+  for (; st + NS < nst; st += NS) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int r = wid + kGWaves * h;
-    if (r < M) {
-      float p = ssp[h][0] + ssp[h][1];
-      for (int c = lane + 128; c < a.nt; c += 64) p += a.ss_in[(size_t)r * a.nt + c];
-      const float sum = wave_sum(p);
-      if (lane == 0) inv_s[r] = rsqrtf(sum / (float)a.K + a.eps);
-    }
+    for (int i = 0; i < NS; ++i) step(R[i], A[i], st + i);
   }
-  const int pos = a.st->pos;
-  const int er = tid / 32, ei = tid % 32;  // this thread's epilogue element
-  // the range's shared tile pairs: [0] the one it starts in, [1] the one it
-  // ends in (-1: none)
-  int ptp[2] = {-1, -1};
-  float py[2][T] = {{0.f, 0.f}, {0.f, 0.f}};
-  zero_acc();
-  // After the product of unit u: if u ends a segment (the last unit of a
-  // tile pair or of the range), reduce it and finish or keep it.
-  auto seg_end = [&](int u) {
-    const int tp = u / nst;
-    if (u + 1 != u1 && u + 1 != (tp + 1) * nst) return;
-    float y[T];
-    reduce(y);
-    zero_acc();
-    const int sa = u0 > tp * nst ? u0 : tp * nst;  // first unit of the segment
-    const bool whole = sa == tp * nst && u + 1 == (tp + 1) * nst;
-    if (whole) {
-      if (tid < 32 * M)
-        vgemm_epi<WFMT, EPI>(a, tp, er, ei, y[0] * inv_s[er], y[1] * inv_s[er], pos);
-    } else if (sa == u0) {
-      ptp[0] = tp;
-      py[0][0] = y[0];
-      py[0][1] = y[1];
-    } else {
-      ptp[1] = tp;
-      py[1][0] = y[0];
-      py[1][1] = y[1];
-    }
-  };
-  auto step = [&](uint4 (&R)[St::NLD], uint4 (&A)[BPW][2], int u) {
-    stage(R);
-    __builtin_amdgcn_sched_barrier(0);
-    gload_w(R, u + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    product(u, A);
-    __builtin_amdgcn_sched_barrier(0);
-    gload_a(A, u + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    seg_end(u);
-  };
-  int u = u0;
-  for (; u + 2 <= u1; u += 2) {
-    step(R0, A0, u);
-    step(R1, A1, u + 1);
-  }
-  if (u < u1) {
-    stage(R0);
-    product(u, A0);
-    seg_end(u);
-  }
-
-  // shared tile pairs: write the sums through, count, and the last of the
-  // pair's workgroups adds the slots in order and finishes it
-  int slot[2], ncon[2];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    slot[p] = ncon[p] = 0;
-    if (ptp[p] < 0) continue;
-    const long long first = (long long)ptp[p] * nst;
-    const int g0 = owner(first), g1 = owner(first + nst - 1);
-    slot[p] = (int)gb - g0;
-    ncon[p] = g1 - g0 + 1;
-    if (tid < 32 * M) {
-      float* dst = a.skpart + ((size_t)ptp[p] * kSkMaxC + slot[p]) * (kMaxRows * 64) + er * 64 + ei;
-      st_agent(dst, py[p][0]);
-      st_agent(dst + 32, py[p][1]);
-    }
+  for (int i = 0; i < NS; ++i) {
+    if (st + i >= nst) break;
+    stage(R[i]);
+    product(st + i, A[i]);
   }
-  if (ptp[0] < 0 && ptp[1] < 0) return;
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (tid < 2) {
-    last_s[tid] = 0;
-    if (ptp[tid] >= 0) last_s[tid] = atomic_add_agent(a.skcnt + ptp[tid], 1) == ncon[tid] - 1;
+  __syncthreads();  // the stage buffer becomes the partial-tile buffer
+  vred_put<T>(red, wid, rl, kh, col_live, acc);
+  vnorm_finish(a, wid, lane, ssp, inv_s);
+  // Two lanes per pair and verify row, each summing one of the pair's rows.
+  PairIn in[Vp::NI];
+  const int h = tid & 1;
+#pragma unroll
+  for (int it = 0; it < Vp::NI; ++it) {
+    if (it * kGBlock >= 2 * np * M) break;
+    const int e = min((tid + it * kGBlock) >> 1, np * M - 1), r = e / np;
+    in[it] = vpair_in<WFMT, EPI>(a, p0 + e - r * np, r);
   }
   __syncthreads();
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    if (!last_s[p]) continue;
-    if (tid == 0) atomic_store_agent(a.skcnt + ptp[p], 0);  // ready for the next product
-    if (tid < 32 * M) {
-      const float* src = a.skpart + (size_t)ptp[p] * kSkMaxC * (kMaxRows * 64) + er * 64 + ei;
-      float v0[kSkMaxC], v1[kSkMaxC];
-#pragma unroll
-      for (int k = 0; k < kSkMaxC; ++k) {
-        const int kk = k < ncon[p] ? k : 0;
-        v0[k] = ld_agent(src + (size_t)kk * (kMaxRows * 64));
-        v1[k] = ld_agent(src + (size_t)kk * (kMaxRows * 64) + 32);
-      }
-      float y0 = 0.f, y1 = 0.f;
-#pragma unroll
-      for (int k = 0; k < kSkMaxC; ++k)
-        if (k < ncon[p]) {
-          y0 += v0[k];
-          y1 += v1[k];
-        }
-      vgemm_epi<WFMT, EPI>(a, ptp[p], er, ei, y0 * inv_s[er], y1 * inv_s[er], pos);
-    }
+  for (int it = 0; it < Vp::NI; ++it) {
+    const int e = (tid + it * kGBlock) >> 1;
+    if (e >= np * M) break;  // (both lanes of a pair)
+    const int r = e / np, i = e - r * np;
+    const float y = vred_sum<T>(red, h * NB + i / 32, i % 32, r, M) * inv_s[r];
+    const float o = __shfl_xor(y, 1, AIO_WAVE);
+    if (h == 0) vpair_epi<WFMT, EPI>(a, in[it], p0 + i, r, y, o);
   }
 }
 
@@ -1289,13 +1175,13 @@ hipError_t launch_vgemm(const aio_model& m, const VGemmArgs& g, int blocks) {
   }
   const dim3 grid(blocks, a.ks);
   if (m.cfg.wfmt == AIO_WFMT_INT8) {
-    constexpr int lds = vgemm_lds<AIO_WFMT_INT8>();
+    constexpr int lds = vgemm_lds<AIO_WFMT_INT8, 2>(64);
     const hipError_t e = hipFuncSetAttribute((const void*)k_vgemm<AIO_WFMT_INT8, EPI>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_vgemm<AIO_WFMT_INT8, EPI>), grid, dim3(kGBlock), lds, m.stream, a);
   } else {
-    constexpr int lds = vgemm_lds<AIO_WFMT_BF16>();
+    constexpr int lds = vgemm_lds<AIO_WFMT_BF16, 2>(64);
     const hipError_t e = hipFuncSetAttribute((const void*)k_vgemm<AIO_WFMT_BF16, EPI>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -1304,41 +1190,44 @@ hipError_t launch_vgemm(const aio_model& m, const VGemmArgs& g, int blocks) {
   return hipGetLastError();
 }
 
-// Stream-K launch of the gate/up product of `tiles` tile pairs: one
-// workgroup per CU, but every range at least `per` units long, so that at
-// most kSkMaxC - 1 ranges meet in one tile pair (a pair of nst units spans
-// at most 1 + ceil((nst - 1) / per) ranges).
+template <int WFMT, int EPI, int NB, int NLD, int NS>
+hipError_t launch_vpair_t(const aio_model& m, const VGemmArgs& a) {
+  using Vp = VPair<WFMT, NB, NLD, NS>;
+  const void* fn = (const void*)k_vpair<WFMT, EPI, NB, NLD, NS>;
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, Vp::Lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_vpair<WFMT, EPI, NB, NLD, NS>), dim3((a.pairs + a.np - 1) / a.np),
+                     dim3(kGBlock), Vp::Lds, m.stream, a);
+  return hipGetLastError();
+}
+
+// Launch of a product of `pairs` row pairs, in as few rounds of one workgroup
+// per CU as workgroups of at most 64 pairs allow, each round full.  The load
+// slots of a workgroup (16 rows of bf16, 32 of int8) round its pairs up; few
+// of them leave registers for more stages in flight.
 template <int EPI>
-hipError_t launch_vgemm_sk(const aio_model& m, const VGemmArgs& g, int tiles) {
+hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   VGemmArgs a = g;
   a.ks = 1;
   a.nt = m.cfg.d_model / 64;
   a.eps = m.cfg.rms_eps;
   a.ss_in = m.at<float>(m.lay.vss);
-  a.tiles = tiles;
-  a.skpart = m.at<float>(m.lay.skpart);
-  a.skcnt = m.at<int>(m.lay.skcnt);
-  if ((size_t)tiles > m.lay.sk_tiles) return hipErrorInvalidValue;
-  const int nst = (a.K / 32 + 7) / 8;  // stages of 256 k
-  const long long U = (long long)tiles * nst;
-  const int per = std::max(2, (nst - 1 + kSkMaxC - 3) / (kSkMaxC - 2));
-  const long long G = std::max<long long>(1, std::min<long long>(m.num_cus, U / per));
+  a.pairs = pairs;
+  const int rounds = (pairs + 64 * m.num_cus - 1) / (64 * m.num_cus);
+  a.np = (pairs + rounds * m.num_cus - 1) / (rounds * m.num_cus);
+  constexpr int I8 = AIO_WFMT_INT8, BF = AIO_WFMT_BF16;
   if (m.cfg.wfmt == AIO_WFMT_INT8) {
-    constexpr int lds = vgemm_lds<AIO_WFMT_INT8>();
-    const hipError_t e = hipFuncSetAttribute((const void*)k_vgemm_sk<AIO_WFMT_INT8, EPI>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_vgemm_sk<AIO_WFMT_INT8, EPI>), dim3((unsigned)G), dim3(kGBlock), lds,
-                       m.stream, a);
-  } else {
-    constexpr int lds = vgemm_lds<AIO_WFMT_BF16>();
-    const hipError_t e = hipFuncSetAttribute((const void*)k_vgemm_sk<AIO_WFMT_BF16, EPI>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_vgemm_sk<AIO_WFMT_BF16, EPI>), dim3((unsigned)G), dim3(kGBlock), lds,
-                       m.stream, a);
+    if (a.np <= 16) return launch_vpair_t<I8, EPI, 1, 1, 4>(m, a);
+    if (a.np <= 32) return launch_vpair_t<I8, EPI, 1, 2, 2>(m, a);
+    if (a.np <= 48) return launch_vpair_t<I8, EPI, 2, 3, 2>(m, a);
+    return launch_vpair_t<I8, EPI, 2, 4, 2>(m, a);
   }
-  return hipGetLastError();
+  if (a.np <= 8) return launch_vpair_t<BF, EPI, 1, 1, 4>(m, a);
+  if (a.np <= 16) return launch_vpair_t<BF, EPI, 1, 2, 4>(m, a);
+  if (a.np <= 24) return launch_vpair_t<BF, EPI, 1, 3, 2>(m, a);
+  if (a.np <= 32) return launch_vpair_t<BF, EPI, 1, 4, 2>(m, a);
+  if (a.np <= 48) return launch_vpair_t<BF, EPI, 2, 6, 2>(m, a);
+  return launch_vpair_t<BF, EPI, 2, 8, 2>(m, a);
 }
 
 // Split of x * g and chunk sums of squares for the M rows of x (layer 0:
@@ -1395,9 +1284,9 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
     g.N = (H + 2 * Hkv) * hd; g.K = d;
     g.out = q; g.ldo = H * hd;
     g.kc = m.kv_layer(l, 0); g.vc = m.kv_layer(l, 1);
-    g.rope = m.rope; g.st = m.state();
+    g.rope = m.rope; g.pos = pos;
     g.H = H; g.Hkv = Hkv; g.hd = hd; g.max_ctx = c.max_ctx;
-    if ((e = launch_vgemm<EPI_QKV>(m, g, (H + 2 * Hkv) * (hd / 64))) != hipSuccess) return e;
+    if ((e = launch_vpair<EPI_QKV>(m, g, (H + 2 * Hkv) * (hd / 2))) != hipSuccess) return e;
 
     VAttnArgs t{};
     t.q = q; t.kc = g.kc; t.vc = g.vc;
@@ -1423,7 +1312,7 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
     VGemmArgs o{};
     o.act = actB; o.lda = ka; o.M = M;
     o.w0 = L.wo; o.s0 = (const uint16_t*)L.so;
-    o.N = d; o.K = H * hd; o.out = x; o.ldo = d; o.st = m.state();
+    o.N = d; o.K = H * hd; o.out = x; o.ldo = d;
     o.g_next = (const uint16_t*)L.ffn_norm; o.act_next = actA;
     if ((e = launch_vgemm<EPI_RESID>(m, o, d / 64)) != hipSuccess) return e;
 
@@ -1431,13 +1320,13 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
     gu.act = actA; gu.lda = ka; gu.M = M;
     gu.w0 = L.w_gate; gu.w1 = L.w_up;
     gu.s0 = (const uint16_t*)L.s_gate; gu.s1 = (const uint16_t*)L.s_up;
-    gu.N = F; gu.K = d; gu.act_out = actB; gu.lda_out = ka; gu.st = m.state();
-    if ((e = launch_vgemm_sk<EPI_SWIGLU>(m, gu, (F + 31) / 32)) != hipSuccess) return e;
+    gu.N = F; gu.K = d; gu.act_out = actB; gu.lda_out = ka;
+    if ((e = launch_vpair<EPI_SWIGLU>(m, gu, F)) != hipSuccess) return e;
 
     VGemmArgs dn{};
     dn.act = actB; dn.lda = ka; dn.M = M;
     dn.w0 = L.w_down; dn.s0 = (const uint16_t*)L.s_down;
-    dn.N = d; dn.K = F; dn.out = x; dn.ldo = d; dn.st = m.state();
+    dn.N = d; dn.K = F; dn.out = x; dn.ldo = d;
     dn.g_next = (const uint16_t*)g_after; dn.act_next = actA;
     if ((e = launch_vgemm<EPI_RESID>(m, dn, d / 64)) != hipSuccess) return e;
   }
@@ -1451,7 +1340,7 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
   VGemmArgs lm{};
   lm.act = actA; lm.lda = ka; lm.M = M;
   lm.w0 = m.lm_head; lm.s0 = (const uint16_t*)m.s_lm_head;
-  lm.N = c.vocab; lm.K = d; lm.out = logits; lm.ldo = c.vocab; lm.st = m.state();
+  lm.N = c.vocab; lm.K = d; lm.out = logits; lm.ldo = c.vocab;
   return launch_vgemm<EPI_STORE>(m, lm, (c.vocab + 63) / 64);
 }
 
@@ -1464,6 +1353,6 @@ hipError_t aio_launch_lm_rows(const aio_model& m, int rows, float* logits) {
   VGemmArgs lm{};
   lm.act = actA; lm.lda = m.lay.ka; lm.M = rows;
   lm.w0 = m.lm_head; lm.s0 = (const uint16_t*)m.s_lm_head;
-  lm.N = c.vocab; lm.K = c.d_model; lm.out = logits; lm.ldo = c.vocab; lm.st = m.state();
+  lm.N = c.vocab; lm.K = c.d_model; lm.out = logits; lm.ldo = c.vocab;
   return launch_vgemm<EPI_STORE>(m, lm, (c.vocab + 63) / 64);
 }

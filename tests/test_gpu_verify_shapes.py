@@ -1,0 +1,40 @@
+"""The verify products' row pairs per workgroup at their edges (needs an MI355X with 256 CUs: np = pairs / 256, rounded up).  Each
+case is held to the bounds of the verify's oracle comparison: fp32 sums in
+another order, and one bf16 rounding per cache entry."""
+import pytest
+
+from tests import test_gpu_verify as verify
+
+pytestmark = pytest.mark.gpu
+
+ONE = dict(n_layers=1)
+WIDE_QKV = dict(n_layers=1, n_heads=64, n_kv_heads=64, head_dim=128)
+
+CASES = {
+    # gate/up with np pairs of rows per workgroup; the last workgroup is
+    # ragged where np does not divide the pairs
+    "np1": dict(ONE, ffn_dim=64),
+    "np8": dict(ONE, ffn_dim=2048),
+    "np9": dict(ONE, ffn_dim=2112),
+    "np17": dict(ONE, ffn_dim=4160),
+    "np25": dict(ONE, ffn_dim=6208),
+    "np33": dict(ONE, ffn_dim=8256),
+    "np49": dict(ONE, ffn_dim=12352),
+    "np64": dict(ONE, ffn_dim=16384),
+    # two rounds of workgroups, 33 pairs each
+    "two_rounds": dict(ONE, ffn_dim=16448),
+    "int8_np16": dict(ONE, ffn_dim=4096, wfmt="int8"),
+    "int8_np17": dict(ONE, ffn_dim=4160, wfmt="int8"),
+    "int8_np33": dict(ONE, ffn_dim=8256, wfmt="int8"),
+    "int8_np49": dict(ONE, ffn_dim=12352, wfmt="int8"),
+    # QKV with 48 pairs per workgroup (heads of 64 pairs, so workgroups start
+    # inside a head and span q, k and v), three ragged K stages
+    "qkv48": dict(WIDE_QKV, d_model=576),
+    "qkv48_int8": dict(WIDE_QKV, d_model=576, wfmt="int8"),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_verify_shapes(name, monkeypatch):
+    monkeypatch.setitem(verify.CASES, name, CASES[name])
+    verify.test_verify_equals_sequential_decode(name)
