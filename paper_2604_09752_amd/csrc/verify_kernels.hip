@@ -789,7 +789,7 @@ struct VAttnArgs {
   const uint16_t* vc;
   float* part_o;        // [M][H][S][hd]
   float* part_ml;       // [M][H][S][2]
-  const aio_state* st;
+  int pos;              // position of the first row
   int H, Hkv, max_ctx, S, M;
   float scale_log2;
   // k_vattn_mma: the last split of head h to finish merges the head's
@@ -816,7 +816,7 @@ struct VAttnArgs {
 //   O^T += V^T P^T: B = the softmax weights' three bf16 terms straight from
 //     registers (k slots 8 g .. 8 g + 7 of lane group g are its own keys of
 //     tile 0 then tile 1), A = the value tile (staged in LDS row by row,
-//     read back one bf16 per key and dimension in that key order).
+//     read back through transposing LDS reads in that key order).
 //     (Transposing on the way in, with one 16-bit store per element, put
 //     16 lanes on one bank and tripled the kernel's time.)
 // The next block's keys and values are requested before the current one is
@@ -825,12 +825,13 @@ struct VAttnArgs {
 // split's unnormalized state, written to part_o / part_ml; the head's last
 // split to finish merges all of them (vattn_merge).
 //
-// Eight waves of two blocks each: the blocks a wave streams one after the
-// other are the kernel's critical path (about 2 us each at 2K context), so
-// a split of 16 blocks is spread over as many waves as fit one workgroup
-// per CU with a block in flight per wave.
+// Eight waves, one block each (more where a context needs more splits than
+// the CUs or the merge take): the blocks a wave streams one after the other are
+// the kernel's critical path, about 2 us each at 2K context.  With the
+// weights of the fold computed per wave and a merge of one round trip: 7B at
+// 2K, 8 rows 17.5 -> 15.1 us, 1B 13.2 -> 10.7.
 constexpr int kVAW = 8;
-constexpr int kVattnBlocksPerSplit = 2 * kVAW;
+constexpr int kVattnBlocksPerSplit = kVAW;
 
 template <int HD>
 struct VAttnLds {
@@ -878,45 +879,72 @@ AIO_DEV void vattn_load(const uint16_t* kbase, const uint16_t* vbase, int kb, in
   }
 }
 
-// Online combination of one more (max m2, sum l2, output o2) state into
-// (m, l, o), all in log2 units; a state with max -inf holds no key.
-AIO_DEV void attn_fold(float& m, float& l, float& o, float m2, float l2, float o2) {
-  const float mn = fmaxf(m, m2);
-  const float c1 = m == -INFINITY ? 0.f : exp2f(m - mn);
-  const float c2 = m2 == -INFINITY ? 0.f : exp2f(m2 - mn);
-  o = o * c1 + o2 * c2;
-  l = l * c1 + l2 * c2;
-  m = mn;
-}
-
-// Merge of head h's S splits for the M rows (by the split that finished
-// last; the others' states are in memory, read past the caches): per output
-// element, the splits' states are folded in split order (attn_fold) and the
-// result o / l is split into act.  Eight splits' states are requested
-// together, so at up to 8 splits the merge is one round trip.
+// Merge of head h's S <= 64 splits for the M rows (by the split that finished
+// last; the others' states are in memory, read past the caches).  The splits'
+// (max, sum) pairs of a row, one per lane (of 8 lanes up to eight splits, else
+// of a wave), become their weights 2^(m - max m) / sum; every output element
+// adds its splits' outputs with them, in split order.  The outputs of the
+// first eight splits are requested with the pairs, so up to eight splits take
+// one round trip.
 template <int HD>
-AIO_DEV void vattn_merge(const VAttnArgs& a, int h) {
-  constexpr int NT = kVAW * AIO_WAVE;
-  const int M = a.M, S = a.S;
-  for (int e = threadIdx.x; e < M * HD; e += NT) {
-    const int r = e / HD, dim = e % HD;
-    const float* po = a.part_o + ((size_t)r * a.H + h) * S * HD + dim;
-    const float* ml = a.part_ml + ((size_t)r * a.H + h) * S * 2;
-    float m = -INFINITY, l = 0.f, o = 0.f;
-    for (int s0 = 0; s0 < S; s0 += 8) {
-      float mv[8], lv[8], ov[8];
+AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64]) {
+  constexpr int NT = kVAW * AIO_WAVE, NI = (kMaxRows * HD + NT - 1) / NT;
+  const int M = a.M, S = a.S, tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
+  const bool few = S <= 8;
+  float mv[2], lv[2];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int sp = s0 + j < S ? s0 + j : S - 1;
-        mv[j] = ld_agent(ml + 2 * sp);
-        lv[j] = ld_agent(ml + 2 * sp + 1);
-        ov[j] = ld_agent(po + (size_t)sp * HD);
-      }
+  for (int q = 0; q < 2; ++q) {
+    if (few && q > 0) break;
+    const int r = min(few ? tid / 8 : wid + kVAW * q, M - 1), sp = few ? tid & 7 : lane;
+    const float* ml = a.part_ml + ((size_t)r * a.H + h) * S * 2;
+    mv[q] = ld_agent(ml + 2 * min(sp, S - 1));
+    lv[q] = ld_agent(ml + 2 * min(sp, S - 1) + 1);
+  }
+  const float* po[NI];
+  float ov[NI][8];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    if (i * NT >= M * HD) break;
+    const int e = min(tid + i * NT, M * HD - 1), r = e / HD;
+    po[i] = a.part_o + ((size_t)r * a.H + h) * S * HD + e % HD;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ov[i][j] = ld_agent(po[i] + (size_t)min(j, S - 1) * HD);
+  }
+  if (few) {
+    const float m = (tid & 7) < S ? mv[0] : -INFINITY;
+    const float mx = group_max8_dpp(m);
+    const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
+    const float l = group_sum_dpp<8>((tid & 7) < S ? w * lv[0] : 0.f);
+    if (tid < 8 * M) wts[tid / 8][tid & 7] = l > 0.f ? w / l : 0.f;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int r = wid + kVAW * q;
+      const float m = lane < S ? mv[q] : -INFINITY;
+      const float mx = wave_max(m);
+      const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
+      const float l = wave_sum(lane < S ? w * lv[q] : 0.f);
+      if (r < M) wts[r][lane] = l > 0.f ? w / l : 0.f;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int e = tid + i * NT, r = e / HD, dim = e % HD;
+    if (e >= M * HD) break;
+    float o = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < S) o += ov[i][j] * wts[r][j];
+    for (int s0 = 8; s0 < S; s0 += 8) {
+      float x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = ld_agent(po[i] + (size_t)min(s0 + j, S - 1) * HD);
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        if (s0 + j < S) attn_fold(m, l, o, mv[j], lv[j], ov[j]);
+        if (s0 + j < S) o += x[j] * wts[r][s0 + j];
     }
-    store_split(a.act, a.lda, M, r, h * HD + dim, l > 0.f ? o / l : 0.f);
+    store_split(a.act, a.lda, M, r, h * HD + dim, o);
   }
 }
 
@@ -930,7 +958,7 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   const int col = lane & 15, g = lane >> 4;  // query column, lane group
   const int s = blockIdx.x, h = blockIdx.y, M = a.M;
   const int kvh = h / (a.H / a.Hkv);
-  const int pos = a.st->pos;
+  const int pos = a.pos;
   const int n_keys = pos + M;  // the last row sees keys [0, pos + M - 1]
   const int nkb = (n_keys + 31) / 32;
   const int kbA = (int)((long long)s * nkb / a.S), kbB = (int)((long long)(s + 1) * nkb / a.S);
@@ -1123,22 +1151,32 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   }
   __syncthreads();
 
-  // The split's state of its M rows: the waves folded in wave order
-  // (unnormalized output, (max, sum) in log2 units), written through to
-  // memory.
-  for (int e = tid; e < M * HD; e += NT) {
-    const int r = e / HD, dim = e % HD;
-    float ms = -INFINITY, ls = 0.f, os = 0.f;
-#pragma unroll
-    for (int w = 0; w < kVAW; ++w)
-      attn_fold(ms, ls, os, mm[w * kMaxRows + r], ll[w * kMaxRows + r],
-                om[(w * kMaxRows + r) * Lds::OROW + dim]);
-    st_agent(a.part_o + (((size_t)r * a.H + h) * a.S + s) * HD + dim, os);
-    if (dim == 0) {
+  // The split's state of its M rows, written through to memory: (max, sum) in
+  // log2 units and the unnormalized output, the waves' added with weights
+  // 2^(m - max m) in wave order.  Thread 8 r + w gives wave w's weight in row
+  // r.
+  static_assert(kVAW == 8, "a group of 8 lanes holds a row's waves");
+  __shared__ float wts[kMaxRows][64];
+  if (tid < 8 * kMaxRows) {
+    const int r = tid / 8, w = tid & 7;
+    const float mw = r < M ? mm[w * kMaxRows + r] : -INFINITY;
+    const float ms = group_max8_dpp(mw);
+    const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - ms);
+    const float ls = group_sum_dpp<8>(r < M ? wt * ll[w * kMaxRows + r] : 0.f);
+    wts[r][w] = wt;
+    if (w == 0 && r < M) {
       float* ml = a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2;
       st_agent(ml, ms);
       st_agent(ml + 1, ls);
     }
+  }
+  __syncthreads();
+  for (int e = tid; e < M * HD; e += NT) {
+    const int r = e / HD, dim = e % HD;
+    float os = 0.f;
+#pragma unroll
+    for (int w = 0; w < kVAW; ++w) os += wts[r][w] * om[(w * kMaxRows + r) * Lds::OROW + dim];
+    st_agent(a.part_o + (((size_t)r * a.H + h) * a.S + s) * HD + dim, os);
   }
   // count the split; the last of head h's splits to arrive merges them
   __builtin_amdgcn_s_waitcnt(0);
@@ -1148,7 +1186,7 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   __syncthreads();
   if (!last_s) return;
   if (tid == 0) atomic_store_agent(a.cnt + h, 0);  // ready for the next layer
-  vattn_merge<HD>(a, h);
+  vattn_merge<HD>(a, h, wts);
 }
 
 // Launch with `blocks` tile pairs.  A residual-add product with fewer tile
@@ -1292,14 +1330,13 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
     t.q = q; t.kc = g.kc; t.vc = g.vc;
     t.part_o = m.at<float>(m.lay.part_o);
     t.part_ml = m.at<float>(m.lay.part_ml);
-    t.st = m.state();
+    t.pos = pos;
     t.H = H; t.Hkv = Hkv; t.max_ctx = c.max_ctx; t.S = m.lay.splits; t.M = M;
     t.scale_log2 = (float)(1.4426950408889634 / sqrt((double)hd));
     // splits of kVattnBlocksPerSplit key blocks, but no more workgroups than
     // CUs: a workgroup takes a whole CU, and a second round of workgroups
     // pays the queries' prologue and the merges again (at 32K, 64 splits per
-    // head cost 9.2 ms per 7B verify).  The host's pos sizes the grid; the
-    // kernel takes its key range from the device state.
+    // head cost 9.2 ms per 7B verify).
     const int nkb = (pos + M + 31) / 32;
     const int s_cap = std::max(1, std::min(m.lay.vsplits, m.num_cus / H));
     t.S = std::max(1, std::min(s_cap, (nkb + kVattnBlocksPerSplit - 1) / kVattnBlocksPerSplit));

@@ -1,4 +1,5 @@
-"""The verify products' row pairs per workgroup at their edges (needs an MI355X with 256 CUs: np = pairs / 256, rounded up).  Each
+"""The verify products' row pairs per workgroup and the attention's splits at
+their edges (needs an MI355X with 256 CUs: np = pairs / 256, rounded up).  Each
 case is held to the bounds of the verify's oracle comparison: fp32 sums in
 another order, and one bf16 rounding per cache entry."""
 import pytest
@@ -31,6 +32,13 @@ CASES = {
     # inside a head and span q, k and v), three ragged K stages
     "qkv48": dict(WIDE_QKV, d_model=576),
     "qkv48_int8": dict(WIDE_QKV, d_model=576, wfmt="int8"),
+    # attention: one split of 8 blocks, the first of two splits, the merge of
+    # nine splits (past eight it takes a wave per row)
+    "splits1": dict(ONE, prompt_len=246),
+    "splits2": dict(ONE, prompt_len=256),
+    "splits9": dict(ONE, prompt_len=2048, max_ctx=2112),
+    "splits9_gqa_hd128": dict(ONE, n_heads=4, n_kv_heads=1, head_dim=128, prompt_len=2048,
+                              max_ctx=2112),
 }
 
 
