@@ -22,24 +22,11 @@ AIO_DEV uint16_t f32_to_bf16(float f) {
 
 AIO_DEV float fp16_to_f32(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 
-// Sum over the 64 lanes of a wave; every lane receives the total.
-AIO_DEV float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, AIO_WAVE);
-  return v;
-}
-
 // Sum over aligned groups of `width` lanes (a power of two <= 64).
 template <int WIDTH>
 AIO_DEV float group_sum(float v) {
 #pragma unroll
   for (int off = WIDTH / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, AIO_WAVE);
-  return v;
-}
-
-AIO_DEV float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, AIO_WAVE));
   return v;
 }
 
@@ -95,4 +82,43 @@ AIO_DEV float group_sum_dpp(float v) {
   v += dpp_mov<0x141>(v);  // row_half_mirror
   if (WIDTH == 16) v += dpp_mov<0x140>(v);  // row_mirror
   return v;
+}
+
+// Lane exchanges between the halves and between the rows of 16 of a wave, as
+// VALU swaps (an LDS exchange takes an LDS round trip and its wait):
+//   swap32: a = {a.lo, b.lo}, b = {a.hi, b.hi}   (lanes 0-31, 32-63)
+//   swap16: a = {a0, b0, a2, b2}, b = {a1, b1, a3, b3}   (rows of 16 lanes)
+AIO_DEV void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+AIO_DEV void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+// Sum and maximum over the 64 lanes of a wave; every lane receives the same
+// total.  Six VALU steps, where exchanges through LDS take six round trips.
+AIO_DEV float wave_sum(float v) {
+  v = group_sum_dpp<16>(v);
+  float o = v;
+  swap16(v, o);
+  v += o;
+  o = v;
+  swap32(v, o);
+  return v + o;
+}
+AIO_DEV float wave_max(float v) {
+  v = fmaxf(v, dpp_mov<0xB1>(v));
+  v = fmaxf(v, dpp_mov<0x4E>(v));
+  v = fmaxf(v, dpp_mov<0x141>(v));
+  v = fmaxf(v, dpp_mov<0x140>(v));
+  float o = v;
+  swap16(v, o);
+  v = fmaxf(v, o);
+  o = v;
+  swap32(v, o);
+  return fmaxf(v, o);
 }

@@ -68,10 +68,7 @@ namespace {
 
 constexpr int kT = 512;          // threads per workgroup
 constexpr int kW = kT / AIO_WAVE; // waves per workgroup
-#ifndef AIO_STEP_NLD
-#define AIO_STEP_NLD 8
-#endif
-constexpr int kNLD = AIO_STEP_NLD;  // 16-byte weight loads per lane per batch
+constexpr int kNLD = 8;  // 16-byte weight loads per lane per batch
 // Batches in flight per wave (register buffers).  A deeper prefetch streams
 // the loops a little faster but delays the input poll queued behind it
 // (vector memory returns in order).
@@ -439,52 +436,64 @@ AIO_DEV void issue(const MegaArgs& a, const GPhase& P, int batch, uint4 (&buf)[k
   }
 }
 
-// Reduce N per-lane values over the 64 lanes of a wave.  Each halving
-// exchange (offsets 32, 16, ...) keeps half of the values, so after log2 N
-// of them lane l holds value (l >> (6 - log2 N)) & (N - 1) summed over N
-// lanes; plain exchanges finish the sum within groups of 64 / N lanes
-// (10 shuffles for 8 values instead of 48).
-template <int N>
-constexpr int log2_of() { return N == 8 ? 3 : (N == 4 ? 2 : (N == 2 ? 1 : 0)); }
+// Reduce 8 per-lane values over the 64 lanes of a wave.  Each of three halving
+// exchanges (lane bits 5, 4, 3) keeps half of the values, so lane l then holds
+// value l / 8 summed over 8 lanes; plain exchanges finish the sum within
+// groups of 8 lanes.  All of them are VALU swaps and DPP moves: as shuffles
+// through LDS, a batch's ten exchanges were six LDS round trips on the path
+// from the last weights of a phase to its outputs.  With the norm sums and the
+// fold of the attention's lane groups exchanged the same way, per token at 2K:
+// 1B 812 -> 772 us, 7B 2420 -> 2365, 7B int8 1810 -> 1740.
+constexpr int kRed = 8;
+static_assert(kNLD == kRed, "a batch leaves at most 8 sums per lane");
 
-// One halving exchange over lane bit OFF: values [0, HALF) keep the lower
-// or upper half of [0, 2 HALF) and add the partner's other half.
-template <int OFF, int HALF, int N>
-AIO_DEV void halve(float (&v)[N], int lane) {
-  const bool up = lane & OFF;
+// One halving exchange over lane bit 3 or 2 (with lane l ^ 8 or l ^ 7): values
+// [0, HALF) keep the lower or upper half of [0, 2 HALF) and add the partner's
+// other half.
+template <int BIT, int HALF>
+AIO_DEV void halve(float (&v)[kRed], int lane) {
+  constexpr int CTRL = BIT == 8 ? 0x128 : 0x141;  // row_ror:8, row_half_mirror
+  const bool up = lane & BIT;
 #pragma unroll
   for (int i = 0; i < HALF; ++i) {
     const float send = up ? v[i] : v[i + HALF], keep = up ? v[i + HALF] : v[i];
-    v[i] = keep + __shfl_xor(send, OFF, AIO_WAVE);
+    v[i] = keep + dpp_mov<CTRL>(send);
+  }
+}
+// The same over bit 5 and 4.
+template <int HALF>
+AIO_DEV void halve32(float (&v)[kRed]) {
+#pragma unroll
+  for (int i = 0; i < HALF; ++i) {
+    swap32(v[i], v[i + HALF]);
+    v[i] += v[i + HALF];
+  }
+}
+template <int HALF>
+AIO_DEV void halve16(float (&v)[kRed]) {
+#pragma unroll
+  for (int i = 0; i < HALF; ++i) {
+    swap16(v[i], v[i + HALF]);
+    v[i] += v[i + HALF];
   }
 }
 
-template <int N>
-AIO_DEV float reduce_rows(float (&v)[N], int lane) {
-  static_assert(N == 2 || N == 4 || N == 8, "reduce_rows takes 2, 4 or 8 values");
-  constexpr int LOG = log2_of<N>();
-  halve<32, N / 2>(v, lane);
-  if constexpr (N >= 4) halve<16, N / 4>(v, lane);
-  if constexpr (N >= 8) halve<8, 1>(v, lane);
-  float s = v[0];
-#pragma unroll
-  for (int off = 32 >> LOG; off >= 1; off >>= 1) s += __shfl_xor(s, off, AIO_WAVE);
-  return s;
+AIO_DEV float reduce_rows(float (&v)[kRed], int lane) {
+  halve32<4>(v);
+  halve16<2>(v);
+  halve<8, 1>(v, lane);
+  return group_sum_dpp<8>(v[0]);
 }
 
 // The same over each half wave (lanes 0-31 and 32-63 separately): lane l
-// then holds value ((l >> (5 - log2 N)) & (N - 1)) of half l / 32.
-template <int N>
-AIO_DEV float reduce_rows_half(float (&v)[N], int lane) {
-  static_assert(N == 2 || N == 4 || N == 8, "reduce_rows_half takes 2, 4 or 8 values");
-  constexpr int LOG = log2_of<N>();
-  halve<16, N / 2>(v, lane);
-  if constexpr (N >= 4) halve<8, N / 4>(v, lane);
-  if constexpr (N >= 8) halve<4, 1>(v, lane);
+// then holds value (l / 4) % 8 of half l / 32.
+AIO_DEV float reduce_rows_half(float (&v)[kRed], int lane) {
+  halve16<4>(v);
+  halve<8, 2>(v, lane);
+  halve<4, 1>(v, lane);
   float s = v[0];
-#pragma unroll
-  for (int off = 16 >> LOG; off >= 1; off >>= 1) s += __shfl_xor(s, off, AIO_WAVE);
-  return s;
+  s += dpp_mov<0x4E>(s);         // lane ^ 2
+  return s + dpp_mov<0xB1>(s);   // lane ^ 1
 }
 
 // Multiply-accumulate one batch and leave each wave's row partials in LDS
@@ -516,19 +525,18 @@ AIO_DEV void compute(const GPhase& P, int batch, const uint4 (&buf)[kNLD],
       t = dot4_i8(w.w, make_float4(h[v][12], h[v][13], h[v][14], h[v][15]), t);
     }
   }
-  constexpr int LOG = log2_of<kNLD>();
   if constexpr (lpr<WFMT>() < AIO_WAVE) {
-    const float s = reduce_rows_half<kNLD>(acc, lane);
-    const int idx = (lane >> (5 - LOG)) & (kNLD - 1), hf = lane >> 5;
-    if ((lane & ((AIO_WAVE / 2 >> LOG) - 1)) == 0 && idx < UB * RPU) {
+    const float s = reduce_rows_half(acc, lane);
+    const int idx = (lane >> 2) & (kRed - 1), hf = lane >> 5;
+    if ((lane & 3) == 0 && idx < UB * RPU) {
       const int ul = idx / RPU, r = idx % RPU;
       const int lu = batch * 2 * UB + 2 * ul + hf;
       if (P.u0 + lu < P.u1) red[(lu * RPU + r) * kW + wave] = s;
     }
   } else {
-    const float s = reduce_rows<kNLD>(acc, lane);
-    const int idx = (lane >> (6 - LOG)) & (kNLD - 1);
-    if ((lane & ((AIO_WAVE >> LOG) - 1)) == 0 && idx < UB * RPU) {
+    const float s = reduce_rows(acc, lane);
+    const int idx = lane >> 3;
+    if ((lane & 7) == 0 && idx < UB * RPU) {
       const int ul = idx / RPU, r = idx % RPU;
       const int lu = batch * UB + ul;
       if (P.u0 + lu < P.u1) red[(lu * RPU + r) * kW + wave] = s;
@@ -1003,6 +1011,37 @@ AIO_DEV void attend_key(uint4 kk, uint4 vv, bool valid, const float (&q)[G][8],
   }
 }
 
+// Fold the softmax states of lanes l and l ^ OFF (8, 16 or 32) into one, held
+// by both: a and b are the states of the lane with bit OFF clear and set (for 8
+// the lane's own and its partner's).
+template <int OFF>
+AIO_DEV void lane_pair(float v, float& a, float& b) {
+  a = b = v;
+  if constexpr (OFF == 32) swap32(a, b);
+  else if constexpr (OFF == 16) swap16(a, b);
+  else b = dpp_mov<0x128>(v);  // row_ror:8
+}
+template <int OFF, int G>
+AIO_DEV void attn_fold(float (&o)[G][8], float (&m)[G], float (&l)[G]) {
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) {
+    float ma, mb, la, lb;
+    lane_pair<OFF>(m[gg], ma, mb);
+    lane_pair<OFF>(l[gg], la, lb);
+    const float mx = fmaxf(ma, mb);
+    const float ca = ma == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ma - mx);
+    const float cb = mb == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mb - mx);
+    l[gg] = la * ca + lb * cb;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float oa, ob;
+      lane_pair<OFF>(o[gg][i], oa, ob);
+      o[gg][i] = oa * ca + ob * cb;
+    }
+    m[gg] = mx;
+  }
+}
+
 // Four keys of a group: their K and V rows.
 struct KV4 {
   uint4 k[4], v[4];
@@ -1101,7 +1140,7 @@ AIO_DEV void attn_merge(const MegaArgs& a, int g, float* lds, unsigned ver) {
       const float ms = untagf(v[3 * i + 1]);
       if (need[3 * i] && ms != -INFINITY) {
         const float mn = fmaxf(Mt, ms);
-        const float c0 = exp2f(Mt - mn), c1 = exp2f(ms - mn);
+        const float c0 = __builtin_amdgcn_exp2f(Mt - mn), c1 = __builtin_amdgcn_exp2f(ms - mn);
         Ot = Ot * c0 + c1 * untagf(v[3 * i]);
         Lt = Lt * c0 + c1 * untagf(v[3 * i + 2]);
         Mt = mn;
@@ -1125,7 +1164,7 @@ AIO_DEV void attn_merge(const MegaArgs& a, int g, float* lds, unsigned ver) {
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       const float mk = sm_M[k * G + gg];
-      const float w = mk == -INFINITY ? 0.f : exp2f(mk - M);
+      const float w = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk - M);
       Os = fmaf(w, sm_O[k * NOUT + c], Os);
       Ls = fmaf(w, sm_L[k * G + gg], Ls);
     }
@@ -1240,22 +1279,9 @@ AIO_DEV void attn_phase(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y, f
     // combine the groups: the AIO_WAVE / LPK groups of each wave with lane
     // exchanges (every group of the wave ends with the wave's state), then
     // the kW wave states in LDS
-#pragma unroll
-    for (int off = LPK; off < AIO_WAVE; off <<= 1) {
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        const float m2 = __shfl_xor(m[gg], off, AIO_WAVE);
-        const float l2 = __shfl_xor(l[gg], off, AIO_WAVE);
-        const float mx = fmaxf(m[gg], m2);
-        const float c1 = m[gg] == -INFINITY ? 0.f : exp2f(m[gg] - mx);
-        const float c2 = m2 == -INFINITY ? 0.f : exp2f(m2 - mx);
-        l[gg] = l[gg] * c1 + l2 * c2;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          o[gg][i] = o[gg][i] * c1 + __shfl_xor(o[gg][i], off, AIO_WAVE) * c2;
-        m[gg] = mx;
-      }
-    }
+    if constexpr (LPK == 8) attn_fold<8, G>(o, m, l);
+    attn_fold<16, G>(o, m, l);
+    attn_fold<32, G>(o, m, l);
     if (T.lane < LPK) {  // group 0 of each wave
 #pragma unroll
       for (int gg = 0; gg < G; ++gg) {
@@ -1278,7 +1304,7 @@ AIO_DEV void attn_phase(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y, f
 #pragma unroll
         for (int w = 0; w < kW; ++w) {
           const float mk = sm_m[w * G + gg];
-          const float wt = mk == -INFINITY ? 0.f : exp2f(mk - M);
+          const float wt = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk - M);
           Ot = fmaf(wt, sm_o[(w * G + gg) * HD + dim], Ot);
           Lt = fmaf(wt, sm_l[w * G + gg], Lt);
         }

@@ -254,7 +254,7 @@ AIO_DEV void vmma(const VFrag<WFMT, T>& f, bool col_live, f32x16 (&acc)[T]) {
 // LDS of a skinny-GEMM workgroup (the eight waves' sums meet in one step there,
 // and the epilogue's operands are requested before the loop.  Two steps, half
 // of the waves adding to the other half's, and late requests took 0.5 to 1.0
-// us more per product: O 7B 12.2 -> 11.6, int8 11.0 -> 10.0, 1B 7.6 -> 6.9;
+// us more per product, at the same rows and positions: O 7B 12.2 -> 11.6, int8 11.0 -> 10.0, 1B 7.6 -> 6.9;
 // down 22.0 -> 21.3, 18.3 -> 17.4, 10.6 -> 10.1): the weight stage during the product, then
 // the waves' partial tiles [waves][T] of [32][33] (with four tiles each 16
 // floats longer, so that the two rows of a pair, two tiles apart, lie in
@@ -614,11 +614,11 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
 // and ii + hd / 2 of a head section, SWIGLU: the same row of gate and up).
 // Workgroup b owns the np pairs from np b: as many as spread the product
 // evenly over the CUs, up to 64, so every CU streams the same bytes in one
-// workgroup.  Measured with 2-3 or 8 rows at 2K, in us, against workgroups of
-// whole 32-row tile pairs (QKV) and tile pairs dealt out over the CUs whose
+// workgroup.  Measured (7B: 9 rows at 2048, 1B: 3 rows at 1531), in us, against
+// workgroups of whole 32-row tile pairs (QKV) and tile pairs dealt out over the CUs whose
 // shares then met through memory (SWIGLU): gate/up 7B bf16 (43 pairs) 38.2 ->
-// 34.0, int8 27.0 -> 23.3, 1B (22 pairs) 15.3 -> 11.1; QKV 1B (5 pairs) 10.8
-// -> 7.7, 7B int8 (24 pairs) 16.6 -> 16.2.  The 7B's bf16 QKV does not gain
+// 34.0, int8 27.0 -> 23.3, 1B (22 pairs) 15.3 -> 11.1; QKV 1B (8 pairs; 32
+// before, on 64 CUs) 10.8 -> 7.7, 7B int8 (24 pairs) 16.6 -> 16.2.  The 7B's bf16 QKV does not gain
 // (22.3 -> 23.2): its 192 workgroups of 32 pairs already streamed at the rate
 // HBM gives.  Other np (22 to 64) were within 3 % or slower.
 //
@@ -828,8 +828,8 @@ struct VAttnArgs {
 // Eight waves, one block each (more where a context needs more splits than
 // the CUs or the merge take): the blocks a wave streams one after the other are
 // the kernel's critical path, about 2 us each at 2K context.  With the
-// weights of the fold computed per wave and a merge of one round trip: 7B at
-// 2K, 8 rows 17.5 -> 15.1 us, 1B 13.2 -> 10.7.
+// weights of the fold computed per wave and a merge of one round trip: 7B, 9
+// rows at 2048, 17.5 -> 15.1 us, 1B, 3 rows at 1531, 13.2 -> 10.7.
 constexpr int kVAW = 8;
 constexpr int kVattnBlocksPerSplit = kVAW;
 
