@@ -59,6 +59,8 @@ struct MegaArgs {
   const int* gu_bounds;            // [blocks + 1] gate/up units of each workgroup (null: even split)
   int L, d, H, Hkv, hd, F, V, max_ctx, S;
   int red_words;   // floats of one LDS buffer of matrix-phase partials
+  int each[5], rest[5];  // units per workgroup by Kind, and how many own one more
+  unsigned s_inv;  // 2^32 / S rounded up (0 for S = 1)
   float eps, scale_log2;
 };
 

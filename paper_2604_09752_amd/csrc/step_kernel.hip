@@ -311,15 +311,18 @@ AIO_DEV GPhase make_phase(const MegaArgs& a, int layer) {
   P.nvw = P.K / (kW * epv<WFMT>());
   const int nu = n_units<KIND>(a);
   P.nu = nu;
-  const int b = blockIdx.x, nbk = gridDim.x;
+  const int b = blockIdx.x;
   if (KIND == K_GU && a.gu_bounds) {
     // calibrated split (aio_tune_step), read as wave-uniform scalars
     typedef __attribute__((address_space(4))) const int cint;
     P.u0 = ((cint*)a.gu_bounds)[b];
     P.u1 = ((cint*)a.gu_bounds)[b + 1];
   } else {
-    P.u0 = (int)((long long)b * nu / nbk);
-    P.u1 = (int)((long long)(b + 1) * nu / nbk);
+    // the first `rest` workgroups own one unit more than the others (from the
+    // host: the division by the grid was a few hundred instructions per phase)
+    const int each = a.each[KIND], rest = a.rest[KIND];
+    P.u0 = b * each + (b < rest ? b : rest);
+    P.u1 = P.u0 + each + (b < rest ? 1 : 0);
   }
   return P;
 }
@@ -343,7 +346,7 @@ AIO_DEV const char* row_base(const MegaArgs& a, const GPhase& P, int u, int r) {
     constexpr int half = HD / 2;
     const int p = 2 * u + (r & 1);
     int v = (p / half) * HD + (p % half) + (r >> 1) * half;  // virtual row
-    const int qrows = a.H * a.hd, krows = a.Hkv * a.hd;
+    const int qrows = a.H * HD, krows = a.Hkv * HD;
     if (v >= qrows + krows) { mat = 2; v -= qrows + krows; }
     else if (v >= qrows) { mat = 1; v -= qrows; }
     row = v;
@@ -726,23 +729,25 @@ struct EpiPre {
 struct QkvRow {
   int i, sec, rlo;
 };
+template <int HD>
 AIO_DEV QkvRow qkv_row(const MegaArgs& a, int u) {
-  const int half = a.hd / 2, qrows = a.H * a.hd, krows = a.Hkv * a.hd;
+  constexpr int half = HD / 2;
+  const int qrows = a.H * HD, krows = a.Hkv * HD;
   const int p = 2 * u, head = p / half, i = p % half;  // pairs p, p+1 -> dims i, i+1
-  int sec = 0, rlo = head * a.hd + i;                   // virtual row of dim i
+  int sec = 0, rlo = head * HD + i;                     // virtual row of dim i
   if (rlo >= qrows + krows) { sec = 2; rlo -= qrows + krows; }
   else if (rlo >= qrows) { sec = 1; rlo -= qrows; }
   return QkvRow{i, sec, rlo};
 }
 
-template <int WFMT, int KIND>
+template <int WFMT, int KIND, int HD>
 AIO_DEV EpiPre epi_fetch(const MegaArgs& a, const GPhase& P, int pos, int u) {
   EpiPre e;
   e.cs = make_float4(0.f, 0.f, 0.f, 0.f);
   e.s[0] = e.s[1] = 0u;
   if constexpr (KIND == K_QKV) {
-    const QkvRow r = qkv_row(a, u);
-    const int half = a.hd / 2;
+    const QkvRow r = qkv_row<HD>(a, u);
+    constexpr int half = HD / 2;
     const u32x4 c = *(gl_u32x4*)(a.rope + (size_t)pos * half + r.i);
     e.cs = make_float4(__uint_as_float(c.x), __uint_as_float(c.y), __uint_as_float(c.z),
                        __uint_as_float(c.w));
@@ -763,7 +768,7 @@ AIO_DEV float fp16_hi(uint32_t w) { return fp16_to_f32((uint16_t)(w >> 16)); }
 
 // Epilogue of a matrix phase: sum the kW wave partials of each row, then the
 // phase-specific output, stored with version `vo`.
-template <int WFMT, int KIND>
+template <int WFMT, int KIND, int HD>
 AIO_DEV void epilogue(const MegaArgs& a, const GPhase& P, int layer, int pos, const float* red,
                       Smem& sm, float& xr, const EpiPre& pre, float inv, const Thr& T,
                       unsigned vo, unsigned ep0) {
@@ -793,10 +798,10 @@ AIO_DEV void epilogue(const MegaArgs& a, const GPhase& P, int layer, int pos, co
     }
     const int u = P.u0 + t;
     // the prefetched epilogue inputs serve the first unit; a later one loads its own
-    const EpiPre e = t == tid ? pre : epi_fetch<WFMT, KIND>(a, P, pos, u);
+    const EpiPre e = t == tid ? pre : epi_fetch<WFMT, KIND, HD>(a, P, pos, u);
     if constexpr (KIND == K_QKV) {
-      const int half = a.hd / 2;
-      const QkvRow qr = qkv_row(a, u);
+      constexpr int half = HD / 2;
+      const QkvRow qr = qkv_row<HD>(a, u);
       const int sec = qr.sec, rlo = qr.rlo;
       // y[0] = dim i, y[1] = dim i+1, y[2] = dim i+half, y[3] = dim i+1+half
       if constexpr (WFMT == AIO_WFMT_INT8) {
@@ -820,14 +825,14 @@ AIO_DEV void epilogue(const MegaArgs& a, const GPhase& P, int layer, int pos, co
         st_tag(a.q + rlo + half, y[2], vo);
         st_tag(a.q + rlo + half + 1, y[3], vo);
       } else {
-        const int g = rlo / a.hd, ii = rlo % a.hd;
-        uint16_t* c = (sec == 1 ? kc : vc) + ((size_t)g * a.max_ctx + pos) * a.hd;
+        const int g = rlo / HD, ii = rlo % HD;
+        uint16_t* c = (sec == 1 ? kc : vc) + ((size_t)g * a.max_ctx + pos) * HD;
         const unsigned b0 = f32_to_bf16(y[0]), b1 = f32_to_bf16(y[1]);
         const unsigned b2 = f32_to_bf16(y[2]), b3 = f32_to_bf16(y[3]);
         st_dev((unsigned*)(c + ii), b0 | (b1 << 16));
         st_dev((unsigned*)(c + ii + half), b2 | (b3 << 16));
         // the same bf16 values, tagged, for this step's attention
-        unsigned* n = a.kvn + ((size_t)(sec - 1) * a.Hkv + g) * a.hd + ii;
+        unsigned* n = a.kvn + ((size_t)(sec - 1) * a.Hkv + g) * HD + ii;
         st_dev(n, (b0 << 16) | vo);
         st_dev(n + 1, (b1 << 16) | vo);
         st_dev(n + half, (b2 << 16) | vo);
@@ -916,7 +921,7 @@ AIO_DEV void gemv_phase(const MegaArgs& a, int layer, int pos, int token, Bufs& 
   EpiPre pre;
   {
     const int t = T.tid < P.u1 - P.u0 ? T.tid : 0;
-    pre = epi_fetch<WFMT, KIND>(a, P, pos, P.u0 + t < P.nu ? P.u0 + t : P.nu - 1);
+    pre = epi_fetch<WFMT, KIND, HD>(a, P, pos, P.u0 + t < P.nu ? P.u0 + t : P.nu - 1);
   }
   // batch 0 is in flight (prefetch); then the input words, then the other
   // batches, so the wait for the input is queued behind one batch only
@@ -956,7 +961,7 @@ AIO_DEV void gemv_phase(const MegaArgs& a, int layer, int pos, int token, Bufs& 
     for (int w = 0; w < kW; ++w) tot += ss8[w];
     inv = rsqrtf(tot / (float)P.K + a.eps);
   }
-  epilogue<WFMT, KIND>(a, P, layer, pos, red, sm, xr, pre, inv, T, ver_of(ep0, k), ep0);
+  epilogue<WFMT, KIND, HD>(a, P, layer, pos, red, sm, xr, pre, inv, T, ver_of(ep0, k), ep0);
   if (KIND != K_LM) {
     // A workgroup's memory requests leave its CU in the order they were
     // issued, by whatever wave.  The outputs are stored by the first waves
@@ -1114,14 +1119,20 @@ struct AUnit {
   int g, s, j, nk, nkw, jd;  // jd: a row read by masked slots
 };
 
+// n / S, for n S below 2^32 (s_inv is 2^32 / S rounded up, 0 for S = 1).
+AIO_DEV unsigned div_s(const MegaArgs& a, unsigned n) {
+  const unsigned q = __umulhi(n, a.s_inv);
+  return a.s_inv ? q : n;
+}
+
 template <int HD>
 AIO_DEV AUnit attn_unit(const MegaArgs& a, int layer, int unit, int pos, const Thr& T) {
   constexpr int LPK = HD / 8, NGR = kT / LPK, GPW = AIO_WAVE / LPK;
   const int S = a.S;
   AUnit u;
-  u.g = unit / S;
-  u.s = unit % S;
-  const int chunk = (pos + S - 1) / S;
+  u.g = (int)div_s(a, (unsigned)unit);
+  u.s = unit - u.g * S;
+  const int chunk = (int)div_s(a, (unsigned)(pos + S - 1));
   const int j0 = min(pos, u.s * chunk), j1 = min(pos, j0 + chunk);
   const int n = j1 - j0;
   const int gi = T.tid / LPK, li = T.tid % LPK, gw = T.wave * GPW;
@@ -1380,8 +1391,11 @@ AIO_DEV void attn_phase(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y, f
   stamp_detail(a, k, 0);
   // splits per merging thread (R threads per output): as many loads as
   // there are splits to fold
-  for (int g = 0; g < a.Hkv; ++g) {
-    if ((g * S + S - 1) % (int)gridDim.x != (int)blockIdx.x) continue;
+  // (over this workgroup's units: testing every head for its last split took
+  // a division each, 2.3 of the attention's 10.4 us with 32 heads)
+  for (int unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    const int g = (int)div_s(a, (unsigned)unit);
+    if (unit != g * S + S - 1) continue;
     if (S <= 2 * R) attn_merge<HD, G, 2>(a, g, lds, vo);
     else if (S <= 8 * R) attn_merge<HD, G, 8>(a, g, lds, vo);
     else attn_merge<HD, G, 16>(a, g, lds, vo);
@@ -1562,6 +1576,13 @@ hipError_t aio_launch_step_kernel(const aio_model& m, float* logits, int32_t* to
   a.max_ctx = c.max_ctx;
   a.S = m.lay.mega_splits;
   a.red_words = red_words(c, m.mega_blocks);
+  const int units[5] = {(c.n_heads + 2 * c.n_kv_heads) * c.head_dim / 4, c.d_model, c.ffn_dim,
+                        c.d_model, c.vocab};  // by Kind
+  for (int k = 0; k < 5; ++k) {
+    a.each[k] = units[k] / m.mega_blocks;
+    a.rest[k] = units[k] % m.mega_blocks;
+  }
+  a.s_inv = a.S > 1 ? (unsigned)(((1ull << 32) + (unsigned)a.S - 1) / (unsigned)a.S) : 0u;
   a.eps = c.rms_eps;
   a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)c.head_dim));
   const int blocks = m.mega_blocks;
