@@ -66,6 +66,20 @@
 
 namespace {
 
+// The kernel's arguments, read where they lie.  Each phase takes a fresh pointer
+// that the compiler cannot see through, so that it loads the few it needs
+// (scalar loads) instead of keeping all of them over the whole kernel, where
+// they were spilled to vector register lanes and read back one by one in every
+// phase (some 400 spilled scalars; now 8, and no scratch memory.  Tiny decoder
+// 67.5 -> 64.2 us per token, 1B at 2K 734 -> 712, 7B 2278 -> 2258, int8 1599 ->
+// 1575).
+typedef __attribute__((address_space(4))) const MegaArgs CArgs;
+AIO_DEV CArgs& step_args() {
+  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(CArgs*)p;
+}
+
 constexpr int kT = 512;          // threads per workgroup
 constexpr int kW = kT / AIO_WAVE; // waves per workgroup
 constexpr int kNLD = 8;  // 16-byte weight loads per lane per batch
@@ -91,14 +105,15 @@ constexpr int rpu_of() { return KIND == K_QKV ? 4 : (KIND == K_GU ? 2 : 1); }
 
 // ---------------------------------------------------------- coherent access
 
+typedef __attribute__((address_space(1))) unsigned gl_u32;
 AIO_DEV unsigned ld_dev(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load((const gl_u32*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 AIO_DEV void st_dev(unsigned* p, unsigned v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store((gl_u32*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 AIO_DEV unsigned add_dev(unsigned* p, unsigned v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_add((gl_u32*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // 16-byte device-scope load of words base[off .. off + 3].  `base` must be
@@ -142,7 +157,7 @@ AIO_DEV bool tags_ok(const u32x4 v, unsigned ver) {
 // One step of a bounded wait.  Once any wait has given up (the error word is
 // set), every later wait stops at its next check, so a value that never
 // arrives costs well under a second instead of hanging the device.
-AIO_DEV bool spin_on(const MegaArgs& a, unsigned& spins) {
+AIO_DEV bool spin_on(CArgs& a, unsigned& spins) {
   __builtin_amdgcn_s_sleep(2);
   if ((++spins & 63u) == 0) {
     if (ld_dev(a.sync + kSyncErr) != 0u) return false;
@@ -184,7 +199,7 @@ AIO_DEV bool stale16(const bool (&need)[N], const u32x4 (&v)[N], unsigned ver) {
   return stale;
 }
 template <int N>
-AIO_DEV void await16(const MegaArgs& a, const unsigned* base, const int (&off)[N],
+AIO_DEV void await16(CArgs& a, const unsigned* base, const int (&off)[N],
                      const bool (&need)[N], u32x4 (&v)[N], unsigned ver) {
   if (!stale16(need, v, ver)) return;
   unsigned spins = 0;
@@ -206,7 +221,7 @@ AIO_DEV bool stale4(const bool (&need)[N], const unsigned (&v)[N], unsigned ver)
   return stale;
 }
 template <int N>
-AIO_DEV void await4(const MegaArgs& a, const unsigned* base, const int (&off)[N],
+AIO_DEV void await4(CArgs& a, const unsigned* base, const int (&off)[N],
                     const bool (&need)[N], unsigned (&v)[N], unsigned ver) {
   if (!stale4(need, v, ver)) return;
   unsigned spins = 0;
@@ -222,7 +237,7 @@ AIO_DEV void await4(const MegaArgs& a, const unsigned* base, const int (&off)[N]
 AIO_DEV void stamp(unsigned long long* arr, unsigned k) {
   if (arr && threadIdx.x == 0) arr[(size_t)k * gridDim.x + blockIdx.x] = wall_clock64();
 }
-AIO_DEV void stamp_detail(const MegaArgs& a, unsigned k, int col) {
+AIO_DEV void stamp_detail(CArgs& a, unsigned k, int col) {
   if (a.detail && threadIdx.x == 0)
     a.detail[((size_t)k * gridDim.x + blockIdx.x) * 2 + col] = wall_clock64();
 }
@@ -235,7 +250,7 @@ AIO_DEV void stamp_detail(const MegaArgs& a, unsigned k, int col) {
 // loads already in flight, and the first use of the pointer inside a weight
 // loop would then wait for all of them.
 typedef __attribute__((address_space(4))) const MegaLayer CMegaLayer;
-AIO_DEV const CMegaLayer* layer_at(const MegaArgs& a, int layer) {
+AIO_DEV const CMegaLayer* layer_at(CArgs& a, int layer) {
   return (const CMegaLayer*)(a.layers + layer);
 }
 
@@ -279,7 +294,7 @@ AIO_DEV int lane_vec(int v, int lane) {
 // Units of a matrix phase: QKV unit u = rotation pairs 2u, 2u+1 (rows lo
 // and hi of each); GU unit = row n of gate and of up; else one row.
 template <int KIND>
-AIO_DEV int n_units(const MegaArgs& a) {
+AIO_DEV int n_units(CArgs& a) {
   if (KIND == K_QKV) return (a.H + 2 * a.Hkv) * a.hd / 4;
   if (KIND == K_O || KIND == K_DOWN) return a.d;
   if (KIND == K_GU) return a.F;
@@ -287,7 +302,7 @@ AIO_DEV int n_units(const MegaArgs& a) {
 }
 
 template <int WFMT, int KIND>
-AIO_DEV GPhase make_phase(const MegaArgs& a, int layer) {
+AIO_DEV GPhase make_phase(CArgs& a, int layer) {
   GPhase P;
   const CMegaLayer* L = layer_at(a, layer < a.L ? layer : 0);
   P.w1 = P.w2 = nullptr;
@@ -339,7 +354,7 @@ AIO_DEV T* pick3(int i, T* p0, T* p1, T* p2) {
 
 // Row r of unit u as (matrix base, row index in it, scale array).
 template <int WFMT, int KIND, int HD>
-AIO_DEV const char* row_base(const MegaArgs& a, const GPhase& P, int u, int r) {
+AIO_DEV const char* row_base(CArgs& a, const GPhase& P, int u, int r) {
   constexpr size_t wb = WFMT == AIO_WFMT_BF16 ? 2 : 1;
   int mat = 0, row = u;
   if (KIND == K_QKV) {
@@ -388,7 +403,7 @@ AIO_DEV bool slot_ok(const GPhase& P, int u, int vi) { return u < P.u1 && vi < P
 // to count the loads in flight, and it would then wait for all of them --
 // both buffers -- before every batch.
 template <int WFMT, int KIND, int VPL, int HD>
-AIO_DEV void issue(const MegaArgs& a, const GPhase& P, int batch, uint4 (&buf)[kNLD], const Thr& T) {
+AIO_DEV void issue(CArgs& a, const GPhase& P, int batch, uint4 (&buf)[kNLD], const Thr& T) {
   constexpr int RPU = rpu_of<KIND>();
   constexpr int UB = kNLD / (RPU * VPL);
   static_assert(UB >= 1, "a batch must hold at least one unit");
@@ -565,7 +580,7 @@ struct Input {
 // Step 1: request the norm gains (they do not depend on other workgroups)
 // and the input words.
 template <int WFMT, int KIND, int VPL>
-AIO_DEV void input_issue(const MegaArgs& a, const GPhase& P, int layer, Input<WFMT, KIND, VPL>& I,
+AIO_DEV void input_issue(CArgs& a, const GPhase& P, int layer, Input<WFMT, KIND, VPL>& I,
                          const Thr& T) {
   using In = Input<WFMT, KIND, VPL>;
   constexpr int E = In::E, NQ = In::NQ, NG = In::NG;
@@ -606,7 +621,7 @@ AIO_DEV void input_issue(const MegaArgs& a, const GPhase& P, int layer, Input<WF
 // products (it is the same for every row); this wave's share of sum(x^2)
 // goes to ss8[wave].
 template <int WFMT, int KIND, int VPL>
-AIO_DEV void input_finish(const MegaArgs& a, const GPhase& P, int layer, int token, unsigned ver,
+AIO_DEV void input_finish(CArgs& a, const GPhase& P, int layer, int token, unsigned ver,
                           Input<WFMT, KIND, VPL>& I, float (&h)[VPL][epv<WFMT>()], float* ss8,
                           const Thr& T) {
   using In = Input<WFMT, KIND, VPL>;
@@ -711,7 +726,7 @@ struct Smem {
 // a thread's first (more rows per workgroup than threads) read it: the
 // first row's exact value stays in the thread's register (k_step's xr).
 template <int KIND>
-AIO_DEV unsigned resid(const MegaArgs& a, int u) {
+AIO_DEV unsigned resid(CArgs& a, int u) {
   return ld_dev((KIND == K_O ? a.xb : a.xa) + u);
 }
 
@@ -730,7 +745,7 @@ struct QkvRow {
   int i, sec, rlo;
 };
 template <int HD>
-AIO_DEV QkvRow qkv_row(const MegaArgs& a, int u) {
+AIO_DEV QkvRow qkv_row(CArgs& a, int u) {
   constexpr int half = HD / 2;
   const int qrows = a.H * HD, krows = a.Hkv * HD;
   const int p = 2 * u, head = p / half, i = p % half;  // pairs p, p+1 -> dims i, i+1
@@ -741,7 +756,7 @@ AIO_DEV QkvRow qkv_row(const MegaArgs& a, int u) {
 }
 
 template <int WFMT, int KIND, int HD>
-AIO_DEV EpiPre epi_fetch(const MegaArgs& a, const GPhase& P, int pos, int u) {
+AIO_DEV EpiPre epi_fetch(CArgs& a, const GPhase& P, int pos, int u) {
   EpiPre e;
   e.cs = make_float4(0.f, 0.f, 0.f, 0.f);
   e.s[0] = e.s[1] = 0u;
@@ -769,7 +784,7 @@ AIO_DEV float fp16_hi(uint32_t w) { return fp16_to_f32((uint16_t)(w >> 16)); }
 // Epilogue of a matrix phase: sum the kW wave partials of each row, then the
 // phase-specific output, stored with version `vo`.
 template <int WFMT, int KIND, int HD>
-AIO_DEV void epilogue(const MegaArgs& a, const GPhase& P, int layer, int pos, const float* red,
+AIO_DEV void epilogue(CArgs& a, const GPhase& P, int layer, int pos, const float* red,
                       Smem& sm, float& xr, const EpiPre& pre, float inv, const Thr& T,
                       unsigned vo, unsigned ep0) {
   constexpr int RPU = rpu_of<KIND>();
@@ -849,7 +864,7 @@ AIO_DEV void epilogue(const MegaArgs& a, const GPhase& P, int layer, int pos, co
       float yy = y[0];
       if constexpr (WFMT == AIO_WFMT_INT8) yy *= fp16_lo(e.s[0]);
       if constexpr (KIND == K_LM) {
-        a.logits[u] = yy;
+        *((__attribute__((address_space(1))) float*)a.logits + u) = yy;
         if (am_better(yy, u, bv, bi)) { bv = yy; bi = u; }
       } else {
         // the thread's first row keeps its exact value in xr; only the
@@ -904,8 +919,9 @@ struct Bufs {
 // phase; each buffer is refilled with the phase's batch kNBUF further on as
 // soon as it is consumed.
 template <int WFMT, int HD, int KIND, int VPL>
-AIO_DEV void gemv_phase(const MegaArgs& a, int layer, int pos, int token, Bufs& W, float* lds,
+AIO_DEV void gemv_phase(int layer, int pos, int token, Bufs& W, float* lds,
                         Smem& sm, unsigned ep0, unsigned k, float& xr) {
+  CArgs& a = step_args();
   constexpr int RPU = rpu_of<KIND>();
   // LDS partials and norm sums alternate between two buffers by phase
   // parity: a wave may start this phase while another still reads the
@@ -985,7 +1001,8 @@ AIO_DEV void gemv_phase(const MegaArgs& a, int layer, int pos, int token, Bufs& 
 // Issue the first batch of a matrix phase into buffer 0 (the phase itself
 // issues the others once its input words are requested).
 template <int WFMT, int HD, int KIND, int VPL>
-AIO_DEV void prefetch(const MegaArgs& a, int layer, Bufs& W) {
+AIO_DEV void prefetch(int layer, Bufs& W) {
+  CArgs& a = step_args();
   const GPhase N = make_phase<WFMT, KIND>(a, layer);
   issue<WFMT, KIND, VPL, HD>(a, N, 0, W.b[0], thr());
 }
@@ -1128,13 +1145,13 @@ struct AUnit {
 };
 
 // n / S, for n S below 2^32 (s_inv is 2^32 / S rounded up, 0 for S = 1).
-AIO_DEV unsigned div_s(const MegaArgs& a, unsigned n) {
+AIO_DEV unsigned div_s(CArgs& a, unsigned n) {
   const unsigned q = __umulhi(n, a.s_inv);
   return a.s_inv ? q : n;
 }
 
 template <int HD>
-AIO_DEV AUnit attn_unit(const MegaArgs& a, int layer, int unit, int pos, const Thr& T) {
+AIO_DEV AUnit attn_unit(CArgs& a, int layer, int unit, int pos, const Thr& T) {
   constexpr int LPK = HD / 8, NGR = kT / LPK, GPW = AIO_WAVE / LPK;
   const int S = a.S;
   AUnit u;
@@ -1174,7 +1191,8 @@ AIO_DEV void load4(const AUnit& u, KV4& d, int t0) {
 // poll for q waits behind them, but the keys are needed before q is of any
 // use, so nothing is lost; requesting them earlier lets them arrive sooner.
 template <int HD>
-AIO_DEV void attn_prefetch(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y) {
+AIO_DEV void attn_prefetch(int layer, int pos, KV4& X, KV4& Y) {
+  CArgs& a = step_args();
   const int units = a.Hkv * a.S;
   const int unit = (int)blockIdx.x < units ? (int)blockIdx.x : units - 1;
   const AUnit u = attn_unit<HD>(a, layer, unit, pos, thr());
@@ -1187,7 +1205,7 @@ AIO_DEV void attn_prefetch(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y
 // log-sum-exp; the R partial folds then meet in LDS.  All loads of a thread
 // are issued before its first wait.
 template <int HD, int G, int MS>
-AIO_DEV void attn_merge(const MegaArgs& a, int g, float* lds, unsigned ver) {
+AIO_DEV void attn_merge(CArgs& a, int g, float* lds, unsigned ver) {
   constexpr int NOUT = G * HD, R = kT / NOUT;
   const Thr T = thr();
   const int tid = T.tid, c = tid % NOUT, r = tid / NOUT, gg = c / HD, dim = c % HD;
@@ -1265,8 +1283,9 @@ AIO_DEV void attn_merge(const MegaArgs& a, int g, float* lds, unsigned ver) {
 // flight while the other is consumed, with no copies between them.  Then
 // the workgroup merges the heads whose last split it ran.
 template <int HD, int G>
-AIO_DEV void attn_phase(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y, float* lds,
+AIO_DEV void attn_phase(int layer, int pos, KV4& X, KV4& Y, float* lds,
                         Smem& sm, unsigned ep0, unsigned k) {
+  CArgs& a = step_args();
   constexpr int LPK = HD / 8, NGR = kT / LPK;
   constexpr int NOUT = G * HD;            // outputs of a unit
   constexpr int R = kT / NOUT > 0 ? kT / NOUT : 1;  // threads per output
@@ -1414,7 +1433,8 @@ AIO_DEV void attn_phase(const MegaArgs& a, int layer, int pos, KV4& X, KV4& Y, f
 }
 
 template <int WFMT, int HD, int G, int VQ, int VD>
-__global__ __launch_bounds__(kT, 1) void k_step(MegaArgs a) {
+__global__ __launch_bounds__(kT, 1) void k_step(MegaArgs) {
+  CArgs& a = step_args();
   extern __shared__ float lds[];
   __shared__ Smem sm;
   const int pos = a.st->pos, token = a.st->token[0];
@@ -1422,7 +1442,7 @@ __global__ __launch_bounds__(kT, 1) void k_step(MegaArgs a) {
   const unsigned ep0 = ld_dev(a.sync + kSyncEpoch);
   Bufs W;
   KV4 X, Y;
-  prefetch<WFMT, HD, K_QKV, VQ>(a, 0, W);
+  prefetch<WFMT, HD, K_QKV, VQ>(0, W);
   // The residual stream of this thread's first row of the O and down
   // projections (both split the d rows the same way), kept exact in a
   // register for the whole step: handing it between workgroups costs its
@@ -1439,23 +1459,24 @@ __global__ __launch_bounds__(kT, 1) void k_step(MegaArgs a) {
       st_tag(a.xb + P.u0 + t, xr, ver_of(ep0, 0));
     }
   }
-  for (int l = 0; l < a.L; ++l) {
+  const int nl = a.L;
+  for (int l = 0; l < nl; ++l) {
     const unsigned k = 5u * (unsigned)l;
-    gemv_phase<WFMT, HD, K_QKV, VQ>(a, l, pos, token, W, lds, sm, ep0, k + 1, xr);
-    attn_prefetch<HD>(a, l, pos, X, Y);
-    attn_phase<HD, G>(a, l, pos, X, Y, lds + 2 * a.red_words, sm, ep0, k + 2);
-    prefetch<WFMT, HD, K_O, VQ>(a, l, W);
-    gemv_phase<WFMT, HD, K_O, VQ>(a, l, pos, token, W, lds, sm, ep0, k + 3, xr);
-    prefetch<WFMT, HD, K_GU, VQ>(a, l, W);
-    gemv_phase<WFMT, HD, K_GU, VQ>(a, l, pos, token, W, lds, sm, ep0, k + 4, xr);
-    prefetch<WFMT, HD, K_DOWN, VD>(a, l, W);
-    gemv_phase<WFMT, HD, K_DOWN, VD>(a, l, pos, token, W, lds, sm, ep0, k + 5, xr);
-    if (l + 1 < a.L)
-      prefetch<WFMT, HD, K_QKV, VQ>(a, l + 1, W);
+    gemv_phase<WFMT, HD, K_QKV, VQ>(l, pos, token, W, lds, sm, ep0, k + 1, xr);
+    attn_prefetch<HD>(l, pos, X, Y);
+    attn_phase<HD, G>(l, pos, X, Y, lds + 2 * a.red_words, sm, ep0, k + 2);
+    prefetch<WFMT, HD, K_O, VQ>(l, W);
+    gemv_phase<WFMT, HD, K_O, VQ>(l, pos, token, W, lds, sm, ep0, k + 3, xr);
+    prefetch<WFMT, HD, K_GU, VQ>(l, W);
+    gemv_phase<WFMT, HD, K_GU, VQ>(l, pos, token, W, lds, sm, ep0, k + 4, xr);
+    prefetch<WFMT, HD, K_DOWN, VD>(l, W);
+    gemv_phase<WFMT, HD, K_DOWN, VD>(l, pos, token, W, lds, sm, ep0, k + 5, xr);
+    if (l + 1 < nl)
+      prefetch<WFMT, HD, K_QKV, VQ>(l + 1, W);
     else
-      prefetch<WFMT, HD, K_LM, VQ>(a, l + 1, W);
+      prefetch<WFMT, HD, K_LM, VQ>(l + 1, W);
   }
-  gemv_phase<WFMT, HD, K_LM, VQ>(a, a.L, pos, token, W, lds, sm, ep0, 5u * (unsigned)a.L + 1, xr);
+  gemv_phase<WFMT, HD, K_LM, VQ>(nl, pos, token, W, lds, sm, ep0, 5u * (unsigned)nl + 1, xr);
 }
 
 // The grid is one workgroup per CU and a CU holds at most one (registers
