@@ -1,8 +1,30 @@
-// Lane exchanges of the verify and prefill kernels (the step kernel does not
-// use them).
+// Lane exchanges and division helpers of the verify and prefill kernels (the
+// step kernel does not use them).
 #pragma once
 
 #include "common.h"
+
+// Division by a number the host knows: n / d as the high half of a product, for
+// the n below the limit given to make_udiv (inv 0: divide).  A division by a
+// kernel argument is some 30 instructions in a row (64-bit: over 100), on the
+// path to a kernel's first loads.  Without them: verify of the 1B, 3 rows at
+// 1531, 1142 -> 1127 us (7B, 9 rows at 2048, 3443 -> 3417), prefill of 23 rows of
+// the 1B 2011 -> 1988, 2048 rows 14706 -> 14643.
+struct UDiv {
+  unsigned inv, d;
+};
+inline UDiv make_udiv(unsigned d, unsigned limit) {
+  // 2^32 / d rounded up is exact while n d <= 2^32
+  const bool ok = d > 1 && (uint64_t)limit * d <= (1ull << 32);
+  return UDiv{ok ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u, d};
+}
+AIO_DEV int udiv(int n, const UDiv& v) {
+  if (v.inv) return (int)__umulhi((unsigned)n, v.inv);
+  return v.d == 1 ? n : (int)((unsigned)n / v.d);
+}
+
+// log2 of a head dimension (64 or 128).
+AIO_DEV int hd_shift(int hd) { return hd == 128 ? 7 : 6; }
 
 // Maximum over aligned groups of 8 lanes, as group_sum_dpp sums them.
 AIO_DEV float group_max8_dpp(float v) {

@@ -187,6 +187,7 @@ struct PTile {
   static constexpr int BM = 16 * kMB * WN;                  // weight rows
   static constexpr int BN = 16 * PB * WR;                   // prompt rows
   static constexpr int SK = KG * kKT;                       // k per stage
+  static constexpr int kBand = 512 / BN;                    // rows of tiles in a band (ptile_id)
   static constexpr int UPT = BM / kUnit;                    // units per tile
   static constexpr int BCols = kNT * BN;                    // activation columns
   static constexpr int BLd = BN * (SK / 4) / GT;            // 16-byte activation loads per thread
@@ -236,6 +237,9 @@ struct PGemmArgs {
   float* act_next;
   int lda_next;
   const uint16_t* g_next;
+  // divisions of ptile_id: by the tiles of a whole band, and by the rows of
+  // tiles of the last, shorter one
+  UDiv by_band, by_tail;
 };
 
 // Where block `blk` (0..3) of unit `bx` reads its 32 rows: matrix index
@@ -400,7 +404,7 @@ struct PTileId {
   int bx, by, kz;
 };
 template <class Tl>
-AIO_DEV PTileId ptile_id() {
+AIO_DEV PTileId ptile_id(const PGemmArgs& a) {
   PTileId t;
   if (gridDim.z > 1) {
     t.bx = (int)blockIdx.x;
@@ -413,12 +417,16 @@ AIO_DEV PTileId ptile_id() {
   // XCD lin % 8 holds g / 8 workgroups, the first g % 8 XCDs one more
   const int xcd = lin & 7, rem = xcd * (g / 8) + min(xcd, g & 7) + (lin >> 3);
   t.kz = 0;
-  constexpr int kBand = 512 / Tl::BN;
-  const int by0 = rem / (kBand * nx) * kBand;
-  const int nb = min(kBand, ny - by0);
+  constexpr int kBand = Tl::kBand;
+  const int by0 = udiv(rem, a.by_band) * kBand;
   const int in = rem - by0 * nx;
-  t.bx = in / nb;
-  t.by = by0 + in % nb;
+  if (ny - by0 >= kBand) {
+    t.bx = in / kBand;
+    t.by = by0 + in % kBand;
+  } else {
+    t.bx = udiv(in, a.by_tail);
+    t.by = by0 + in - t.bx * (ny - by0);
+  }
   return t;
 }
 
@@ -546,7 +554,7 @@ AIO_DEV void pgemm_epi(const PGemmArgs& a, const BlockSrc& slo, const BlockSrc& 
       for (int p = 0; p < PB; ++p)
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          const int ii = (slo.vrow0 + 16 * q + 4 * g) % a.hd;
+          const int ii = (slo.vrow0 + 16 * q + 4 * g) & (a.hd - 1);
           const float4* t = (const float4*)(a.rope + (size_t)(a.pos0 + min(rw0 + 16 * p + c16,
                                                                            a.R - 1)) * half + ii);
           cs[p][q][0] = t[0];
@@ -561,7 +569,7 @@ AIO_DEV void pgemm_epi(const PGemmArgs& a, const BlockSrc& slo, const BlockSrc& 
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const int row = slo.row0 + 16 * q + 4 * g;            // first of 4 rows in its matrix
-        const int ii = (slo.vrow0 + 16 * q + 4 * g) % a.hd;  // its index in the head (< hd / 2)
+        const int ii = (slo.vrow0 + 16 * q + 4 * g) & (a.hd - 1);  // its index in the head (< hd / 2)
         float lo[4], hi[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -589,7 +597,7 @@ AIO_DEV void pgemm_epi(const PGemmArgs& a, const BlockSrc& slo, const BlockSrc& 
           *(float4*)(qp + half) = make_float4(hi[0], hi[1], hi[2], hi[3]);
         } else {
           uint16_t* c = (mat == 1 ? a.kc : a.vc) +
-                        ((size_t)(row / a.hd) * a.max_ctx + a.pos0 + r) * a.hd + ii;
+                        ((size_t)(row >> hd_shift(a.hd)) * a.max_ctx + a.pos0 + r) * a.hd + ii;
           *(uint2*)c = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
           *(uint2*)(c + half) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
         }
@@ -620,7 +628,7 @@ __global__ __launch_bounds__(Tl::GT, 2) void k_pgemm(PGemmArgs a) {
   const int kg = wid / (Tl::kWN * Tl::kWR);
   const int wn = wid % Tl::kWN, wr = wid / Tl::kWN % Tl::kWR;
   const int c16 = lane & 15, g = lane >> 4;  // row of a fragment, lane group
-  const PTileId tid3 = ptile_id<Tl>();
+  const PTileId tid3 = ptile_id<Tl>(a);
   const int bx = tid3.bx, r0 = tid3.by * Tl::BN;
   constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
 
@@ -670,7 +678,8 @@ __global__ __launch_bounds__(Tl::GT, 2) void k_pgemm(PGemmArgs a) {
   // used.
   constexpr int NS = Tl::kNS;
   const int nst = a.K / Tl::SK, kz = tid3.kz;
-  const int sA = kz * nst / a.ks, sB = (kz + 1) * nst / a.ks, sL = sB - 1;
+  const int ksh = __builtin_ctz(a.ks);  // a power of two
+  const int sA = (kz * nst) >> ksh, sB = ((kz + 1) * nst) >> ksh, sL = sB - 1;
   uint4 ra[NS][A_LD], rb[NS][kBLd];
 #pragma unroll
   for (int i = 0; i < NS; ++i) gload_stage<WFMT, Tl::SK>(aptr, bptr, min(sA + i, sL), ra[i], rb[i]);
@@ -876,6 +885,7 @@ struct PAttnArgs {
   int lda;
   int R, pos0, H, Hkv, max_ctx;
   float scale_log2;     // log2(e) / sqrt(hd)
+  UDiv by_g, by_hpx;    // divisions by H / Hkv and by H / 8
 };
 
 constexpr int kAW = 4;  // waves per workgroup: they split the key blocks
@@ -925,11 +935,11 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
   if (gridDim.y % 8 == 0) {
     const int lin = (int)(blockIdx.x + gridDim.x * blockIdx.y);
     const int hpx = (int)gridDim.y / 8, j = lin / 8;
-    h = (lin % 8) * hpx + j % hpx;
-    qt = j / hpx;
+    qt = udiv(j, a.by_hpx);
+    h = (lin % 8) * hpx + j - qt * hpx;
   }
   const int q0 = ((int)gridDim.x - 1 - qt) * 32;
-  const int G = a.H / a.Hkv, kvh = h / G;
+  const int kvh = udiv(h, a.by_g);
   const int rows = min(32, a.R - q0);
   const int n_keys = a.pos0 + q0 + rows;  // keys the block's last row sees
   const int nkb = (n_keys + 31) / 32;
@@ -1241,7 +1251,11 @@ hipError_t launch_pgemm_t(const aio_model& m, const PGemmArgs& g, int units) {
   const void* fn = (const void*)k_pgemm<WFMT, EPI, Tl>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, Tl::Lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_pgemm<WFMT, EPI, Tl>), grid, dim3(Tl::GT), Tl::Lds, m.stream, g);
+  PGemmArgs a = g;
+  const unsigned tiles = grid.x * grid.y, tail = grid.y % Tl::kBand;
+  a.by_band = make_udiv(Tl::kBand * grid.x, tiles);
+  a.by_tail = make_udiv(tail ? tail : 1, tiles);
+  hipLaunchKernelGGL((k_pgemm<WFMT, EPI, Tl>), grid, dim3(Tl::GT), Tl::Lds, m.stream, a);
   return hipGetLastError();
 }
 
@@ -1347,6 +1361,8 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     t.kc = g.kc; t.vc = g.vc;
     t.act = b.actA; t.lda = b.lda_a;
     t.R = R; t.pos0 = pos0; t.H = H; t.Hkv = Hkv; t.max_ctx = c.max_ctx;
+    t.by_g = make_udiv((unsigned)(H / Hkv), (unsigned)H);
+    t.by_hpx = make_udiv((unsigned)std::max(H / 8, 1), (unsigned)H * (unsigned)((R + 31) / 32));
     t.scale_log2 = (float)(1.4426950408889634 / sqrt((double)hd));
     e = hd == 128 ? launch_pattn_t<128>(m, t) : launch_pattn_t<64>(m, t);
     if (e != hipSuccess) return e;

@@ -164,6 +164,7 @@ struct VGemmArgs {
   float* ss_out;
   int pairs, np;            // QKV, SWIGLU: row pairs of the product and per workgroup
   int pos;                  // QKV: position of the first row
+  UDiv by_np, by_nst;       // divisions by np and by the K stages (QKV, SWIGLU)
 };
 
 // The k of the two MFMA fragments a lane holds in a block of 32 k (lane
@@ -303,7 +304,7 @@ AIO_DEV PairIn vpair_in(const VGemmArgs& a, int p, int r) {
   PairIn in{make_float2(1.f, 0.f), 1.f, 1.f};
   if constexpr (EPI == EPI_QKV) {
     const int qrows = a.H * a.hd, krows = a.Hkv * a.hd, half = a.hd / 2;
-    const int head = p / half, ii = p - head * half, n = head * a.hd + ii;
+    const int head = p >> (hd_shift(a.hd) - 1), ii = p - head * half, n = head * a.hd + ii;
     if (n < qrows + krows) in.cs = a.rope[(size_t)(a.pos + r) * half + ii];
     if constexpr (WFMT == AIO_WFMT_INT8) {
       // both rows of the pair lie in the same (q, k or v) section
@@ -332,7 +333,7 @@ AIO_DEV void vpair_epi(const VGemmArgs& a, const PairIn& in, int p, int r, float
   }
   if constexpr (EPI == EPI_QKV) {
     const int qrows = a.H * a.hd, krows = a.Hkv * a.hd, half = a.hd / 2;
-    const int head = p / half, ii = p - head * half, n = head * a.hd + ii;
+    const int head = p >> (hd_shift(a.hd) - 1), ii = p - head * half, n = head * a.hd + ii;
     float lo = y0, hi = y1;
     if (n < qrows + krows) {
       lo = y0 * in.cs.x - y1 * in.cs.y;
@@ -343,7 +344,7 @@ AIO_DEV void vpair_epi(const VGemmArgs& a, const PairIn& in, int p, int r, float
       a.out[(size_t)r * a.ldo + n + half] = hi;
     } else {
       const bool is_k = n < qrows + krows;
-      const int g = (n - (is_k ? qrows : qrows + krows)) / a.hd;
+      const int g = (n - (is_k ? qrows : qrows + krows)) >> hd_shift(a.hd);
       uint16_t* c = (is_k ? a.kc : a.vc) + ((size_t)g * a.max_ctx + a.pos + r) * a.hd;
       c[ii] = f32_to_bf16(lo);
       c[ii + half] = f32_to_bf16(hi);
@@ -667,7 +668,7 @@ __global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
     const char* w;
     int n;
     if constexpr (EPI == EPI_QKV) {
-      const int half = a.hd / 2, head = p / half;
+      const int half = a.hd / 2, head = p >> (hd_shift(a.hd) - 1);
       const int qrows = a.H * a.hd, krows = a.Hkv * a.hd;
       n = head * a.hd + p - head * half + (hi ? half : 0);
       w = (const char*)a.w0;
@@ -683,7 +684,7 @@ __global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
   const uint16_t* actp = a.act + (size_t)(col_live ? rl : 0) * a.lda;
   const int nkb = a.K / 32, nst = (nkb + St::BPS - 1) / St::BPS;
   // workgroup b starts at stage b mod nst and wraps (see k_vgemm)
-  const int rot = (int)(blockIdx.x % (unsigned)nst);
+  const int rot = (int)blockIdx.x - udiv(blockIdx.x, a.by_nst) * nst;
   auto kb0 = [&](int st) {  // first 32-k block of stage st (st < 2 nst)
     const int q = st + rot;
     return (q >= nst ? q - nst : q) * St::BPS;
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
 #pragma unroll
   for (int it = 0; it < Vp::NI; ++it) {
     if (it * kGBlock >= 2 * np * M) break;
-    const int e = min((tid + it * kGBlock) >> 1, np * M - 1), r = e / np;
+    const int e = min((tid + it * kGBlock) >> 1, np * M - 1), r = np == a.np ? udiv(e, a.by_np) : e / np;
     in[it] = vpair_in<WFMT, EPI>(a, p0 + e - r * np, r);
   }
   __syncthreads();
@@ -774,7 +775,7 @@ __global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
   for (int it = 0; it < Vp::NI; ++it) {
     const int e = (tid + it * kGBlock) >> 1;
     if (e >= np * M) break;  // (both lanes of a pair)
-    const int r = e / np, i = e - r * np;
+    const int r = np == a.np ? udiv(e, a.by_np) : e / np, i = e - r * np;
     const float y = vred_sum<T>(red, h * NB + i / 32, i % 32, r, M) * inv_s[r];
     const float o = __shfl_xor(y, 1, AIO_WAVE);
     if (h == 0) vpair_epi<WFMT, EPI>(a, in[it], p0 + i, r, y, o);
@@ -791,6 +792,8 @@ struct VAttnArgs {
   float* part_ml;       // [M][H][S][2]
   int pos;              // position of the first row
   int H, Hkv, max_ctx, S, M;
+  int blocks, more;     // key blocks per split, and how many splits take one more
+  UDiv by_g;            // query heads per kv head
   float scale_log2;
   // k_vattn_mma: the last split of head h to finish merges the head's
   // splits into act (split o [32][lda]); cnt [H] counts finished splits
@@ -957,11 +960,10 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
   const int col = lane & 15, g = lane >> 4;  // query column, lane group
   const int s = blockIdx.x, h = blockIdx.y, M = a.M;
-  const int kvh = h / (a.H / a.Hkv);
+  const int kvh = udiv(h, a.by_g);
   const int pos = a.pos;
   const int n_keys = pos + M;  // the last row sees keys [0, pos + M - 1]
-  const int nkb = (n_keys + 31) / 32;
-  const int kbA = (int)((long long)s * nkb / a.S), kbB = (int)((long long)(s + 1) * nkb / a.S);
+  const int kbA = s * a.blocks + min(s, a.more), kbB = kbA + a.blocks + (s < a.more);
 
   const uint16_t* kbase = a.kc + (size_t)kvh * a.max_ctx * HD;
   const uint16_t* vbase = a.vc + (size_t)kvh * a.max_ctx * HD;
@@ -1253,6 +1255,10 @@ hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   a.pairs = pairs;
   const int rounds = (pairs + 64 * m.num_cus - 1) / (64 * m.num_cus);
   a.np = (pairs + rounds * m.num_cus - 1) / (rounds * m.num_cus);
+  constexpr int kStageBlocks = VStage<AIO_WFMT_BF16>::BPS;
+  static_assert(kStageBlocks == VStage<AIO_WFMT_INT8>::BPS, "one stage length");
+  a.by_nst = make_udiv((unsigned)((a.K / 32 + kStageBlocks - 1) / kStageBlocks), (unsigned)pairs);
+  a.by_np = make_udiv((unsigned)a.np, (unsigned)(a.np * kMaxRows));
   constexpr int I8 = AIO_WFMT_INT8, BF = AIO_WFMT_BF16;
   if (m.cfg.wfmt == AIO_WFMT_INT8) {
     if (a.np <= 16) return launch_vpair_t<I8, EPI, 1, 1, 4>(m, a);
@@ -1340,6 +1346,9 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
     const int nkb = (pos + M + 31) / 32;
     const int s_cap = std::max(1, std::min(m.lay.vsplits, m.num_cus / H));
     t.S = std::max(1, std::min(s_cap, (nkb + kVattnBlocksPerSplit - 1) / kVattnBlocksPerSplit));
+    t.blocks = nkb / t.S;
+    t.more = nkb % t.S;
+    t.by_g = make_udiv((unsigned)(H / Hkv), (unsigned)H);
     t.cnt = m.at<int>(m.lay.vacnt);
     t.act = actB;
     t.lda = ka;
