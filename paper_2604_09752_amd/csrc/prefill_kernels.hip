@@ -28,11 +28,10 @@
 #include "aio_internal.h"
 #include "common.h"
 #include "lanes.h"
+#include "skinny.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
@@ -1162,6 +1161,405 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
                       o[hb][4 * g + 3] * inv);
 }
 
+// ------------------------------------------- products of a few prompt rows
+
+// Products of at most kSkRows prompt rows.  The tiles of k_pgemm leave such a
+// product to 128 or 176 workgroups, and a CU streams no more than about 30
+// bytes per ns, so its weights should come in equal shares through all of
+// them: a workgroup owns np row pairs (k_spair) or 64 rows and a K slice
+// (k_sresid) and passes its weights through LDS in stages of 256 k.  Wave w
+// multiplies 32-k block w of every stage by all prompt rows: lane rl of a half
+// wave reads prompt row rl's 16 activations of the block from memory and
+// splits them, and the three terms are three products into 32x32 tiles, hi
+// (first terms) and lo.  The waves' tiles meet in LDS.  What bounds it is the
+// bytes through each CU, some 45 per ns with the activations (every workgroup
+// reads those of its K slice).  23 rows of the 1B, in us, Short tiles of k_pgemm
+// before and now: QKV 19.5 -> 12.6, O 15.7 -> 10.4, gate/up 20.0 -> 18.0, down
+// 21.5 -> 13.7.
+constexpr int kSkRows = 32;
+
+struct SkArgs {
+  PGemmArgs g;
+  int pairs, np;        // k_spair: row pairs of the product and per workgroup
+  UDiv by_np, by_nst;   // k_spair: divisions by np and by the K stages of a slice
+};
+constexpr int kSkPairKs = 4;  // most K slices of a k_spair product
+
+// The three bf16 terms of 8 activations.
+AIO_DEV void split_frag(const uint4& a, const uint4& b, bf16x8 (&f)[kNT]) {
+  const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  uint32_t t[8][kNT];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) split3t(x[i], t[i]);
+#pragma unroll
+  for (int k = 0; k < kNT; ++k) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = (t[2 * i][k] >> 16) | t[2 * i + 1][k];
+    f[k] = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+  }
+}
+
+// The streaming loop of both kernels: rows lrow[] of K weights, k blocks [kbA,
+// kbB), stages rotated by rot, NS of them in flight in registers.
+template <int WFMT, int NLD, int NS>
+struct SkStream {
+  using St = VStage<WFMT>;
+  static_assert(St::BPW == 1, "one block per wave and stage");
+  const char* lrow[NLD];
+  int lds_off[NLD];
+  int lchunk, wid, rl, kh, kbA, kbB, nst, rot, kend;
+  const float* actp;  // prompt row rl (the last one past the rows: not stored)
+
+  AIO_DEV int kb0(int st) const {  // first block of stage st (st < 2 nst)
+    const int q = st + rot;
+    return kbA + (q >= nst ? q - nst : q) * St::BPS;
+  }
+  AIO_DEV void load(uint4 (&R)[NLD], uint4 (&A)[4], int st) const {
+    constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
+    const int b0 = kb0(min(st, nst - 1));
+    const int off = min(b0 * 32 * wbytes + lchunk * 16, kend);
+#pragma unroll
+    for (int j = 0; j < NLD; ++j) R[j] = ldg_nt(lrow[j] + off);
+    const int block = min(b0 + wid, kbB - 1) * 32;
+    const float* lo = actp + vk_lo<WFMT>(block, kh);
+    const float* hi = actp + vk_hi<WFMT>(block, kh);
+    A[0] = ldg(lo);
+    A[1] = ldg(lo + 4);
+    A[2] = ldg(hi);
+    A[3] = ldg(hi + 4);
+  }
+  AIO_DEV void stage(char* smem, const uint4 (&R)[NLD]) const {
+    __syncthreads();  // every wave is done with the previous stage
+#pragma unroll
+    for (int j = 0; j < NLD; ++j) {
+      const u32x4 w = {R[j].x, R[j].y, R[j].z, R[j].w};
+      *(u32x4*)(smem + lds_off[j]) = w;
+    }
+    __syncthreads();
+  }
+  // (a block past the end multiplies zeros)
+  AIO_DEV void product(const char* smem, const uint4 (&A)[4], int st, f32x16 (&hi)[2],
+                       f32x16 (&lo)[2]) const {
+    const bool live = kb0(st) + wid < kbB;
+    uint4 z[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      z[i] = make_uint4(live ? A[i].x : 0u, live ? A[i].y : 0u, live ? A[i].z : 0u,
+                        live ? A[i].w : 0u);
+    bf16x8 wa[2], wb[2], ba[kNT], bb[kNT];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      frag_lds<WFMT>(smem + (t * 32 + rl) * St::RS, wid, kh, wa[t], wb[t]);
+    split_frag(z[0], z[1], ba);
+    split_frag(z[2], z[3], bb);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      hi[t] = mfma(wa[t], ba[0], hi[t]);
+      lo[t] = mfma(wa[t], ba[1], lo[t]);
+      hi[t] = mfma(wb[t], bb[0], hi[t]);
+      lo[t] = mfma(wa[t], ba[2], lo[t]);
+      lo[t] = mfma(wb[t], bb[1], lo[t]);
+      lo[t] = mfma(wb[t], bb[2], lo[t]);
+    }
+  }
+  // All stages; then the wave's tiles to LDS (the caller's barrier follows).
+  // `between` runs once the first stages are requested.
+  template <class F>
+  AIO_DEV void run(char* smem, int rows, F&& between) const {
+    f32x16 hi[2], lo[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) hi[t][i] = lo[t][i] = 0.f;
+    uint4 R[NS][NLD], A[NS][4];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) load(R[i], A[i], i);
+    between();
+    // a stage's register set is refilled with the stage NS ahead: the weights
+    // and activations of NS stages stay in flight through its product
+    int st = 0;
+    for (; st + NS < nst; st += NS) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        stage(smem, R[i]);
+        uint4 a[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = make_uint4(A[i][q].x, A[i][q].y, A[i][q].z, A[i][q].w);
+        __builtin_amdgcn_sched_barrier(0);
+        load(R[i], A[i], st + i + NS);
+        __builtin_amdgcn_sched_barrier(0);
+        product(smem, a, st + i, hi, lo);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (st + i >= nst) break;
+      stage(smem, R[i]);
+      product(smem, A[i], st + i, hi, lo);
+    }
+    __syncthreads();  // the stage buffer becomes the partial-tile buffer
+    float* red = (float*)smem;
+    if (rl < rows) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          red[(wid * 2 + t) * kVRedTile<2> + (8 * (v / 4) + 4 * kh + (v % 4)) * 33 + rl] =
+              hi[t][v] + lo[t][v];
+    }
+  }
+};
+
+// Prompt row r of row i of tile t: the waves' sums.
+AIO_DEV float sk_sum(const float* red, int t, int i, int r) {
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < kGWaves; ++w) s += red[(w * 2 + t) * kVRedTile<2> + i * 33 + r];
+  return s;
+}
+
+// QKV and gate/up.  Pairs and their layout as in the tile products' epilogue:
+// rows ii and ii + hd / 2 of a head section, or row p of gate and of up.
+template <int WFMT, int EPI, int NLD, int NS>
+__global__ __launch_bounds__(kGBlock, 1) void k_spair(SkArgs sa) {
+  static_assert(EPI == PE_QKV || EPI == PE_SWIGLU, "products of row pairs");
+  using St = VStage<WFMT>;
+  constexpr int RPL = kGBlock / St::CPR;  // rows a load slot covers
+  constexpr int NI = (NLD * RPL * kSkRows + kGBlock - 1) / kGBlock;
+  const PGemmArgs& a = sa.g;
+  extern __shared__ __align__(16) char smem[];
+  __shared__ float inv_s[kSkRows];
+  __shared__ int last_s;
+  const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
+  constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
+  const int p0 = (int)blockIdx.x * sa.np, np = min(sa.np, sa.pairs - p0);
+  const int qrows = a.H * a.hd, krows = a.Hkv * a.hd, half = a.hd / 2;
+  SkStream<WFMT, NLD, NS> s;
+  s.lchunk = tid % St::CPR;
+#pragma unroll
+  for (int j = 0; j < NLD; ++j) {
+    const int sl = min(j * RPL + tid / St::CPR, 2 * np - 1);
+    const bool hi = sl >= np;
+    const int p = p0 + (hi ? sl - np : sl);
+    int n = p, mat = hi;
+    if constexpr (EPI == PE_QKV) {
+      const int head = p >> (hd_shift(a.hd) - 1);
+      n = head * a.hd + p - head * half + (hi ? half : 0);
+      mat = 0;
+      if (n >= qrows + krows) { mat = 2; n -= qrows + krows; }
+      else if (n >= qrows) { mat = 1; n -= qrows; }
+    }
+    s.lrow[j] = pick_mat(a, mat) + (size_t)n * a.K * wbytes;
+    s.lds_off[j] = ((hi ? 32 : 0) + p - p0) * St::RS + s.lchunk * 16;
+  }
+  s.wid = wid;
+  s.rl = lane & 31;
+  s.kh = lane >> 5;
+  const int kz = (int)blockIdx.y, ksh = __builtin_ctz(a.ks);
+  s.kbA = (kz * (a.K / 32)) >> ksh;
+  s.kbB = ((kz + 1) * (a.K / 32)) >> ksh;
+  s.nst = (s.kbB - s.kbA + St::BPS - 1) / St::BPS;
+  // (by_nst divides by the stages of the longest slice)
+  s.rot = min((int)blockIdx.x - udiv(blockIdx.x, sa.by_nst) * (int)sa.by_nst.d, s.nst - 1);
+  s.kend = s.kbB * 32 * wbytes - 16;
+  s.actp = a.act + (size_t)min(s.rl, a.R - 1) * a.lda;
+  // the norm's row factors: wave w sums rows w, w + 8, ...
+  float ssp[kSkRows / kGWaves][2];
+  s.run(smem, a.R, [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < kSkRows / kGWaves; ++h) {
+      const float* ss = a.ss_in + (size_t)min(wid + kGWaves * h, a.R - 1) * a.nss;
+      ssp[h][0] = lane < a.nss ? ss[lane] : 0.f;
+      ssp[h][1] = lane + 64 < a.nss ? ss[lane + 64] : 0.f;
+    }
+  });
+#pragma unroll
+  for (int h = 0; h < kSkRows / kGWaves; ++h) {
+    const int r = wid + kGWaves * h;
+    if (r >= a.R) break;
+    float p = ssp[h][0] + ssp[h][1];
+    for (int c = lane + 128; c < a.nss; c += 64) p += a.ss_in[(size_t)r * a.nss + c];
+    const float sum = wave_sum(p);
+    if (lane == 0) inv_s[r] = rsqrtf(sum / (float)a.K + a.eps);
+  }
+  // Two lanes per pair and prompt row, each summing one of the pair's rows;
+  // what the epilogue reads besides is requested before the barrier.
+  float2 cs[NI];
+  float sc[NI];
+  const int h = tid & 1;
+#pragma unroll
+  for (int it = 0; it < NI; ++it) {
+    cs[it] = make_float2(1.f, 0.f);
+    sc[it] = 1.f;
+    if (it * kGBlock >= 2 * np * a.R) break;
+    const int e = min((tid + it * kGBlock) >> 1, np * a.R - 1);
+    const int r = np == sa.np ? udiv(e, sa.by_np) : e / np, p = p0 + e - r * np;
+    if constexpr (EPI == PE_QKV) {
+      const int head = p >> (hd_shift(a.hd) - 1), ii = p - head * half, n = head * a.hd + ii;
+      if (n < qrows + krows) cs[it] = a.rope[(size_t)(a.pos0 + r) * half + ii];
+      if constexpr (WFMT == AIO_WFMT_INT8) {
+        const uint16_t* q = n >= qrows + krows ? a.s2 + (n - qrows - krows)
+                                               : (n >= qrows ? a.s1 + (n - qrows) : a.s0 + n);
+        sc[it] = fp16_to_f32(q[h ? half : 0]);
+      }
+    } else if constexpr (WFMT == AIO_WFMT_INT8) {
+      sc[it] = fp16_to_f32((h ? a.s1 : a.s0)[p]);
+    }
+  }
+  __syncthreads();
+  const float* red = (const float*)smem;
+  float y[NI];
+  float* part = a.fix + ((size_t)blockIdx.x * a.ks * 2 + h) * sa.np * a.R;
+  const size_t pstep = (size_t)2 * sa.np * a.R;
+#pragma unroll
+  for (int it = 0; it < NI; ++it) {
+    const int e = (tid + it * kGBlock) >> 1;
+    if (e >= np * a.R) break;  // (both lanes of a pair)
+    const int r = np == sa.np ? udiv(e, sa.by_np) : e / np, i = e - r * np;
+    y[it] = sk_sum(red, h, i, r);
+    if (a.ks > 1) st_agent(part + kz * pstep + e, y[it]);
+  }
+  if (a.ks > 1) {
+    // as in k_sresid: the last slice to arrive adds all of them in order
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) last_s = atomic_add_agent(a.tcnt + blockIdx.x, 1) == a.ks - 1;
+    __syncthreads();
+    if (!last_s) return;
+    if (tid == 0) atomic_store_agent(a.tcnt + blockIdx.x, 0);  // ready for the next product
+    float pv[NI][kSkPairKs];
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      if (it * kGBlock >= 2 * np * a.R) break;
+      const int e = min((tid + it * kGBlock) >> 1, np * a.R - 1);
+#pragma unroll
+      for (int k = 0; k < kSkPairKs; ++k) pv[it][k] = ld_agent(part + (k < a.ks ? k : 0) * pstep + e);
+    }
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      if (it * kGBlock >= 2 * np * a.R) break;
+      y[it] = 0.f;
+#pragma unroll
+      for (int k = 0; k < kSkPairKs; ++k)
+        if (k < a.ks) y[it] += pv[it][k];
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < NI; ++it) {
+    const int e = (tid + it * kGBlock) >> 1;
+    if (e >= np * a.R) break;
+    const int r = np == sa.np ? udiv(e, sa.by_np) : e / np, i = e - r * np, p = p0 + i;
+    const float yv = y[it] * inv_s[r] * sc[it];
+    const float o = dpp_mov<0xB1>(yv);  // lane ^ 1
+    if constexpr (EPI == PE_QKV) {
+      // each lane stores its own row of the rotated pair
+      const int head = p >> (hd_shift(a.hd) - 1), ii = p - head * half, n = head * a.hd + ii;
+      const float v = n < qrows + krows ? yv * cs[it].x + (h ? o : -o) * cs[it].y : yv;
+      const int off = h ? half : 0;
+      if (n < qrows) {
+        a.out[(size_t)r * a.ldo + n + off] = v;
+      } else {
+        const bool is_k = n < qrows + krows;
+        const int g = (n - (is_k ? qrows : qrows + krows)) >> hd_shift(a.hd);
+        ((is_k ? a.kc : a.vc) + ((size_t)g * a.max_ctx + a.pos0 + r) * a.hd)[ii + off] = f32_to_bf16(v);
+      }
+    } else if (h == 0) {
+      a.act_out[(size_t)r * a.lda_out + p] = yv / (1.f + expf(-yv)) * o;
+    }
+  }
+}
+
+// O and down: 64 rows of the matrix and one of a.ks K slices per workgroup.
+// With ks > 1 every slice writes its sums through to a.fix[slice][R][N], and
+// the last one to arrive (a.tcnt) adds them in slice order.
+template <int WFMT, int NS>
+__global__ __launch_bounds__(kGBlock, 1) void k_sresid(PGemmArgs a) {
+  using St = VStage<WFMT>;
+  constexpr int NLD = St::NLD, NI = 64 * kSkRows / kGBlock;
+  extern __shared__ __align__(16) char smem[];
+  __shared__ int last_s;
+  const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
+  constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
+  const int n0 = (int)blockIdx.x * 64, kz = (int)blockIdx.y, ksh = __builtin_ctz(a.ks);
+  SkStream<WFMT, NLD, NS> s;
+  s.lchunk = tid % St::CPR;
+#pragma unroll
+  for (int j = 0; j < NLD; ++j) {
+    const int r = (j * kGBlock + tid) / St::CPR;
+    s.lrow[j] = (const char*)a.w0 + (size_t)(n0 + r) * a.K * wbytes;
+    s.lds_off[j] = r * St::RS + s.lchunk * 16;
+  }
+  const int nkb = a.K / 32;
+  s.wid = wid;
+  s.rl = lane & 31;
+  s.kh = lane >> 5;
+  s.kbA = (kz * nkb) >> ksh;
+  s.kbB = ((kz + 1) * nkb) >> ksh;
+  s.nst = (s.kbB - s.kbA + St::BPS - 1) / St::BPS;
+  s.rot = (int)(blockIdx.x % (unsigned)s.nst);
+  s.kend = s.kbB * 32 * wbytes - 16;
+  s.actp = a.act + (size_t)min(s.rl, a.R - 1) * a.lda;
+  // thread -> prompt rows r and output column n of the epilogue
+  const int n = n0 + lane;
+  float xv[NI], gn = 1.f, sc = 1.f;
+  s.run(smem, a.R, [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int it = 0; it < NI; ++it)
+      xv[it] = a.out[(size_t)min(wid + kGWaves * it, a.R - 1) * a.ldo + n];
+    if (a.act_next) gn = bf16_to_f32(a.g_next[n]);
+    if constexpr (WFMT == AIO_WFMT_INT8) sc = fp16_to_f32(a.s0[n]);
+  });
+  __syncthreads();
+  const float* red = (const float*)smem;
+  float v[NI];
+#pragma unroll
+  for (int it = 0; it < NI; ++it) {
+    const int r = wid + kGWaves * it;
+    if (r >= a.R) break;
+    v[it] = sk_sum(red, lane / 32, lane % 32, r) * sc;
+    if (a.ks > 1) st_agent(a.fix + ((size_t)kz * a.R + r) * a.N + n, v[it]);
+  }
+  float pv[NI][kVerifyMaxKs];
+  if (a.ks > 1) {
+    // every wave's stores have completed (written through) before the slice
+    // is counted
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) last_s = atomic_add_agent(a.tcnt + blockIdx.x, 1) == a.ks - 1;
+    __syncthreads();
+    if (!last_s) return;
+    if (tid == 0) atomic_store_agent(a.tcnt + blockIdx.x, 0);  // ready for the next product
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      if (wid + kGWaves * it >= a.R) break;
+#pragma unroll
+      for (int k = 0; k < kVerifyMaxKs; ++k)
+        pv[it][k] = ld_agent(a.fix + ((size_t)(k < a.ks ? k : 0) * a.R + wid + kGWaves * it) * a.N + n);
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < NI; ++it) {
+    const int r = wid + kGWaves * it;
+    if (r >= a.R) break;  // (whole waves)
+    float x = xv[it];
+    if (a.ks > 1) {
+#pragma unroll
+      for (int k = 0; k < kVerifyMaxKs; ++k)
+        if (k < a.ks) x += pv[it][k];
+    } else {
+      x += v[it];
+    }
+    a.out[(size_t)r * a.ldo + n] = x;
+    if (a.act_next) {
+      a.act_next[(size_t)r * a.lda_next + n] = x * gn;
+      const float sq = wave_sum(x * x);
+      if (lane == 0) a.ss_out[(size_t)r * a.nss + blockIdx.x] = sq;
+    }
+  }
+}
+
 // ----------------------------------------------------------------- launchers
 
 hipError_t launch_pnorm(const aio_model& m, const PfBuffers& b, int R, const uint16_t* embed,
@@ -1259,6 +1657,83 @@ hipError_t launch_pgemm_t(const aio_model& m, const PGemmArgs& g, int units) {
   return hipGetLastError();
 }
 
+// Products of a few prompt rows (SkArgs).  Pairs: one round of workgroups of at
+// most 32 pairs (one 32-row tile of each of their rows).  Residual: K split as
+// far as there are CUs and every wave keeps two blocks, and the slices' sums fit
+// the fix-up room.
+template <int WFMT, int EPI, int NLD, int NS>
+hipError_t launch_spair_t(const aio_model& m, const SkArgs& a) {
+  constexpr int lds = vgemm_lds<WFMT, 2>(64);
+  const void* fn = (const void*)k_spair<WFMT, EPI, NLD, NS>;
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_spair<WFMT, EPI, NLD, NS>), dim3((a.pairs + a.np - 1) / a.np, a.g.ks),
+                     dim3(kGBlock), lds, m.stream, a);
+  return hipGetLastError();
+}
+template <int WFMT, int NS>
+hipError_t launch_sresid_t(const aio_model& m, const PGemmArgs& g) {
+  constexpr int lds = vgemm_lds<WFMT, 2>(64);
+  const void* fn = (const void*)k_sresid<WFMT, NS>;
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_sresid<WFMT, NS>), dim3(g.N / 64, g.ks), dim3(kGBlock), lds, m.stream, g);
+  return hipGetLastError();
+}
+
+// Pairs per workgroup and K slices of a product of `pairs` row pairs; false
+// where it is left to the tile products.  Every workgroup reads the activations
+// of its slice: more than 384 KB of them cost what the even shares gain (7B
+// QKV, K 4096: 23 rows, 368 KB, 31.6 us against the tiles' 32.6; 32 rows, 512 KB,
+// 34.6 / 32.6, int8 32.7 / 30.9), and pairs for half or a quarter of K are
+// preferred where 32 allow it (QKV of the 1B, K 2048, 23 rows: 8 pairs each 14.8
+// us, 32 of a quarter 12.6).  More than 32 pairs would need a second pair of
+// tiles, whose hi and lo do not fit the registers.
+bool sk_pairs(const aio_model& m, const PGemmArgs& g, int pairs, int* np, int* ks) {
+  for (*ks = kSkPairKs; *ks >= 1; *ks /= 2) {
+    *np = (pairs * *ks + m.num_cus - 1) / m.num_cus;
+    if (*np > 32) continue;
+    const size_t tiles = (size_t)(pairs + *np - 1) / *np;
+    if (*ks > 1 && (g.K / 32 / (*ks * kGWaves) < 2 || tiles > m.lay.pcnt_n ||
+                    tiles * *ks * 2 * *np * g.R * 4 > g.fix_bytes))
+      continue;
+    return g.R <= kSkRows && (size_t)4 * g.R * g.K / *ks <= 384 * 1024;
+  }
+  return false;
+}
+
+template <int WFMT, int EPI>
+hipError_t launch_sk(const aio_model& m, const PGemmArgs& g0, int np, int pairs, int ks) {
+  if constexpr (EPI == PE_RESID) {
+    PGemmArgs g = g0;
+    g.ks = 1;
+    const int nkb = g.K / 32, tiles = g.N / 64;
+    while (tiles * g.ks < m.num_cus && 2 * g.ks <= kVerifyMaxKs && nkb / (2 * g.ks * kGWaves) >= 2 &&
+           (size_t)tiles <= m.lay.pcnt_n && (size_t)2 * g.ks * g.R * g.N * 4 <= g.fix_bytes)
+      g.ks *= 2;
+    return launch_sresid_t<WFMT, 2>(m, g);
+  } else {
+    SkArgs a{};
+    a.g = g0;
+    a.pairs = pairs;
+    a.np = np;
+    a.g.ks = ks;
+    a.by_np = make_udiv((unsigned)np, (unsigned)(np * kSkRows));
+    constexpr int bps = VStage<WFMT>::BPS;
+    const int slice = (g0.K / 32 + ks - 1) / ks;  // blocks of the longest slice
+    a.by_nst = make_udiv((unsigned)((slice + bps - 1) / bps), (unsigned)pairs);
+    if constexpr (WFMT == AIO_WFMT_BF16) {
+      if (np <= 8) return launch_spair_t<WFMT, EPI, 1, 3>(m, a);
+      if (np <= 16) return launch_spair_t<WFMT, EPI, 2, 3>(m, a);
+      if (np <= 24) return launch_spair_t<WFMT, EPI, 3, 2>(m, a);
+      return launch_spair_t<WFMT, EPI, 4, 2>(m, a);
+    } else {
+      if (np <= 16) return launch_spair_t<WFMT, EPI, 1, 3>(m, a);
+      return launch_spair_t<WFMT, EPI, 2, 3>(m, a);
+    }
+  }
+}
+
 // Launch over `units` (of 128 weight rows) of the product.  The partial tiles
 // of a K split go to the scratch that is idle during this product (g.fix),
 // or to the workspace's region where that is larger.
@@ -1270,6 +1745,10 @@ hipError_t launch_pgemm_w(const aio_model& m, const PGemmArgs& g0, int units) {
     g.fix_bytes = m.lay.pfix_bytes;
   }
   g.tcnt = m.at<int>(m.lay.pcnt);
+  const int pairs = EPI == PE_QKV ? g.N / 2 : g.N;
+  int np = 0, sks = 1;
+  if (EPI == PE_RESID ? g.R <= kSkRows : sk_pairs(m, g, pairs, &np, &sks))
+    return launch_sk<WFMT, EPI>(m, g, np, pairs, sks);
   int shape = 0;
   pf_choose(m, units, g.R, g.K, g.fix_bytes, &shape, &g.ks);
   if (shape == 0) return launch_pgemm_t<WFMT, EPI, Big>(m, g, units);
