@@ -918,7 +918,7 @@ struct Bufs {
 // Matrix phase k.  On entry buffer 0 holds (in flight) batch 0 of this
 // phase; each buffer is refilled with the phase's batch kNBUF further on as
 // soon as it is consumed.
-template <int WFMT, int HD, int KIND, int VPL>
+template <int WFMT, int HD, int KIND, int VPL, bool LATE, bool ONE>
 AIO_DEV void gemv_phase(int layer, int pos, int token, Bufs& W, float* lds,
                         Smem& sm, unsigned ep0, unsigned k, float& xr) {
   CArgs& a = step_args();
@@ -940,29 +940,38 @@ AIO_DEV void gemv_phase(int layer, int pos, int token, Bufs& W, float* lds,
     pre = epi_fetch<WFMT, KIND, HD>(a, P, pos, P.u0 + t < P.nu ? P.u0 + t : P.nu - 1);
   }
   // batch 0 is in flight (prefetch); then the input words, then the other
-  // batches, so the wait for the input is queued behind one batch only
+  // batches (LATE: after the wait), so the wait for the input is queued behind
+  // one batch only
   // (the scheduling barriers keep the three groups of loads, and the first
   // check of the input, in this order)
   Input<WFMT, KIND, VPL> I;
   input_issue<WFMT, KIND, VPL>(a, P, layer, I, T);
   __builtin_amdgcn_sched_barrier(0);
+  auto issue_rest = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int j = 1; j < kNBUF; ++j) issue<WFMT, KIND, VPL, HD>(a, P, j, W.b[j], T);
-  __builtin_amdgcn_sched_barrier(0);
+    for (int j = 1; j < kNBUF; ++j) issue<WFMT, KIND, VPL, HD>(a, P, j, W.b[j], T);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (!LATE) issue_rest();
   float h[VPL][epv<WFMT>()];
   input_finish<WFMT, KIND, VPL>(a, P, layer, token, ver_of(ep0, k - 1), I, h, ss8, T);
+  // (a phase that may have one batch requests no second one then)
+  constexpr bool kMaybeOne = KIND == K_O || ONE;
+  if constexpr (LATE && !kMaybeOne) issue_rest();
   stamp(a.bar_leave, k - 1);
   stamp_detail(a, slot, 0);
   // Branch-free body: a batch past the end is computed fully masked and its
   // refill is a masked dummy (cache-hit) load, so the compiler sees the same
   // loads in flight behind each buffer on every path.
   // O has one batch where its rows are few (2048 inputs and rows, or int8
-  // 4096): then only that one is waited for and multiplied.  (The same for
-  // every phase, or a test per batch in the last round, cost the larger shapes
-  // 1 % and gained nothing.)
-  if (KIND == K_O && nb <= 1) {
+  // 4096): then only that one is waited for and multiplied.  The other phases
+  // have this path in small models only (ONE: the tiny decoder 64.3 -> 60.1 us
+  // per token); in the larger ones it cost 1 to 2 % and is never taken, as did a
+  // test per batch in the last round.
+  if (kMaybeOne && nb <= 1) {
     compute<WFMT, KIND, VPL>(P, 0, W.b[0], h, red, T);
   } else {
+    if constexpr (LATE && kMaybeOne) issue_rest();
     int b = 0;
     for (; b + kNBUF < nb; b += kNBUF) {
 #pragma unroll
@@ -1434,6 +1443,15 @@ AIO_DEV void attn_phase(int layer, int pos, KV4& X, KV4& Y, float* lds,
 
 template <int WFMT, int HD, int G, int VQ, int VD>
 __global__ __launch_bounds__(kT, 1) void k_step(MegaArgs) {
+  // A phase requests its later batches behind the first poll for its input, or
+  // (LATE) once the input is in: a poll that fails is repeated behind whatever
+  // was requested meanwhile.  With few bytes per phase the earlier input is
+  // worth more (8 tokens of the 1B at 2K 5715 -> 5556 us, one at 128 669 -> 632, 4 of
+  // the int8 7B at 2K 6299 -> 6143), with many the stream (7B bf16 9052 -> 9137):
+  // late for int8 and for down projections of at most 8192 bf16 inputs (VD up
+  // to 2).
+  constexpr bool LATE = WFMT == AIO_WFMT_INT8 || VD < 3;
+  constexpr bool ONE = VD == 1;  // at most 4096 down inputs
   CArgs& a = step_args();
   extern __shared__ float lds[];
   __shared__ Smem sm;
@@ -1462,21 +1480,21 @@ __global__ __launch_bounds__(kT, 1) void k_step(MegaArgs) {
   const int nl = a.L;
   for (int l = 0; l < nl; ++l) {
     const unsigned k = 5u * (unsigned)l;
-    gemv_phase<WFMT, HD, K_QKV, VQ>(l, pos, token, W, lds, sm, ep0, k + 1, xr);
+    gemv_phase<WFMT, HD, K_QKV, VQ, LATE, ONE>(l, pos, token, W, lds, sm, ep0, k + 1, xr);
     attn_prefetch<HD>(l, pos, X, Y);
     attn_phase<HD, G>(l, pos, X, Y, lds + 2 * a.red_words, sm, ep0, k + 2);
     prefetch<WFMT, HD, K_O, VQ>(l, W);
-    gemv_phase<WFMT, HD, K_O, VQ>(l, pos, token, W, lds, sm, ep0, k + 3, xr);
+    gemv_phase<WFMT, HD, K_O, VQ, LATE, ONE>(l, pos, token, W, lds, sm, ep0, k + 3, xr);
     prefetch<WFMT, HD, K_GU, VQ>(l, W);
-    gemv_phase<WFMT, HD, K_GU, VQ>(l, pos, token, W, lds, sm, ep0, k + 4, xr);
+    gemv_phase<WFMT, HD, K_GU, VQ, LATE, ONE>(l, pos, token, W, lds, sm, ep0, k + 4, xr);
     prefetch<WFMT, HD, K_DOWN, VD>(l, W);
-    gemv_phase<WFMT, HD, K_DOWN, VD>(l, pos, token, W, lds, sm, ep0, k + 5, xr);
+    gemv_phase<WFMT, HD, K_DOWN, VD, LATE, ONE>(l, pos, token, W, lds, sm, ep0, k + 5, xr);
     if (l + 1 < nl)
       prefetch<WFMT, HD, K_QKV, VQ>(l + 1, W);
     else
       prefetch<WFMT, HD, K_LM, VQ>(l + 1, W);
   }
-  gemv_phase<WFMT, HD, K_LM, VQ>(nl, pos, token, W, lds, sm, ep0, 5u * (unsigned)nl + 1, xr);
+  gemv_phase<WFMT, HD, K_LM, VQ, LATE, ONE>(nl, pos, token, W, lds, sm, ep0, 5u * (unsigned)nl + 1, xr);
 }
 
 // The grid is one workgroup per CU and a CU holds at most one (registers
