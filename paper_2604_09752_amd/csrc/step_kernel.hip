@@ -83,9 +83,8 @@ AIO_DEV CArgs& step_args() {
 constexpr int kT = 512;          // threads per workgroup
 constexpr int kW = kT / AIO_WAVE; // waves per workgroup
 constexpr int kNLD = 8;  // 16-byte weight loads per lane per batch
-// Batches in flight per wave (register buffers).  A deeper prefetch streams
-// the loops a little faster but delays the input poll queued behind it
-// (vector memory returns in order).
+// Batches in flight per wave (register buffers).  A third one delays the input
+// poll queued behind it: 2 (7B) to 9 % (1B, int8 7B) slower.
 #ifndef AIO_STEP_NBUF
 #define AIO_STEP_NBUF 2
 #endif
@@ -1210,9 +1209,10 @@ AIO_DEV void attn_prefetch(int layer, int pos, KV4& X, KV4& Y) {
 }
 
 // Merge the S split partials of kv head g (its G query heads) into o.
-// Thread (r, c) folds splits r, r + R, ... of output c with a running
-// log-sum-exp; the R partial folds then meet in LDS.  All loads of a thread
-// are issued before its first wait.
+// Thread (r, c) folds splits r, r + R, ... of output c, MS of them at a time
+// (their maximum first, then their weights, which do not depend on one
+// another); the R partial folds then meet in LDS.  All loads of a thread are
+// issued before its first wait.
 template <int HD, int G, int MS>
 AIO_DEV void attn_merge(CArgs& a, int g, float* lds, unsigned ver) {
   constexpr int NOUT = G * HD, R = kT / NOUT;
