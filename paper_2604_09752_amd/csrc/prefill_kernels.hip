@@ -1593,6 +1593,7 @@ hipError_t launch_pnorm(const aio_model& m, const PfBuffers& b, int R, const uin
 //   Short  prompts of a few blocks of 16 rows, split over K to cover the CUs
 //          (23 rows, 1B: QKV 20.5 against Wide's 23.8 us, O 15.6 / 21.4,
 //          gate/up 19.2 / 24.8, down 21.4 / 31.3)
+//          (up to 32 rows most products now go to k_spair and k_sresid)
 struct PfShape {
   int bm, bn, sk, per_cu;
   double few, full, round, base, split, slice;
