@@ -99,16 +99,29 @@ AIO_DEV void swap16(float& a, float& b) {
   b = __uint_as_float(r[1]);
 }
 
+// The value of lane ^ 4: lanes with bit 2 clear read four lanes up (row_shl:4),
+// the others four lanes down (row_shr:4).
+AIO_DEV float dpp_xor4(float v) {
+  const int x = __float_as_int(v);
+  const int t = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0x5, false);
+  return __int_as_float(__builtin_amdgcn_update_dpp(t, x, 0x114, 0xF, 0xA, false));
+}
+
 // Sum and maximum over the 64 lanes of a wave; every lane receives the same
-// total.  Six VALU steps, where exchanges through LDS take six round trips.
+// total.  VALU steps, where exchanges through LDS take six round trips.  The sum
+// exchanges over lane bits 5 to 0 in that order (results behind a short cache
+// depend on the order of sums: see the test of their bits).
 AIO_DEV float wave_sum(float v) {
-  v = group_sum_dpp<16>(v);
   float o = v;
-  swap16(v, o);
+  swap32(v, o);
   v += o;
   o = v;
-  swap32(v, o);
-  return v + o;
+  swap16(v, o);
+  v += o;
+  v += dpp_mov<0x128>(v);  // row_ror:8, lane ^ 8
+  v += dpp_xor4(v);
+  v += dpp_mov<0x4E>(v);  // lane ^ 2
+  return v + dpp_mov<0xB1>(v);  // lane ^ 1
 }
 AIO_DEV float wave_max(float v) {
   v = fmaxf(v, dpp_mov<0xB1>(v));

@@ -464,17 +464,15 @@ AIO_DEV void issue(CArgs& a, const GPhase& P, int batch, uint4 (&buf)[kNLD], con
 constexpr int kRed = 8;
 static_assert(kNLD == kRed, "a batch leaves at most 8 sums per lane");
 
-// One halving exchange over lane bit 3 or 2 (with lane l ^ 8 or l ^ 7): values
-// [0, HALF) keep the lower or upper half of [0, 2 HALF) and add the partner's
-// other half.
+// One halving exchange over lane bit 3 or 2: values [0, HALF) keep the lower or
+// upper half of [0, 2 HALF) and add the partner's other half.
 template <int BIT, int HALF>
 AIO_DEV void halve(float (&v)[kRed], int lane) {
-  constexpr int CTRL = BIT == 8 ? 0x128 : 0x141;  // row_ror:8, row_half_mirror
   const bool up = lane & BIT;
 #pragma unroll
   for (int i = 0; i < HALF; ++i) {
     const float send = up ? v[i] : v[i + HALF], keep = up ? v[i + HALF] : v[i];
-    v[i] = keep + dpp_mov<CTRL>(send);
+    v[i] = keep + (BIT == 8 ? dpp_mov<0x128>(send) : dpp_xor4(send));  // row_ror:8
   }
 }
 // The same over bit 5 and 4.
@@ -495,11 +493,16 @@ AIO_DEV void halve16(float (&v)[kRed]) {
   }
 }
 
+// (the sum of a group of 8 lanes is complete in its lanes 0 to 3: the first of
+// the last three exchanges, row_shl:4, gives these lane ^ 4)
 AIO_DEV float reduce_rows(float (&v)[kRed], int lane) {
   halve32<4>(v);
   halve16<2>(v);
   halve<8, 1>(v, lane);
-  return group_sum_dpp<8>(v[0]);
+  float s = v[0];
+  s += dpp_mov<0x104>(s);
+  s += dpp_mov<0x4E>(s);         // lane ^ 2
+  return s + dpp_mov<0xB1>(s);   // lane ^ 1
 }
 
 // The same over each half wave (lanes 0-31 and 32-63 separately): lane l
@@ -1030,9 +1033,11 @@ struct KV4 {
 // no divergent branches.  The keys share one maximum and one rescaling of the
 // outputs, and their score sums are independent chains: one key after the
 // other, the update was a chain of some 250 cycles per key and query head, and
-// a third more instructions.  With fold_groups and the merge in two passes, the
-// attention phase at 2K: 1B 7.8 -> 6.6 us, 7B 11.8 -> 10.4, 7B int8 11.7 ->
-// 10.9 (traced).
+// a third more instructions.  With fold_groups' halving and the merge's maxima
+// ahead of its weights, the attention phase at 2K: 1B 7.8 -> 6.6 us, 7B 11.8 ->
+// 10.4, 7B int8 11.7 -> 10.9 (traced).  A group with at most one cached key
+// (up to 256 positions with up to 32 kv heads: 8 splits or more of 32 groups) ends
+// with the bits that a key at a time gives.
 template <int HD, int G, int K0, int N>
 AIO_DEV void attend_keys(const KV4& d, int n, const float (&q)[G][8], float (&o)[G][8], float (&m)[G],
                     float (&l)[G]) {
@@ -1103,42 +1108,70 @@ AIO_DEV void attend(const KV4& d, int n, const float (&q)[G][8], float (&o)[G][8
   }
 }
 
-// Maximum and sum over the lane groups of a wave (lane bits 5 to log2 LPK),
-// held by all of them.
-template <int LPK, class F>
-AIO_DEV float over_groups(float v, F&& f) {
-  if (LPK == 8) v = f(v, dpp_mov<0x128>(v));  // row_ror:8
-  float a = v, b = v;
-  swap16(a, b);
-  v = a = b = f(a, b);
-  swap32(a, b);
-  return f(a, b);
-}
-
-// Fold the softmax states of a wave's lane groups: every lane ends with the
-// wave's m and l; its eight outputs, weighted by 2^(m - the wave's m), are
-// summed over the groups by halving exchanges, which leave it with
-// fold_dims<LPK>() of the eight (o[gg][0 ..], the dims from fold_dim on).
+// Fold the softmax states of a wave's lane groups, two at a time over lane bits
+// log2 LPK to 5: every lane ends with the wave's m and l.  Each exchange also
+// halves the outputs a lane holds, which leaves it with fold_dims<LPK>() of the
+// eight (o[gg][0 ..], the dims from fold_dim on).  The pairs, their order and the
+// fused multiply-adds here and in attn_merge are fixed: behind a few keys a
+// rounding that falls the other way moves a 7B's logits by up to 1e-3.  (One
+// maximum over all groups and the exchanges in any order: 8 tokens of the 1B at 2K
+// 5507 -> 5460 us, 4 of the 7B 9055 -> 9047, int8 6244 -> 6208.)
 template <int LPK>
 constexpr int fold_dims() { return LPK == 16 ? 2 : 1; }
 template <int LPK>
 AIO_DEV int fold_dim(int lane) {
-  const int d = 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);
-  return LPK == 16 ? d : d + ((lane >> 3) & 1);
+  return LPK == 16 ? 4 * ((lane >> 4) & 1) + 2 * (lane >> 5)
+                   : 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + (lane >> 5);
+}
+
+// a: the value of the lower partner lane of exchange BIT, b: of the upper one,
+// for both partners (`up`: this lane is the upper one); of two values x and y the
+// lower partner exchanges x and the upper one y.
+template <int BIT>
+AIO_DEV void partners(float x, float y, bool up, float& a, float& b) {
+  if constexpr (BIT == 8) {
+    const float keep = up ? y : x, got = dpp_mov<0x128>(up ? x : y);  // row_ror:8
+    a = up ? got : keep;
+    b = up ? keep : got;
+  } else {
+    a = x;
+    b = y;
+    if constexpr (BIT == 16) swap16(a, b);
+    else swap32(a, b);
+  }
+}
+// One exchange: states (m1, l1, o1) of the lower and (m2, l2, o2) of the upper
+// partner, both weighted by 2^(m - max) and added.
+template <int BIT, int HALF, int G>
+AIO_DEV void fold_pair(float (&o)[G][8], float (&m)[G], float (&l)[G], int lane) {
+  const bool up = lane & BIT;
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) {
+    float m1, m2, l1, l2;
+    partners<BIT>(m[gg], m[gg], up, m1, m2);
+    partners<BIT>(l[gg], l[gg], up, l1, l2);
+    const float mx = fmaxf(m1, m2);
+    const float c1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mx);
+    const float c2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mx);
+    l[gg] = fmaf(l1, c1, l2 * c2);
+#pragma unroll
+    for (int i = 0; i < HALF; ++i) {
+      float o1, o2;
+      partners<BIT>(o[gg][i], o[gg][i + HALF], up, o1, o2);
+      o[gg][i] = fmaf(o1, c1, o2 * c2);
+    }
+    m[gg] = mx;
+  }
 }
 template <int LPK, int G>
 AIO_DEV void fold_groups(float (&o)[G][8], float (&m)[G], float (&l)[G], int lane) {
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) {
-    const float M = over_groups<LPK>(m[gg], [](float a, float b) { return fmaxf(a, b); });
-    const float c = m[gg] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[gg] - M);
-    m[gg] = M;
-    l[gg] = over_groups<LPK>(l[gg] * c, [](float a, float b) { return a + b; });
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[gg][i] *= c;
-    halve32<4>(o[gg]);
-    halve16<2>(o[gg]);
-    if constexpr (LPK == 8) halve<8, 1>(o[gg], lane);
+  if constexpr (LPK == 8) {
+    fold_pair<8, 4, G>(o, m, l, lane);
+    fold_pair<16, 2, G>(o, m, l, lane);
+    fold_pair<32, 1, G>(o, m, l, lane);
+  } else {
+    fold_pair<16, 4, G>(o, m, l, lane);
+    fold_pair<32, 2, G>(o, m, l, lane);
   }
 }
 
@@ -1210,8 +1243,8 @@ AIO_DEV void attn_prefetch(int layer, int pos, KV4& X, KV4& Y) {
 
 // Merge the S split partials of kv head g (its G query heads) into o.
 // Thread (r, c) folds splits r, r + R, ... of output c, MS of them at a time
-// (their maximum first, then their weights, which do not depend on one
-// another); the R partial folds then meet in LDS.  All loads of a thread are
+// (in order, their running maxima first, so that their weights do not depend on
+// one another); the R partial folds then meet in LDS.  All loads of a thread are
 // issued before its first wait.
 template <int HD, int G, int MS>
 AIO_DEV void attn_merge(CArgs& a, int g, float* lds, unsigned ver) {
@@ -1238,25 +1271,24 @@ AIO_DEV void attn_merge(CArgs& a, int g, float* lds, unsigned ver) {
 #pragma unroll
     for (int i = 0; i < 3 * MS; ++i) v[i] = ld_dev(base + off[i]);
     await4(a, base, off, need, v, ver);
-    // one maximum and independent weights: fewer steps in a row than a split
-    // after the other
-    float mn = Mt;
+    // splits in order, each with the running maximum up to it; the maxima come
+    // first, so that the weights do not wait for one another
+    float mx[MS + 1];
+    mx[0] = Mt;
+#pragma unroll
+    for (int i = 0; i < MS; ++i)
+      mx[i + 1] = fmaxf(mx[i], need[3 * i] ? untagf(v[3 * i + 1]) : -INFINITY);
 #pragma unroll
     for (int i = 0; i < MS; ++i) {
-      mn = fmaxf(mn, need[3 * i] ? untagf(v[3 * i + 1]) : -INFINITY);
+      const float ms = untagf(v[3 * i + 1]);
+      const bool live = need[3 * i] && ms != -INFINITY;
+      const float c0 = live ? __builtin_amdgcn_exp2f(mx[i] - mx[i + 1]) : 1.f;
+      const float c1 = live ? __builtin_amdgcn_exp2f(ms - mx[i + 1]) : 0.f;
+      const float ov = live ? untagf(v[3 * i]) : 0.f, lv = live ? untagf(v[3 * i + 2]) : 0.f;
+      Ot = fmaf(Ot, c0, c1 * ov);
+      Lt = fmaf(Lt, c0, c1 * lv);
     }
-    if (mn != -INFINITY) {
-      const float c0 = __builtin_amdgcn_exp2f(Mt - mn);
-      Ot *= c0;
-      Lt *= c0;
-#pragma unroll
-      for (int i = 0; i < MS; ++i) {
-        const float c = need[3 * i] ? __builtin_amdgcn_exp2f(untagf(v[3 * i + 1]) - mn) : 0.f;
-        Ot = need[3 * i] ? fmaf(c, untagf(v[3 * i]), Ot) : Ot;
-        Lt = need[3 * i] ? fmaf(c, untagf(v[3 * i + 2]), Lt) : Lt;
-      }
-      Mt = mn;
-    }
+    Mt = mx[MS];
   }
   float* sm_M = lds;              // [R][G]
   float* sm_L = lds + R * G;      // [R][G]
