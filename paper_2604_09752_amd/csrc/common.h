@@ -111,17 +111,25 @@ AIO_DEV float dpp_xor4(float v) {
 // total.  VALU steps, where exchanges through LDS take six round trips.  The sum
 // exchanges over lane bits 5 to 0 in that order (results behind a short cache
 // depend on the order of sums: see the test of their bits).
-AIO_DEV float wave_sum(float v) {
+AIO_DEV float half_wave_sum(float v) {
   float o = v;
-  swap32(v, o);
-  v += o;
-  o = v;
   swap16(v, o);
   v += o;
   v += dpp_mov<0x128>(v);  // row_ror:8, lane ^ 8
   v += dpp_xor4(v);
   v += dpp_mov<0x4E>(v);  // lane ^ 2
   return v + dpp_mov<0xB1>(v);  // lane ^ 1
+}
+AIO_DEV float wave_sum(float v) {
+  float o = v;
+  swap32(v, o);
+  return half_wave_sum(v + o);
+}
+// The sum of x^2, the lower half's squares fused into the first exchange.
+AIO_DEV float wave_sum_sq(float x) {
+  float o = x;
+  swap32(x, o);
+  return half_wave_sum(fmaf(x, x, o * o));
 }
 AIO_DEV float wave_max(float v) {
   v = fmaxf(v, dpp_mov<0xB1>(v));

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kNormThreads) void k_pnorm(PNormArgs a) {
       }
       out[e] = v * bf16_to_f32(a.gain[e]);
     }
-    const float sq = wave_sum(v * v);
+    const float sq = wave_sum_sq(v);
     if ((tid & (AIO_WAVE - 1)) == 0 && e < a.d) a.ss[(size_t)r * (a.d / 64) + e / 64] = sq;
   }
 }
@@ -1554,7 +1554,7 @@ __global__ __launch_bounds__(kGBlock, 1) void k_sresid(PGemmArgs a) {
     a.out[(size_t)r * a.ldo + n] = x;
     if (a.act_next) {
       a.act_next[(size_t)r * a.lda_next + n] = x * gn;
-      const float sq = wave_sum(x * x);
+      const float sq = wave_sum_sq(x);
       if (lane == 0) a.ss_out[(size_t)r * a.nss + blockIdx.x] = sq;
     }
   }

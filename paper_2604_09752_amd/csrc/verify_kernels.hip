@@ -38,6 +38,16 @@ namespace {
 
 constexpr int kMaxRows = AIO_MAX_VERIFY_ROWS;
 
+// Up to this many visible positions a verify's sums keep one order.  There the new
+// rows attend mostly to one another, so a K or V element whose fp32 value rounds
+// the other way moves everything after it: two orders of the gate/up sums put the
+// cache rows of a 7B verify of 4 rows at position 17 up to 1.1e-3 apart (each as
+// far from a 64-bit evaluation), 7e-4 at 40, 2.5e-4 at 400 and 2048.  So gate/up
+// runs in the order of k_vgemm_sk up to here, some 4 us per layer of a 7B slower
+// than k_vpair, which takes it beyond; every other kernel of a verify has the same
+// order on both sides (256: one attention split, a key block per wave).
+constexpr int kOrderKeys = 256;
+
 // Device-coherent access for the slices of a split residual product: the
 // parts are written through to memory and read past the (per-XCD) L2, so
 // handing them over needs no fence that writes back or drops a whole L2
@@ -104,7 +114,7 @@ __global__ __launch_bounds__(kNormBlock) void k_vnorm(VNormArgs a) {
       v = xr[e];
     }
     store_split(a.act, a.lda, a.M, r, e, v * bf16_to_f32(a.gain[e]));
-    const float sq = wave_sum(v * v);
+    const float sq = wave_sum_sq(v);
     if ((tid & (AIO_WAVE - 1)) == 0) a.ss[(size_t)r * (a.d / 64) + e / 64] = sq;
   }
 }
@@ -145,6 +155,11 @@ struct VGemmArgs {
   int pairs, np;            // QKV, SWIGLU: row pairs of the product and per workgroup
   int pos;                  // QKV: position of the first row
   UDiv by_np, by_nst;       // divisions by np and by the K stages (QKV, SWIGLU)
+  // stream-K SWIGLU: `units` units in ranges of each or each + 1; shared tile
+  // pairs' sums in skpart, their arrivals counted in skcnt
+  int units, each, rest;
+  float* skpart;
+  int* skcnt;
 };
 
 // Register sets of weight stages in flight per workgroup (three measured
@@ -190,14 +205,16 @@ AIO_DEV void vred_put(float* red, int wid, int rl, int kh, bool col_live,
     for (int v = 0; v < 16; ++v)
       red[(wid * T + t) * kVRedTile<T> + (8 * (v / 4) + 4 * kh + (v % 4)) * 33 + rl] = acc[t][v];
 }
-// Row r of output i of tile t: every wave's sums of the three split terms.
+// Row r of output i of tile t: every wave's sums of the three split terms, waves
+// w and w + 4 first (an order that results behind a short cache keep to).
 template <int T>
 AIO_DEV float vred_sum(const float* red, int t, int i, int r, int M) {
+  constexpr int kHalf = kGWaves / 2, kNext = kHalf * T * kVRedTile<T>;
   float s = 0.f;
 #pragma unroll
-  for (int w = 0; w < kGWaves; ++w) {
+  for (int w = 0; w < kHalf; ++w) {
     const float* p = red + (w * T + t) * kVRedTile<T> + i * 33 + r;
-    s += p[0] + p[M] + p[2 * M];
+    s += (p[0] + p[kNext]) + (p[M] + p[M + kNext]) + (p[2 * M] + p[2 * M + kNext]);
   }
   return s;
 }
@@ -245,8 +262,8 @@ AIO_DEV void vpair_epi(const VGemmArgs& a, const PairIn& in, int p, int r, float
     const int head = p >> (hd_shift(a.hd) - 1), ii = p - head * half, n = head * a.hd + ii;
     float lo = y0, hi = y1;
     if (n < qrows + krows) {
-      lo = y0 * in.cs.x - y1 * in.cs.y;
-      hi = y1 * in.cs.x + y0 * in.cs.y;
+      lo = fmaf(y0, in.cs.x, -(y1 * in.cs.y));
+      hi = fmaf(y1, in.cs.x, y0 * in.cs.y);
     }
     if (n < qrows) {
       a.out[(size_t)r * a.ldo + n] = lo;
@@ -514,23 +531,26 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
       }
       a.out[(size_t)r * a.ldo + n] = x;
       store_split(a.act_next, a.lda, M, r, n, x * gn[it]);
-      const float sq = wave_sum(x * x);
+      const float sq = wave_sum_sq(x);
       if (lane == 0) a.ss_out[(size_t)r * nt + blockIdx.x] = sq;
     }
   }
 }
 
-// The QKV and gate/up products: outputs in pairs of weight rows (QKV: rows ii
-// and ii + hd / 2 of a head section, SWIGLU: the same row of gate and up).
-// Workgroup b owns the np pairs from np b: as many as spread the product
-// evenly over the CUs, up to 64, so every CU streams the same bytes in one
-// workgroup.  Measured (7B: 9 rows at 2048, 1B: 3 rows at 1531), in us, against
-// workgroups of whole 32-row tile pairs (QKV) and tile pairs dealt out over the CUs whose
-// shares then met through memory (SWIGLU): gate/up 7B bf16 (43 pairs) 38.2 ->
-// 34.0, int8 27.0 -> 23.3, 1B (22 pairs) 15.3 -> 11.1; QKV 1B (8 pairs; 32
-// before, on 64 CUs) 10.8 -> 7.7, 7B int8 (24 pairs) 16.6 -> 16.2.  The 7B's bf16 QKV does not gain
-// (22.3 -> 23.2): its 192 workgroups of 32 pairs already streamed at the rate
-// HBM gives.  Other np (22 to 64) were within 3 % or slower.
+// The QKV product and, behind all but a short cache, gate/up: outputs in pairs of
+// weight rows (QKV: rows ii and ii + hd / 2 of a head section, SWIGLU: the same row
+// of gate and up).  Workgroup b owns the np pairs from np b.
+//   SWIGLU: as many as spread the product evenly over the CUs, up to 64, so every
+// CU streams the same bytes in one workgroup.  Measured (7B: 9 rows at 2048, 1B: 3
+// rows at 1531), in us, against k_vgemm_sk: 7B bf16 (43 pairs) 38.2 -> 34.0, int8
+// 27.0 -> 23.3, 1B (22 pairs) 15.3 -> 11.1.  Other np (22 to 64) were within 3 %
+// or slower.
+//   QKV: a power of two up to 32, the least that covers the product in one round,
+// so that a workgroup lies in one block of 32 pairs and takes the K stages in the
+// order that belongs to that block: the sums are the same whatever np.  1B (8
+// pairs) 10.8 -> 7.7 us against 32 pairs on 64 CUs.  The 7B's 192 workgroups of 32
+// pairs stream at the rate HBM gives (24 pairs on 256 CUs: bf16 22.3 -> 23.2,
+// int8 16.6 -> 16.2).
 //
 // As in k_vgemm, the weights pass through LDS in stages of 256 k, with NS
 // stages in flight in registers, and wave w multiplies 32-k block w of every
@@ -592,8 +612,10 @@ __global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
   }
   const uint16_t* actp = a.act + (size_t)(col_live ? rl : 0) * a.lda;
   const int nkb = a.K / 32, nst = (nkb + St::BPS - 1) / St::BPS;
-  // workgroup b starts at stage b mod nst and wraps (see k_vgemm)
-  const int rot = (int)blockIdx.x - udiv(blockIdx.x, a.by_nst) * nst;
+  // the stages start at stage b mod nst and wrap (see k_vgemm); b counts blocks of
+  // 32 pairs in QKV, workgroups in SWIGLU
+  const int rb = EPI == EPI_QKV ? p0 / 32 : (int)blockIdx.x;
+  const int rot = rb - udiv(rb, a.by_nst) * nst;
   auto kb0 = [&](int st) {  // first 32-k block of stage st (st < 2 nst)
     const int q = st + rot;
     return (q >= nst ? q - nst : q) * St::BPS;
@@ -691,6 +713,209 @@ __global__ __launch_bounds__(kGBlock, 1) void k_vpair(VGemmArgs a) {
   }
 }
 
+// Stream-K form of the gate/up product, behind a short cache (kOrderKeys).  The
+// product's units, a tile pair (32 rows of gate and of up) times a stage of 256 k,
+// are dealt out in equal contiguous ranges in (tile pair, stage) order, one range
+// per workgroup and one workgroup per CU; the register pipeline (two stages in
+// flight, as in k_vgemm) runs on across tile pairs.  A tile pair inside the range
+// gets its epilogue as soon as its last stage is multiplied; a pair the range
+// shares with its neighbours (at most one at each end) keeps its sums in registers
+// until the range is done, then writes them through to skpart at its slot (its rank
+// among the pair's workgroups) and counts itself in skcnt; the last to arrive adds
+// the slots in slot order and runs the epilogue.
+constexpr int kSkMaxC = kVerifySkMaxC;  // most workgroups sharing one tile pair
+
+template <int WFMT>
+__global__ __launch_bounds__(kGBlock, 1) void k_vgemm_sk(VGemmArgs a) {
+  constexpr int T = 2;
+  using St = VStage<WFMT>;
+  extern __shared__ __align__(16) char smem[];
+  float* red = (float*)smem;
+  __shared__ float inv_s[kMaxRows];
+  __shared__ int last_s[2];
+  const int tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
+  const int rl = lane & 31, kh = lane >> 5;
+  constexpr int wbytes = WFMT == AIO_WFMT_BF16 ? 2 : 1;
+  const int M = a.M;
+  const bool col_live = rl < 3 * M;
+  static_assert(St::BPW == 1, "one block per wave and stage");
+  const int nkb = a.K / 32, nst = (nkb + St::BPS - 1) / St::BPS;
+  // range [u0, u1) of workgroup b: b U / G to (b + 1) U / G
+  const unsigned G = gridDim.x, gb = blockIdx.x;
+  const int u0 = (int)(gb * (unsigned)a.each + gb * (unsigned)a.rest / G);
+  const int u1 = (int)((gb + 1) * (unsigned)a.each + (gb + 1) * (unsigned)a.rest / G);
+  // workgroup whose range holds unit u
+  auto owner = [&](int u) { return (int)(((unsigned)(u + 1) * G - 1) / (unsigned)a.units); };
+
+  const uint16_t* actp = a.act + (size_t)(col_live ? rl : 0) * a.lda;
+  // staging: load j of this thread is chunk lchunk of stage row j RPL + tid / CPR
+  // (row < 32: tile 0, else tile 1, of whichever pair the unit belongs to)
+  constexpr int RPL = kGBlock / St::CPR;
+  const int lchunk = tid % St::CPR, lrow = tid / St::CPR;
+  const int kend = a.K * wbytes - 16;  // last 16-byte chunk of a row
+  // loads past the range re-read its last unit (and are not multiplied)
+  auto gload_w = [&](uint4 (&R)[St::NLD], int u) {
+    const int uu = min(u, u1 - 1), tp = udiv(uu, a.by_nst), s = uu - tp * nst;
+    const int off = min(s * St::KC * wbytes + lchunk * 16, kend);
+#pragma unroll
+    for (int j = 0; j < St::NLD; ++j) {
+      const int rr = j * RPL + lrow;
+      const char* w = (const char*)(rr >= 32 ? a.w1 : a.w0);
+      R[j] = ldg_nt(w + (size_t)(tp * 32 + (rr & 31)) * a.K * wbytes + off);
+    }
+  };
+  auto gload_a = [&](uint4 (&A)[2], int u) {
+    const int uu = min(u, u1 - 1), s = uu - udiv(uu, a.by_nst) * nst;
+    const int block = min(s * St::BPS + wid, nkb - 1) * 32;
+    A[0] = ldg(actp + vk_lo<WFMT>(block, kh));
+    A[1] = ldg(actp + vk_hi<WFMT>(block, kh));
+  };
+  auto stage = [&](const uint4 (&R)[St::NLD]) {
+    __syncthreads();  // every wave is done with the previous stage
+#pragma unroll
+    for (int j = 0; j < St::NLD; ++j) {
+      const u32x4 w = {R[j].x, R[j].y, R[j].z, R[j].w};
+      *(u32x4*)(smem + (j * RPL + lrow) * St::RS + lchunk * 16) = w;
+    }
+    __syncthreads();
+  };
+  f32x16 acc[T];
+  auto zero_acc = [&]() {
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+  };
+  // branch-free: a block past the end multiplies zeros
+  auto product = [&](int u, const uint4 (&A)[2]) {
+    const int s = u - udiv(u, a.by_nst) * nst;
+    VFrag<WFMT, T> f;
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      frag_lds<WFMT>(smem + (t * 32 + rl) * St::RS, wid, kh, f.wa[t], f.wb[t]);
+    f.ba = __builtin_bit_cast(bf16x8, A[0]);
+    f.bb = __builtin_bit_cast(bf16x8, A[1]);
+    vmma(f, col_live && s * St::BPS + wid < nkb, acc);
+  };
+
+  uint4 R[2][St::NLD], A[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    gload_w(R[i], u0 + i);
+    gload_a(A[i], u0 + i);
+  }
+  float ssp[2][2];
+  vnorm_request(a, wid, lane, ssp);
+  vnorm_finish(a, wid, lane, ssp, inv_s);  // (published by the first stage's barriers)
+  const int er = tid / 32, ei = tid % 32;  // this thread's epilogue element
+  // the range's shared tile pairs: [0] the one it starts in, [1] the one it ends in
+  // (-1: none), and this thread's sums of them
+  int ptp[2] = {-1, -1};
+  float py[2][T] = {{0.f, 0.f}, {0.f, 0.f}};
+  auto finish = [&](int tp, float y0, float y1) {
+    const int p = tp * 32 + ei;
+    vpair_epi<WFMT, EPI_SWIGLU>(a, vpair_in<WFMT, EPI_SWIGLU>(a, p, er), p, er, y0 * inv_s[er],
+                                y1 * inv_s[er]);
+  };
+  zero_acc();
+  // After the product of unit u: if u ends a segment (the last unit of a tile pair
+  // or of the range), sum it over the waves and finish or keep it.
+  auto seg_end = [&](int u) {
+    const int tp = udiv(u, a.by_nst);
+    if (u + 1 != u1 && u + 1 != (tp + 1) * nst) return;
+    __syncthreads();  // the stage buffer becomes the partial-tile buffer
+    vred_put<T>(red, wid, rl, kh, col_live, acc);
+    __syncthreads();
+    zero_acc();
+    float y[T] = {0.f, 0.f};
+    if (tid < 32 * M) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) y[t] = vred_sum<T>(red, t, ei, er, M);
+    }
+    // (the next stage() starts with a barrier: every read is done before it writes)
+    const bool head = u0 > tp * nst;  // the segment starts inside the pair
+    if (!head && u + 1 == (tp + 1) * nst) {
+      if (tid < 32 * M) finish(tp, y[0], y[1]);
+    } else if (head || tp * nst == u0) {
+      ptp[0] = tp;
+      py[0][0] = y[0];
+      py[0][1] = y[1];
+    } else {
+      ptp[1] = tp;
+      py[1][0] = y[0];
+      py[1][1] = y[1];
+    }
+  };
+  auto step = [&](uint4 (&Rs)[St::NLD], uint4 (&As)[2], int u) {
+    stage(Rs);
+    __builtin_amdgcn_sched_barrier(0);
+    gload_w(Rs, u + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    product(u, As);
+    __builtin_amdgcn_sched_barrier(0);
+    gload_a(As, u + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    seg_end(u);
+  };
+  int u = u0;
+  for (; u + 2 <= u1; u += 2) {
+    step(R[0], A[0], u);
+    step(R[1], A[1], u + 1);
+  }
+  if (u < u1) {
+    stage(R[0]);
+    product(u, A[0]);
+    seg_end(u);
+  }
+
+  // shared tile pairs: write the sums through, count, and the last of the pair's
+  // workgroups adds the slots in order and finishes it
+  if (ptp[0] < 0 && ptp[1] < 0) return;
+  int ncon[2] = {0, 0};
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (ptp[p] < 0) continue;
+    const int first = ptp[p] * nst, g0 = owner(first);
+    ncon[p] = owner(first + nst - 1) - g0 + 1;
+    if (tid < 32 * M) {
+      float* dst = a.skpart + ((size_t)ptp[p] * kSkMaxC + (gb - g0)) * (kMaxRows * 64) + er * 64 + ei;
+      st_agent(dst, py[p][0]);
+      st_agent(dst + 32, py[p][1]);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      last_s[p] = ptp[p] >= 0 && atomic_add_agent(a.skcnt + ptp[p], 1) == ncon[p] - 1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (!last_s[p]) continue;
+    if (tid == 0) atomic_store_agent(a.skcnt + ptp[p], 0);  // ready for the next product
+    if (tid < 32 * M) {
+      const float* src = a.skpart + (size_t)ptp[p] * kSkMaxC * (kMaxRows * 64) + er * 64 + ei;
+      float v0[kSkMaxC], v1[kSkMaxC];
+#pragma unroll
+      for (int k = 0; k < kSkMaxC; ++k) {
+        const int kk = k < ncon[p] ? k : 0;
+        v0[k] = ld_agent(src + (size_t)kk * (kMaxRows * 64));
+        v1[k] = ld_agent(src + (size_t)kk * (kMaxRows * 64) + 32);
+      }
+      float y0 = 0.f, y1 = 0.f;
+#pragma unroll
+      for (int k = 0; k < kSkMaxC; ++k)
+        if (k < ncon[p]) {
+          y0 += v0[k];
+          y1 += v1[k];
+        }
+      finish(ptp[p], y0, y1);
+    }
+  }
+}
+
 // ------------------------------------------------------- causal attention
 
 struct VAttnArgs {
@@ -741,7 +966,9 @@ struct VAttnArgs {
 // the CUs or the merge take): the blocks a wave streams one after the other are
 // the kernel's critical path, about 2 us each at 2K context.  With the
 // weights of the fold computed per wave and a merge of one round trip: 7B, 9
-// rows at 2048, 17.5 -> 15.1 us, 1B, 3 rows at 1531, 13.2 -> 10.7.
+// rows at 2048, 17.5 -> 15.1 us, 1B, 3 rows at 1531, 13.2 -> 10.7.  Up to 256
+// positions there is one split with a block per wave, and the fold's order is the
+// only one: results there do not depend on how longer contexts are split.
 constexpr int kVAW = 8;
 constexpr int kVattnBlocksPerSplit = kVAW;
 
@@ -794,12 +1021,13 @@ AIO_DEV void vattn_load(const uint16_t* kbase, const uint16_t* vbase, int kb, in
 // Merge of head h's S <= 64 splits for the M rows (by the split that finished
 // last; the others' states are in memory, read past the caches).  The splits'
 // (max, sum) pairs of a row, one per lane (of 8 lanes up to eight splits, else
-// of a wave), become their weights 2^(m - max m) / sum; every output element
-// adds its splits' outputs with them, in split order.  The outputs of the
+// of a wave), become their weights 2^(m - max m) and the row's sum; every output
+// element adds its splits' outputs with them, in split order, and divides by the
+// sum (a single split's weight is 1, its output exact).  The outputs of the
 // first eight splits are requested with the pairs, so up to eight splits take
 // one round trip.
 template <int HD>
-AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64]) {
+AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64], float* sums) {
   constexpr int NT = kVAW * AIO_WAVE, NI = (kMaxRows * HD + NT - 1) / NT;
   const int M = a.M, S = a.S, tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
   const bool few = S <= 8;
@@ -827,7 +1055,8 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64]) {
     const float mx = group_max8_dpp(m);
     const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
     const float l = group_sum_dpp<8>((tid & 7) < S ? w * lv[0] : 0.f);
-    if (tid < 8 * M) wts[tid / 8][tid & 7] = l > 0.f ? w / l : 0.f;
+    if (tid < 8 * M) wts[tid / 8][tid & 7] = w;
+    if (tid < 8 * M && (tid & 7) == 0) sums[tid / 8] = l;
   } else {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -836,7 +1065,8 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64]) {
       const float mx = wave_max(m);
       const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
       const float l = wave_sum(lane < S ? w * lv[q] : 0.f);
-      if (r < M) wts[r][lane] = l > 0.f ? w / l : 0.f;
+      if (r < M) wts[r][lane] = w;
+      if (r < M && lane == 0) sums[r] = l;
     }
   }
   __syncthreads();
@@ -856,7 +1086,8 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64]) {
       for (int j = 0; j < 8; ++j)
         if (s0 + j < S) o += x[j] * wts[r][s0 + j];
     }
-    store_split(a.act, a.lda, M, r, h * HD + dim, o);
+    const float l = sums[r];
+    store_split(a.act, a.lda, M, r, h * HD + dim, l > 0.f ? o / l : 0.f);
   }
 }
 
@@ -1063,41 +1294,51 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   __syncthreads();
 
   // The split's state of its M rows, written through to memory: (max, sum) in
-  // log2 units and the unnormalized output, the waves' added with weights
-  // 2^(m - max m) in wave order.  Thread 8 r + w gives wave w's weight in row
-  // r.
+  // log2 units and the unnormalized output, the waves' folded in wave order, each
+  // step weighting the state so far by c1 and the wave's by c2 (2^ their maxima
+  // minus the new maximum).  Thread 8 r + w computes step w of row r.
   static_assert(kVAW == 8, "a group of 8 lanes holds a row's waves");
   __shared__ float wts[kMaxRows][64];
   if (tid < 8 * kMaxRows) {
     const int r = tid / 8, w = tid & 7;
-    const float mw = r < M ? mm[w * kMaxRows + r] : -INFINITY;
-    const float ms = group_max8_dpp(mw);
-    const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - ms);
-    const float ls = group_sum_dpp<8>(r < M ? wt * ll[w * kMaxRows + r] : 0.f);
-    wts[r][w] = wt;
-    if (w == 0 && r < M) {
-      float* ml = a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2;
-      st_agent(ml, ms);
-      st_agent(ml + 1, ls);
+    float before = -INFINITY, after = -INFINITY, mw = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < kVAW; ++j) {
+      const float mj = r < M ? mm[j * kMaxRows + r] : -INFINITY;
+      if (j < w) before = fmaxf(before, mj);
+      if (j <= w) after = fmaxf(after, mj);
+      if (j == w) mw = mj;
     }
+    wts[r][2 * w] = before == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(before - after);
+    wts[r][2 * w + 1] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - after);
+    if (w == kVAW - 1 && r < M) st_agent(a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2, after);
   }
   __syncthreads();
   for (int e = tid; e < M * HD; e += NT) {
     const int r = e / HD, dim = e % HD;
     float os = 0.f;
 #pragma unroll
-    for (int w = 0; w < kVAW; ++w) os += wts[r][w] * om[(w * kMaxRows + r) * Lds::OROW + dim];
+    for (int w = 0; w < kVAW; ++w)
+      os = fmaf(os, wts[r][2 * w], om[(w * kMaxRows + r) * Lds::OROW + dim] * wts[r][2 * w + 1]);
     st_agent(a.part_o + (((size_t)r * a.H + h) * a.S + s) * HD + dim, os);
+    if (dim == 0) {
+      float ls = 0.f;
+#pragma unroll
+      for (int w = 0; w < kVAW; ++w)
+        ls = fmaf(ls, wts[r][2 * w], ll[w * kMaxRows + r] * wts[r][2 * w + 1]);
+      st_agent(a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2 + 1, ls);
+    }
   }
   // count the split; the last of head h's splits to arrive merges them
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
+  __shared__ float sums[kMaxRows];
   __shared__ int last_s;
   if (tid == 0) last_s = atomic_add_agent(a.cnt + h, 1) == a.S - 1;
   __syncthreads();
   if (!last_s) return;
   if (tid == 0) atomic_store_agent(a.cnt + h, 0);  // ready for the next layer
-  vattn_merge<HD>(a, h, wts);
+  vattn_merge<HD>(a, h, wts, sums);
 }
 
 // Launch with `blocks` tile pairs.  A residual-add product with fewer tile
@@ -1150,10 +1391,11 @@ hipError_t launch_vpair_t(const aio_model& m, const VGemmArgs& a) {
   return hipGetLastError();
 }
 
-// Launch of a product of `pairs` row pairs, in as few rounds of one workgroup
-// per CU as workgroups of at most 64 pairs allow, each round full.  The load
-// slots of a workgroup (16 rows of bf16, 32 of int8) round its pairs up; few
-// of them leave registers for more stages in flight.
+// Launch of a product of `pairs` row pairs (k_vpair).  SWIGLU: in as few rounds of
+// one workgroup per CU as workgroups of at most 64 pairs allow, each round full.
+// QKV: the least power of two of pairs that takes one round, at most 32.  The load
+// slots of a workgroup (16 rows of bf16, 32 of int8) round its pairs up; few of
+// them leave registers for more stages in flight.
 template <int EPI>
 hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   VGemmArgs a = g;
@@ -1162,8 +1404,13 @@ hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   a.eps = m.cfg.rms_eps;
   a.ss_in = m.at<float>(m.lay.vss);
   a.pairs = pairs;
-  const int rounds = (pairs + 64 * m.num_cus - 1) / (64 * m.num_cus);
-  a.np = (pairs + rounds * m.num_cus - 1) / (rounds * m.num_cus);
+  if (EPI == EPI_QKV) {
+    a.np = 1;
+    while (a.np < 32 && a.np * m.num_cus < pairs) a.np *= 2;
+  } else {
+    const int rounds = (pairs + 64 * m.num_cus - 1) / (64 * m.num_cus);
+    a.np = (pairs + rounds * m.num_cus - 1) / (rounds * m.num_cus);
+  }
   constexpr int kStageBlocks = VStage<AIO_WFMT_BF16>::BPS;
   static_assert(kStageBlocks == VStage<AIO_WFMT_INT8>::BPS, "one stage length");
   a.by_nst = make_udiv((unsigned)((a.K / 32 + kStageBlocks - 1) / kStageBlocks), (unsigned)pairs);
@@ -1172,15 +1419,58 @@ hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   if (m.cfg.wfmt == AIO_WFMT_INT8) {
     if (a.np <= 16) return launch_vpair_t<I8, EPI, 1, 1, 4>(m, a);
     if (a.np <= 32) return launch_vpair_t<I8, EPI, 1, 2, 2>(m, a);
-    if (a.np <= 48) return launch_vpair_t<I8, EPI, 2, 3, 2>(m, a);
-    return launch_vpair_t<I8, EPI, 2, 4, 2>(m, a);
+    if constexpr (EPI == EPI_SWIGLU) {
+      if (a.np <= 48) return launch_vpair_t<I8, EPI, 2, 3, 2>(m, a);
+      return launch_vpair_t<I8, EPI, 2, 4, 2>(m, a);
+    }
+    return hipErrorInvalidValue;
   }
   if (a.np <= 8) return launch_vpair_t<BF, EPI, 1, 1, 4>(m, a);
   if (a.np <= 16) return launch_vpair_t<BF, EPI, 1, 2, 4>(m, a);
-  if (a.np <= 24) return launch_vpair_t<BF, EPI, 1, 3, 2>(m, a);
+  if constexpr (EPI == EPI_SWIGLU)
+    if (a.np <= 24) return launch_vpair_t<BF, EPI, 1, 3, 2>(m, a);
   if (a.np <= 32) return launch_vpair_t<BF, EPI, 1, 4, 2>(m, a);
-  if (a.np <= 48) return launch_vpair_t<BF, EPI, 2, 6, 2>(m, a);
-  return launch_vpair_t<BF, EPI, 2, 8, 2>(m, a);
+  if constexpr (EPI == EPI_SWIGLU) {
+    if (a.np <= 48) return launch_vpair_t<BF, EPI, 2, 6, 2>(m, a);
+    return launch_vpair_t<BF, EPI, 2, 8, 2>(m, a);
+  }
+  return hipErrorInvalidValue;
+}
+
+// Stream-K launch of the gate/up product of `tiles` tile pairs: one workgroup per
+// CU, but every range at least `per` units long, so that at most kSkMaxC - 1
+// ranges meet in one tile pair (a pair of nst units spans at most 1 + ceil((nst -
+// 1) / per) ranges).
+hipError_t launch_vgemm_sk(const aio_model& m, const VGemmArgs& g, int tiles) {
+  VGemmArgs a = g;
+  a.ks = 1;
+  a.nt = m.cfg.d_model / 64;
+  a.eps = m.cfg.rms_eps;
+  a.ss_in = m.at<float>(m.lay.vss);
+  a.skpart = m.at<float>(m.lay.skpart);
+  a.skcnt = m.at<int>(m.lay.skcnt);
+  if ((size_t)tiles > m.lay.sk_tiles) return hipErrorInvalidValue;
+  constexpr int kStageBlocks = VStage<AIO_WFMT_BF16>::BPS;
+  const int nst = (a.K / 32 + kStageBlocks - 1) / kStageBlocks;
+  // (at most 2048 pairs of 256 stages and AIO_STEP_MAX_BLOCKS workgroups: the
+  // kernel's products of units and workgroups fit 32 bits)
+  a.units = tiles * nst;
+  const int per = std::max(2, (nst - 1 + kSkMaxC - 3) / (kSkMaxC - 2));
+  const int blocks =
+      std::max(1, std::min(std::min(m.num_cus, AIO_STEP_MAX_BLOCKS), a.units / per));
+  a.each = a.units / blocks;
+  a.rest = a.units % blocks;
+  a.by_nst = make_udiv((unsigned)nst, (unsigned)a.units);
+  const bool i8 = m.cfg.wfmt == AIO_WFMT_INT8;
+  const void* fn = i8 ? (const void*)k_vgemm_sk<AIO_WFMT_INT8> : (const void*)k_vgemm_sk<AIO_WFMT_BF16>;
+  const int lds = i8 ? vgemm_lds<AIO_WFMT_INT8, 2>(64) : vgemm_lds<AIO_WFMT_BF16, 2>(64);
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  if (i8)
+    hipLaunchKernelGGL(k_vgemm_sk<AIO_WFMT_INT8>, dim3(blocks), dim3(kGBlock), lds, m.stream, a);
+  else
+    hipLaunchKernelGGL(k_vgemm_sk<AIO_WFMT_BF16>, dim3(blocks), dim3(kGBlock), lds, m.stream, a);
+  return hipGetLastError();
 }
 
 // Split of x * g and chunk sums of squares for the M rows of x (layer 0:
@@ -1276,7 +1566,8 @@ hipError_t aio_launch_verify(const aio_model& m, int M, int pos, float* logits,
     gu.w0 = L.w_gate; gu.w1 = L.w_up;
     gu.s0 = (const uint16_t*)L.s_gate; gu.s1 = (const uint16_t*)L.s_up;
     gu.N = F; gu.K = d; gu.act_out = actB; gu.lda_out = ka;
-    if ((e = launch_vpair<EPI_SWIGLU>(m, gu, F)) != hipSuccess) return e;
+    e = pos + M <= kOrderKeys ? launch_vgemm_sk(m, gu, F / 32) : launch_vpair<EPI_SWIGLU>(m, gu, F);
+    if (e != hipSuccess) return e;
 
     VGemmArgs dn{};
     dn.act = actB; dn.lda = ka; dn.M = M;

@@ -1,8 +1,9 @@
-"""Decode behind a short cache gives the bits on record (needs an MI355X with 256 CUs).
+"""Decode, verify and short prefills behind a short cache give the bits on
+record (needs an MI355X with 256 CUs).
 
 Behind a few keys the new rows attend mostly to one another, so one cache entry
 whose fp32 value rounds the other way moves everything after it: two equally
-exact evaluations of a 7B run of 4 tokens at position 20 differ by 9e-4 in the
+exact evaluations of a 7B verify of 4 rows at position 17 differ by 1e-3 in the
 cache rows (each is as far from a 64-bit evaluation), at 2048 positions by 2e-4.
 No bound below that holds there between two orders of the same sums, so up to
 256 positions the kernels keep one order, and these digests (SHA-256 of logits,
@@ -43,8 +44,9 @@ CONFIGS = {
 }
 
 # (call, position, rows)
-CALLS = [("step", 0, 1), ("step", 17, 1), ("step", 128, 1), ("step", 255, 1), ("greedy", 60, 4),
-         ("prefill", 200, 1)]
+CALLS = [("verify", 17, 4), ("verify", 31, 2), ("verify", 100, 9), ("verify", 247, 9),
+         ("verify", 246, 10), ("step", 0, 1), ("step", 17, 1), ("step", 128, 1), ("step", 255, 1),
+         ("greedy", 60, 4), ("prefill", 0, 5), ("prefill", 200, 1)]
 
 
 def digests(name):
@@ -65,14 +67,18 @@ def digests(name):
             gpu.kv.copy_(start)
             torch.cuda.synchronize()
             t = [int(v) for v in toks[pos:pos + rows]]
-            if call == "step":
+            n = 1
+            if call == "verify":
+                gpu.verify(t[0], t[1:], pos, logits)
+                n = rows
+            elif call == "step":
                 gpu.decode_step(t[0], pos, logits)
             elif call == "greedy":
                 gpu.greedy(t[0], pos, rows, ids, logits)
             else:
                 gpu.prefill(t, pos, logits)
             gpu.sync()
-            h = hashlib.sha256(logits[:1].cpu().numpy().tobytes())
+            h = hashlib.sha256(logits[:n].cpu().numpy().tobytes())
             h.update(np.ascontiguousarray(gpu.kv_rows(pos, pos + rows)).tobytes())
             if call == "greedy":
                 h.update(ids[:rows].cpu().numpy().tobytes())
