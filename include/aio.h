@@ -55,9 +55,9 @@ enum {
   AIO_EUNSUPPORTED = -3, /* shape or device this build does not handle      */
   AIO_EHIP = -4,         /* a HIP runtime or launch error; see aio_last_hip_error */
   AIO_ENOMEM = -5,       /* the library's own small allocations failed      */
-  AIO_EDEVICE = -6       /* a bounded wait inside the persistent decode kernel
-                            gave up (aio_device_status); the handle's results
-                            from then on are invalid: free it and load again */
+  AIO_EDEVICE = -6       /* a bounded wait inside a kernel gave up
+                            (aio_device_status); the handle's results from
+                            then on are invalid: free it and load again */
 };
 
 /* Weight storage formats. */
@@ -147,7 +147,8 @@ int aio_last_hip_error(void);
  *  cfg, w      host structs; copied.
  *  kv_dev      aio_kv_bytes(cfg) bytes; positions the caller has not written
  *              are never read before a decode or verify call writes them.
- *  ws_dev      aio_workspace_bytes(cfg) bytes, used only by this handle.
+ *  ws_dev      aio_workspace_bytes(cfg) bytes, used only by this handle; what
+ *              it holds does not matter.
  *  hip_stream  hipStream_t every later call enqueues on (NULL = default stream).
  *  out         receives the handle.
  * Allocates and fills the RoPE table (fp32 cos/sin of angles computed in
@@ -250,8 +251,8 @@ int aio_trace_barriers(aio_model* m, int32_t token, int32_t pos, float* logits_d
 int aio_tune_step(aio_model* m, int32_t token, int32_t pos, float* logits_dev, int32_t rounds);
 
 /* Synchronises the model's stream and reports the device-side status word:
- * 0, or 1 if a bounded wait of the persistent kernel for another
- * workgroup's data gave up.  The word is sticky: once set, the results of
+ * 0, or 1 if a bounded wait for another workgroup's data (in the persistent
+ * kernel or in a prefill product) gave up.  The word is sticky: once set, the results of
  * that step and of every later call on the handle are invalid (free the
  * handle and load again).  Synchronises. */
 int aio_device_status(aio_model* m, int32_t* status);

@@ -285,6 +285,13 @@ int aio_model_load(const aio_config* cfg, const aio_weights* w, void* kv_dev, vo
   e = hipMalloc((void**)&m->rope, n * sizeof(float2));
   if (e == hipSuccess) e = hipMemcpy(m->rope, host, n * sizeof(float2), hipMemcpyHostToDevice);
   free(host);
+  // the status word and the arrival counters of verify and prefill, which every
+  // handle uses (the caller's workspace may hold anything)
+  if (e == hipSuccess) e = hipMemset(m->ws + m->lay.sync, 0, (size_t)kSyncWords * 4);
+  if (e == hipSuccess) e = hipMemset(m->ws + m->lay.vcnt, 0, (size_t)(cfg->d_model / 64) * 4);
+  if (e == hipSuccess) e = hipMemset(m->ws + m->lay.skcnt, 0, m->lay.sk_tiles * 4);
+  if (e == hipSuccess) e = hipMemset(m->ws + m->lay.pcnt, 0, m->lay.pcnt_n * 4);
+  if (e == hipSuccess) e = hipMemset(m->ws + m->lay.vacnt, 0, (size_t)cfg->n_heads * 4);
   if (e == hipSuccess && m->use_mega) {
     std::vector<MegaLayer> tab((size_t)cfg->n_layers);
     for (int l = 0; l < cfg->n_layers; ++l) {
@@ -315,11 +322,6 @@ int aio_model_load(const aio_config* cfg, const aio_weights* w, void* kv_dev, vo
         e = hipMemcpy(m->gu_bounds_dev, m->gu_bounds.data(), m->gu_bounds.size() * sizeof(int),
                       hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = hipMemset(m->ws + m->lay.sync, 0, (size_t)kSyncWords * 4);
-    if (e == hipSuccess) e = hipMemset(m->ws + m->lay.vcnt, 0, (size_t)(cfg->d_model / 64) * 4);
-    if (e == hipSuccess) e = hipMemset(m->ws + m->lay.skcnt, 0, m->lay.sk_tiles * 4);
-    if (e == hipSuccess) e = hipMemset(m->ws + m->lay.pcnt, 0, m->lay.pcnt_n * 4);
-    if (e == hipSuccess) e = hipMemset(m->ws + m->lay.vacnt, 0, (size_t)cfg->n_heads * 4);
     if (e == hipSuccess)
       e = hipMemset(m->ws + m->lay.mega_xa, 0, m->lay.mega_end - m->lay.mega_xa);
   }
@@ -623,7 +625,6 @@ int aio_tune_step(aio_model* m, int32_t token, int32_t pos, float* logits_dev, i
 int aio_device_status(aio_model* m, int32_t* status) {
   if (!m || !status) return AIO_EINVAL;
   *status = 0;
-  if (!m->use_mega) return AIO_OK;
   hipError_t e = hipStreamSynchronize(m->stream);
   unsigned err = 0;
   if (e == hipSuccess)
@@ -635,12 +636,10 @@ int aio_device_status(aio_model* m, int32_t* status) {
 
 int aio_uses_step_kernel(const aio_model* m) { return m && m->use_mega ? 1 : 0; }
 
-// Enqueues a copy of the persistent kernel's status word into *word (0 for
-// handles that do not use that kernel); valid after the stream's next
+// Enqueues a copy of the status word into *word; valid after the stream's next
 // synchronisation, which the generation loops make every round anyway.
 static hipError_t enqueue_status_copy(const aio_model* m, unsigned* word) {
   *word = 0;
-  if (!m->use_mega) return hipSuccess;
   return hipMemcpyAsync(word, m->ws + m->lay.sync + (size_t)kSyncErr * 4, 4,
                         hipMemcpyDeviceToHost, m->stream);
 }

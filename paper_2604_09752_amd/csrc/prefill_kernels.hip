@@ -226,6 +226,7 @@ struct PGemmArgs {
   float* fix;           // [tiles][ks, or 1 for ks == 2][values per lane][lanes of a group]
   size_t fix_bytes;     // room at fix
   int* tcnt;            // [tiles], zero between products
+  int* err;             // the handle's status word: set if a wait gave up
   // the folded RMSNorm: QKV and SWIGLU scale output row r by 1 / sqrt(sum
   // of ss_in[r][0 .. nss) / K + eps); RESID (with act_next) writes x g_next
   // to act_next and ss_out[r][n / 64] for its columns
@@ -798,11 +799,13 @@ __global__ __launch_bounds__(Tl::GT, 2) void k_pgemm(PGemmArgs a) {
     // K split.  Each slice takes a ticket when its product is done (the low
     // half of the tile's counter).  All but the last to arrive write their
     // partial tile through to memory and count it written (the high half);
-    // the last keeps its own in registers, waits for the others' writes
-    // (they hold their tickets, so they are past their products and only
-    // storing: the wait is short and cannot be for a workgroup that has not
-    // started), and adds all of them in slice order, so the sum is the same
-    // whatever the arrival order.  Partials are element-major: every store
+    // the last keeps its own in registers, waits for the others' writes, and
+    // adds all of them in slice order, so the sum is the same whatever the
+    // arrival order.  The others hold their tickets, so they are running, their
+    // first waves past their products: the wait is short and never for a
+    // workgroup that has not started.  It relies on the counter being zero at
+    // entry, and is bounded in case it is not (the step kernel's limit; the
+    // status word then says that results are invalid).  Partials are element-major: every store
     // and load instruction of a wave covers 256 contiguous bytes.  Lanes of
     // prompt rows past R move nothing: at a short prompt most of the tile's
     // rows are.  Two slices need one slot per tile, more need one each.
@@ -829,7 +832,14 @@ __global__ __launch_bounds__(Tl::GT, 2) void k_pgemm(PGemmArgs a) {
       return;
     }
     if (tid == 0) {
-      while ((atomic_load_agent(a.tcnt + tile) >> 16) != a.ks - 1) __builtin_amdgcn_s_sleep(1);
+      unsigned spins = 0;
+      while ((atomic_load_agent(a.tcnt + tile) >> 16) != a.ks - 1) {
+        __builtin_amdgcn_s_sleep(1);
+        if ((++spins & 63u) == 0 && (spins > kSpinLimit || atomic_load_agent(a.err))) {
+          atomic_store_agent(a.err, 1);
+          break;
+        }
+      }
       atomic_store_agent(a.tcnt + tile, 0);  // ready for the next product
     }
     __syncthreads();
@@ -1746,6 +1756,7 @@ hipError_t launch_pgemm_w(const aio_model& m, const PGemmArgs& g0, int units) {
     g.fix_bytes = m.lay.pfix_bytes;
   }
   g.tcnt = m.at<int>(m.lay.pcnt);
+  g.err = m.at<int>(m.lay.sync) + kSyncErr;
   const int pairs = EPI == PE_QKV ? g.N / 2 : g.N;
   int np = 0, sks = 1;
   if (EPI == PE_RESID ? g.R <= kSkRows : sk_pairs(m, g, pairs, &np, &sks))

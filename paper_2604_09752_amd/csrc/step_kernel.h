@@ -29,6 +29,10 @@ enum {
   kSyncWords = 4224
 };
 
+// Polls after which a bounded wait (step kernel, split prefill products) gives up
+// and sets the status word kSyncErr: some 0.1 to 0.2 s.
+constexpr unsigned kSpinLimit = 1u << 17;
+
 // Largest grid the step kernel uses (one workgroup per CU).
 #define AIO_STEP_MAX_BLOCKS 256
 

@@ -89,7 +89,6 @@ constexpr int kNLD = 8;  // 16-byte weight loads per lane per batch
 #define AIO_STEP_NBUF 2
 #endif
 constexpr int kNBUF = AIO_STEP_NBUF;
-constexpr unsigned kSpinLimit = 1u << 17;  // ~0.1-0.2 s of polling
 
 // s_waitcnt immediate for vmcnt(0) with expcnt and lgkmcnt left at their
 // maximum (no wait): vmcnt bits [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8].
