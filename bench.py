@@ -206,6 +206,7 @@ def probe_bench(n: int, reps: int = 5) -> int:
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     binding.aio_category_entropy(dm.handle, lg[0], labels, hc)
+    dm.sync()
     h_dev, cat_dev = [float(v) for v in hc.cpu().numpy()]
     small = cat_dev == 0 and n <= 2048 and h_dev <= 0.45
     route_us = (time.perf_counter() - t0) * 1e6

@@ -279,10 +279,13 @@ def aio_spec_generate(target: int, draft: int, pos: int, token: int, n_new: int,
 def spec_generate(target: "DeviceModel", draft: "DeviceModel", pos: int, token: int, n_new: int,
                   k: int):
     """Draft-model speculative generation over two resident models (synchronous)."""
-    tl = target.new_logits(k + 1)
-    dl = draft.new_logits(1)
-    am = torch.zeros(k + 1, dtype=torch.int32, device=target.device)
-    dt = torch.zeros(max(k, 1), dtype=torch.int32, device=draft.device)
+    # scratch of each model's own stream (the call synchronises both)
+    with torch.cuda.stream(target.stream):
+        tl = target.new_logits(k + 1)
+        am = torch.empty(k + 1, dtype=torch.int32, device=target.device)
+    with torch.cuda.stream(draft.stream):
+        dl = draft.new_logits(1)
+        dt = torch.empty(max(k, 1), dtype=torch.int32, device=draft.device)
     return aio_spec_generate(target.handle, draft.handle, pos, token, n_new, k, tl, dl, am, dt)
 
 
@@ -403,8 +406,9 @@ class DeviceModel:
     def pld_generate(self, history, pos: int, token: int, n_new: int, ngram_max: int,
                      ngram_min: int, k: int):
         """Prompt-lookup greedy generation of n_new tokens (synchronous)."""
-        logits = self.new_logits(k + 1)
-        am = torch.zeros(k + 1, dtype=torch.int32, device=self.device)
+        with torch.cuda.stream(self.stream):
+            logits = self.new_logits(k + 1)
+            am = torch.empty(k + 1, dtype=torch.int32, device=self.device)
         return aio_pld_generate(self.handle, history, pos, token, n_new, ngram_max, ngram_min, k,
                                 logits, am)
 

@@ -103,6 +103,7 @@ def test_argmax_bit_exact_vs_torch(tiny):
     x[6] = rng.standard_normal(TINY.vocab).astype(np.float32)
     logits = torch.from_numpy(x).to(tiny.gpu.device)
     out = torch.zeros(rows, dtype=torch.int32, device=tiny.gpu.device)
+    torch.cuda.synchronize()  # the fill runs on another stream than the model
     tiny.gpu.argmax(logits, rows, out)
     tiny.gpu.sync()
     got = out.cpu().numpy()
@@ -138,10 +139,12 @@ def test_greedy_loop_matches_step_by_step(use_graph, mega):
         g2.decode_step(int(t), p, lg2)
     steps = cfg.n_steps
     toks = torch.zeros(steps, dtype=torch.int32, device=g1.device)
+    torch.cuda.synchronize()  # the fill runs on another stream than the model
     g1.greedy(int(prompt[-1]), cfg.prompt_len - 1, steps, toks, lg1)
     g1.sync()
     # step by step on the second model, argmax fed back from the host
     one = torch.zeros(1, dtype=torch.int32, device=g2.device)
+    torch.cuda.synchronize()
     tok, ref = int(prompt[-1]), []
     for s in range(steps):
         g2.decode_step(tok, cfg.prompt_len - 1 + s, lg2)
@@ -153,6 +156,7 @@ def test_greedy_loop_matches_step_by_step(use_graph, mega):
     assert torch.equal(lg1, lg2)
     # a second greedy call reuses the captured graph and continues correctly
     toks2 = torch.zeros(4, dtype=torch.int32, device=g1.device)
+    torch.cuda.synchronize()
     g1.greedy(ref[-1], cfg.prompt_len - 1 + steps, 4, toks2, lg1)
     g1.sync()
     for s in range(4):

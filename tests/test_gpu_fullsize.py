@@ -21,6 +21,7 @@ pytestmark = [pytest.mark.gpu, pytest.mark.timeout(900)]
 
 def _free_running(pair, token, pos, n):
     toks = torch.zeros(n, dtype=torch.int32, device=pair.gpu.device)
+    torch.cuda.synchronize()  # the fill runs on another stream than the model
     pair.gpu.greedy(token, pos, n, toks, pair.logits[0])
     pair.gpu.sync()
     return [int(t) for t in toks.cpu().numpy()]
@@ -53,6 +54,7 @@ def test_fullsize_teacher_forced(name, n_steps):
             pos = P + n_steps
             nxt = tf.next
             toks = torch.zeros(1, dtype=torch.int32, device=pair.gpu.device)
+            torch.cuda.synchronize()
             pair.gpu.greedy(nxt, pos, 1, toks, pair.logits[0])
             pair.gpu.sync()
             g = pair.logits[0].cpu().numpy()

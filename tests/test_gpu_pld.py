@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 def _greedy_device(pair, token, pos, n):
     toks = torch.zeros(n, dtype=torch.int32, device=pair.gpu.device)
+    torch.cuda.synchronize()  # the fill runs on another stream than the model
     pair.gpu.greedy(token, pos, n, toks, pair.logits[0])
     pair.gpu.sync()
     return toks.cpu().numpy().copy()

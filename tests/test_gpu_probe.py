@@ -139,6 +139,7 @@ def test_category_entropy_on_device_matches_host_rule():
         cases = [list(range(3)), [5, 17, 901, 2, 77], list(range(0, cfg.vocab, cfg.vocab // 40))]
         planted = torch.zeros(cfg.vocab, dtype=torch.float32, device=pair.gpu.device)
         planted[:8] = torch.tensor([3.0, 3.0, -1.0, 0.5, 0.5, 0.5, 0.5, 0.5])
+        torch.cuda.synchronize()  # the fills run on another stream than the model
         for logits, labels in [(row, c) for c in cases] + [(planted, [0, 1, 2]), (planted, [3, 4, 5, 6])]:
             B.aio_category_entropy(pair.gpu.handle, logits, labels, out)
             pair.gpu.sync()

@@ -36,6 +36,7 @@ def _oracle_greedy(pair, token, pos, n):
 
 def _greedy(pair, token, pos, n):
     toks = torch.zeros(n, dtype=torch.int32, device=pair.gpu.device)
+    torch.cuda.synchronize()  # the fill runs on another stream than the model
     pair.gpu.greedy(token, pos, n, toks, pair.logits[0])
     pair.gpu.sync()
     return [int(x) for x in toks.cpu().numpy()]
