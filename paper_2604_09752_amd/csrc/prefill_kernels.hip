@@ -1483,7 +1483,7 @@ __global__ __launch_bounds__(kGBlock, 1) void k_spair(SkArgs sa) {
 
 // O and down: 64 rows of the matrix and one of a.ks K slices per workgroup.
 // With ks > 1 every slice writes its sums through to a.fix[slice][R][N], and
-// the last one to arrive (a.tcnt) adds them in slice order.
+// the last one to arrive (a.tcnt) adds them in slice order, then to x.
 template <int WFMT, int NS>
 __global__ __launch_bounds__(kGBlock, 1) void k_sresid(PGemmArgs a) {
   using St = VStage<WFMT>;
@@ -1553,14 +1553,14 @@ __global__ __launch_bounds__(kGBlock, 1) void k_sresid(PGemmArgs a) {
   for (int it = 0; it < NI; ++it) {
     const int r = wid + kGWaves * it;
     if (r >= a.R) break;  // (whole waves)
-    float x = xv[it];
+    float y = v[it];
     if (a.ks > 1) {
+      y = 0.f;
 #pragma unroll
       for (int k = 0; k < kVerifyMaxKs; ++k)
-        if (k < a.ks) x += pv[it][k];
-    } else {
-      x += v[it];
+        if (k < a.ks) y += pv[it][k];
     }
+    const float x = xv[it] + y;  // (rounded once at x's magnitude)
     a.out[(size_t)r * a.ldo + n] = x;
     if (a.act_next) {
       a.act_next[(size_t)r * a.lda_next + n] = x * gn;
