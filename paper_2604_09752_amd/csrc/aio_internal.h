@@ -158,6 +158,12 @@ struct PfBuffers {
 size_t aio_prefill_row_bytes(const aio_config& c);
 // The chunk scratch laid out from `base` (null: only .bytes is meaningful).
 PfBuffers aio_prefill_buffers(const aio_config& c, char* base, int rcap);
+// What a chunk of `rows` rows takes on a GPU of num_cus CUs, for the tests (not
+// part of the ABI; pure host): out[4][3] = kernel (0 Big, 1 Wide, 2 Short tiles, 3
+// the few-row products), K slices and row pairs per workgroup of QKV, O, gate/up
+// and down.  AIO_OK, or the error of the config or of null or non-positive
+// arguments.
+extern "C" int aio_prefill_plan(const aio_config* c, int rows, int num_cus, int32_t* out);
 // One chunk of R <= b.rcap rows (tokens already in b.tokens) at positions
 // pos0 .. pos0 + R - 1.
 hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int R, int pos0);

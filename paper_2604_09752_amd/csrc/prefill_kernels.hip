@@ -224,7 +224,6 @@ struct PGemmArgs {
   // to fix; tcnt[tile] counts arrivals (low half) and writes (high half)
   int ks;
   float* fix;           // [tiles][ks, or 1 for ks == 2][values per lane][lanes of a group]
-  size_t fix_bytes;     // room at fix
   int* tcnt;            // [tiles], zero between products
   int* err;             // the handle's status word: set if a wait gave up
   // the folded RMSNorm: QKV and SWIGLU scale output row r by 1 / sqrt(sum
@@ -1622,6 +1621,19 @@ constexpr PfShape kPfShapes[3] = {
     pf_shape<Short>(2, 0.25, 0.43, 2.4, 7.9, 1.1, 0.9),
 };
 
+// A product of a layer as the choice of its kernel sees it, and the choice.
+struct PfProduct {
+  int epi;           // PEpi
+  int N, K, R;       // as in PGemmArgs
+  int units;         // units of 128 weight rows
+  size_t fix_bytes;  // room for the sums of K slices
+};
+struct PfPlan {
+  int kernel;  // a tile shape of kPfShapes, or kPfFewRows: k_spair, k_sresid
+  int ks, np;  // K slices; row pairs per workgroup (k_spair)
+};
+constexpr int kPfFewRows = 3;
+
 // Bytes of the partial tiles of `tiles` tiles split into ks slices.
 size_t pf_fix_bytes(const PfShape& s, size_t tiles, int ks) {
   return ks == 1 ? 0 : tiles * (ks == 2 ? 1 : ks) * s.bm * s.bn * 4;
@@ -1629,14 +1641,15 @@ size_t pf_fix_bytes(const PfShape& s, size_t tiles, int ks) {
 
 // Shape and K split (up to kPfMaxKs, within the fix-up room) with the least
 // predicted time.
-void pf_choose(const aio_model& m, int units, int R, int K, size_t fix_bytes, int* shape, int* ks) {
+void pf_choose(const PfProduct& p, int num_cus, size_t counters, int* shape, int* ks) {
+  const int units = p.units, R = p.R, K = p.K;
   double best = 1e30;
   for (int i = 0; i < 3; ++i) {
     const PfShape& s = kPfShapes[i];
     const size_t tiles = (size_t)((units * kUnit + s.bm - 1) / s.bm) * ((R + s.bn - 1) / s.bn);
-    const long long slots = (long long)s.per_cu * m.num_cus;
+    const long long slots = (long long)s.per_cu * num_cus;
     for (int k = 1; k <= kPfMaxKs; k *= 2) {
-      if (k > 1 && (pf_fix_bytes(s, tiles, k) > fix_bytes || tiles > m.lay.pcnt_n || K / s.sk < k))
+      if (k > 1 && (pf_fix_bytes(s, tiles, k) > p.fix_bytes || tiles > counters || K / s.sk < k))
         break;
       const long long wgs = (long long)tiles * k, rem = wgs % slots;
       const double st = (double)K / kKT / k;
@@ -1669,9 +1682,7 @@ hipError_t launch_pgemm_t(const aio_model& m, const PGemmArgs& g, int units) {
 }
 
 // Products of a few prompt rows (SkArgs).  Pairs: one round of workgroups of at
-// most 32 pairs (one 32-row tile of each of their rows).  Residual: K split as
-// far as there are CUs and every wave keeps two blocks, and the slices' sums fit
-// the fix-up room.
+// most 32 pairs (one 32-row tile of each of their rows).
 template <int WFMT, int EPI, int NLD, int NS>
 hipError_t launch_spair_t(const aio_model& m, const SkArgs& a) {
   constexpr int lds = vgemm_lds<WFMT, 2>(64);
@@ -1700,78 +1711,115 @@ hipError_t launch_sresid_t(const aio_model& m, const PGemmArgs& g) {
 // preferred where 32 allow it (QKV of the 1B, K 2048, 23 rows: 8 pairs each 14.8
 // us, 32 of a quarter 12.6).  More than 32 pairs would need a second pair of
 // tiles, whose hi and lo do not fit the registers.
-bool sk_pairs(const aio_model& m, const PGemmArgs& g, int pairs, int* np, int* ks) {
+bool sk_pairs(const PfProduct& p, int num_cus, size_t counters, int* np, int* ks) {
+  const int pairs = p.epi == PE_QKV ? p.N / 2 : p.N;
   for (*ks = kSkPairKs; *ks >= 1; *ks /= 2) {
-    *np = (pairs * *ks + m.num_cus - 1) / m.num_cus;
+    *np = (pairs * *ks + num_cus - 1) / num_cus;
     if (*np > 32) continue;
     const size_t tiles = (size_t)(pairs + *np - 1) / *np;
-    if (*ks > 1 && (g.K / 32 / (*ks * kGWaves) < 2 || tiles > m.lay.pcnt_n ||
-                    tiles * *ks * 2 * *np * g.R * 4 > g.fix_bytes))
+    if (*ks > 1 && (p.K / 32 / (*ks * kGWaves) < 2 || tiles > counters ||
+                    tiles * *ks * 2 * *np * p.R * 4 > p.fix_bytes))
       continue;
-    return g.R <= kSkRows && (size_t)4 * g.R * g.K / *ks <= 384 * 1024;
+    return p.R <= kSkRows && (size_t)4 * p.R * p.K / *ks <= 384 * 1024;
   }
   return false;
 }
 
+// K slices of k_sresid: as far as there are CUs and every wave keeps two blocks,
+// and the slices' sums fit the fix-up room.
+int sk_resid_slices(const PfProduct& p, int num_cus, size_t counters) {
+  const int nkb = p.K / 32, tiles = p.N / 64;
+  int ks = 1;
+  while (tiles * ks < num_cus && 2 * ks <= kVerifyMaxKs && nkb / (2 * ks * kGWaves) >= 2 &&
+         (size_t)tiles <= counters && (size_t)2 * ks * p.R * p.N * 4 <= p.fix_bytes)
+    ks *= 2;
+  return ks;
+}
+
+PfPlan pf_plan(const PfProduct& p, int num_cus, size_t counters) {
+  PfPlan c{kPfFewRows, 1, 0};
+  if (p.epi == PE_RESID && p.R <= kSkRows)
+    c.ks = sk_resid_slices(p, num_cus, counters);
+  else if (p.epi == PE_RESID || !sk_pairs(p, num_cus, counters, &c.np, &c.ks)) {
+    c.np = 0;
+    pf_choose(p, num_cus, counters, &c.kernel, &c.ks);
+  }
+  return c;
+}
+
+// Bytes of scratch that are idle during a product of a chunk of R rows and hold the
+// partial sums of its K slices (sized by R alone, so that the split, and with it
+// the order of the sums, does not depend on how much scratch there is).
+enum PfWhich { PF_QKV = 0, PF_O = 1, PF_GU = 2, PF_DOWN = 3 };
+size_t pf_idle_bytes(const aio_config& c, int which, int R) {
+  const size_t d = (size_t)c.d_model, F = (size_t)c.ffn_dim, Hd = (size_t)c.n_heads * c.head_dim;
+  const size_t words[4] = {d + F, F, Hd + std::max(d, Hd), Hd};
+  return 4 * (size_t)R * words[which];
+}
+
+// The product as pf_plan takes it; the workspace's fix-up region serves where it is
+// the larger one.
+PfProduct pf_product(const aio_config& c, const WsLayout& lay, int which, int R) {
+  PfProduct p{};
+  const int Hd = c.n_heads * c.head_dim;
+  p.epi = which == PF_QKV ? PE_QKV : (which == PF_GU ? PE_SWIGLU : PE_RESID);
+  p.N = which == PF_QKV ? Hd + 2 * c.n_kv_heads * c.head_dim : (which == PF_GU ? c.ffn_dim : c.d_model);
+  p.K = which == PF_O ? Hd : (which == PF_DOWN ? c.ffn_dim : c.d_model);
+  p.R = R;
+  p.units = which == PF_GU ? (p.N + 63) / 64 : (p.N + kUnit - 1) / kUnit;
+  p.fix_bytes = std::max(pf_idle_bytes(c, which, R), lay.pfix_bytes);
+  return p;
+}
+
 template <int WFMT, int EPI>
-hipError_t launch_sk(const aio_model& m, const PGemmArgs& g0, int np, int pairs, int ks) {
+hipError_t launch_sk(const aio_model& m, const PGemmArgs& g, const PfPlan& plan) {
   if constexpr (EPI == PE_RESID) {
-    PGemmArgs g = g0;
-    g.ks = 1;
-    const int nkb = g.K / 32, tiles = g.N / 64;
-    while (tiles * g.ks < m.num_cus && 2 * g.ks <= kVerifyMaxKs && nkb / (2 * g.ks * kGWaves) >= 2 &&
-           (size_t)tiles <= m.lay.pcnt_n && (size_t)2 * g.ks * g.R * g.N * 4 <= g.fix_bytes)
-      g.ks *= 2;
     return launch_sresid_t<WFMT, 2>(m, g);
   } else {
     SkArgs a{};
-    a.g = g0;
-    a.pairs = pairs;
-    a.np = np;
-    a.g.ks = ks;
-    a.by_np = make_udiv((unsigned)np, (unsigned)(np * kSkRows));
+    a.g = g;
+    a.pairs = EPI == PE_QKV ? g.N / 2 : g.N;
+    a.np = plan.np;
+    a.by_np = make_udiv((unsigned)a.np, (unsigned)(a.np * kSkRows));
     constexpr int bps = VStage<WFMT>::BPS;
-    const int slice = (g0.K / 32 + ks - 1) / ks;  // blocks of the longest slice
-    a.by_nst = make_udiv((unsigned)((slice + bps - 1) / bps), (unsigned)pairs);
+    const int slice = (g.K / 32 + g.ks - 1) / g.ks;  // blocks of the longest slice
+    a.by_nst = make_udiv((unsigned)((slice + bps - 1) / bps), (unsigned)a.pairs);
     if constexpr (WFMT == AIO_WFMT_BF16) {
-      if (np <= 8) return launch_spair_t<WFMT, EPI, 1, 3>(m, a);
-      if (np <= 16) return launch_spair_t<WFMT, EPI, 2, 3>(m, a);
-      if (np <= 24) return launch_spair_t<WFMT, EPI, 3, 2>(m, a);
+      if (a.np <= 8) return launch_spair_t<WFMT, EPI, 1, 3>(m, a);
+      if (a.np <= 16) return launch_spair_t<WFMT, EPI, 2, 3>(m, a);
+      if (a.np <= 24) return launch_spair_t<WFMT, EPI, 3, 2>(m, a);
       return launch_spair_t<WFMT, EPI, 4, 2>(m, a);
     } else {
-      if (np <= 16) return launch_spair_t<WFMT, EPI, 1, 3>(m, a);
+      if (a.np <= 16) return launch_spair_t<WFMT, EPI, 1, 3>(m, a);
       return launch_spair_t<WFMT, EPI, 2, 3>(m, a);
     }
   }
 }
 
-// Launch over `units` (of 128 weight rows) of the product.  The partial tiles
-// of a K split go to the scratch that is idle during this product (g.fix),
-// or to the workspace's region where that is larger.
+// Launch of product `which` of a chunk of g.R rows.  The partial sums of a K split
+// go to the scratch that is idle during this product (idle), or to the workspace's
+// region where that is larger.
 template <int WFMT, int EPI>
-hipError_t launch_pgemm_w(const aio_model& m, const PGemmArgs& g0, int units) {
+hipError_t launch_pgemm_w(const aio_model& m, const PGemmArgs& g0, int which, void* idle) {
+  const PfProduct p = pf_product(m.cfg, m.lay, which, g0.R);
+  const PfPlan plan = pf_plan(p, m.num_cus, m.lay.pcnt_n);
   PGemmArgs g = g0;
-  if (g.fix_bytes < m.lay.pfix_bytes) {
-    g.fix = m.at<float>(m.lay.pfix);
-    g.fix_bytes = m.lay.pfix_bytes;
-  }
+  g.N = p.N;
+  g.K = p.K;
+  g.ks = plan.ks;
+  g.fix = pf_idle_bytes(m.cfg, which, g.R) < m.lay.pfix_bytes ? m.at<float>(m.lay.pfix) : (float*)idle;
   g.tcnt = m.at<int>(m.lay.pcnt);
   g.err = m.at<int>(m.lay.sync) + kSyncErr;
-  const int pairs = EPI == PE_QKV ? g.N / 2 : g.N;
-  int np = 0, sks = 1;
-  if (EPI == PE_RESID ? g.R <= kSkRows : sk_pairs(m, g, pairs, &np, &sks))
-    return launch_sk<WFMT, EPI>(m, g, np, pairs, sks);
-  int shape = 0;
-  pf_choose(m, units, g.R, g.K, g.fix_bytes, &shape, &g.ks);
-  if (shape == 0) return launch_pgemm_t<WFMT, EPI, Big>(m, g, units);
-  if (shape == 1) return launch_pgemm_t<WFMT, EPI, Wide>(m, g, units);
-  return launch_pgemm_t<WFMT, EPI, Short>(m, g, units);
+  if (plan.kernel == kPfFewRows) return launch_sk<WFMT, EPI>(m, g, plan);
+  if (plan.kernel == 0) return launch_pgemm_t<WFMT, EPI, Big>(m, g, p.units);
+  if (plan.kernel == 1) return launch_pgemm_t<WFMT, EPI, Wide>(m, g, p.units);
+  return launch_pgemm_t<WFMT, EPI, Short>(m, g, p.units);
 }
 
 template <int EPI>
-hipError_t launch_pgemm(const aio_model& m, const PGemmArgs& g, int units) {
-  if (m.cfg.wfmt == AIO_WFMT_INT8) return launch_pgemm_w<AIO_WFMT_INT8, EPI>(m, g, units);
-  return launch_pgemm_w<AIO_WFMT_BF16, EPI>(m, g, units);
+hipError_t launch_pgemm(const aio_model& m, const PGemmArgs& g, int which, void* idle) {
+  if (m.cfg.wfmt == AIO_WFMT_INT8) return launch_pgemm_w<AIO_WFMT_INT8, EPI>(m, g, which, idle);
+  return launch_pgemm_w<AIO_WFMT_BF16, EPI>(m, g, which, idle);
 }
 
 template <int HD>
@@ -1786,6 +1834,20 @@ hipError_t launch_pattn_t(const aio_model& m, const PAttnArgs& t) {
 }
 
 }  // namespace
+
+int aio_prefill_plan(const aio_config* c, int rows, int num_cus, int32_t* out) {
+  const int rc = aio_check_config(c);
+  if (rc) return rc;
+  if (rows < 1 || num_cus < 1 || !out) return AIO_EINVAL;
+  const WsLayout lay = aio_ws_layout(*c);
+  for (int which = 0; which < 4; ++which) {
+    const PfPlan p = pf_plan(pf_product(*c, lay, which, rows), num_cus, lay.pcnt_n);
+    out[3 * which] = p.kernel;
+    out[3 * which + 1] = p.ks;
+    out[3 * which + 2] = p.np;
+  }
+  return AIO_OK;
+}
 
 size_t aio_prefill_row_bytes(const aio_config& c) {
   const size_t d = (size_t)c.d_model, Hd = (size_t)c.n_heads * c.head_dim, F = (size_t)c.ffn_dim;
@@ -1817,7 +1879,7 @@ PfBuffers aio_prefill_buffers(const aio_config& c, char* base, int rcap) {
 // K/V rows in every layer and b.x row R - 1 the last row's final residual.
 hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int R, int pos0) {
   const aio_config& c = m.cfg;
-  const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
+  const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim;
   const int nss = d / 64;
   hipError_t e;
   // layer 0's input rows: the embeddings, with x g and the sums of squares
@@ -1834,18 +1896,13 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     g.ss_in = b.ss; g.nss = nss; g.eps = c.rms_eps;
     g.w0 = L.wq; g.w1 = L.wk; g.w2 = L.wv;
     g.s0 = (const uint16_t*)L.sq; g.s1 = (const uint16_t*)L.sk; g.s2 = (const uint16_t*)L.sv;
-    g.N = (H + 2 * Hkv) * hd; g.K = d;
     g.out = b.q; g.ldo = H * hd;
     g.kc = m.kv_layer(l, 0); g.vc = m.kv_layer(l, 1);
     g.rope = m.rope; g.pos0 = pos0;
     g.H = H; g.Hkv = Hkv; g.hd = hd; g.max_ctx = c.max_ctx;
-    // partial tiles of a product split over K go to activations idle meanwhile
-    // (sized by R alone, so that the split, and with it the order of the
-    // sums, does not depend on how much scratch there is)
-    const size_t row4 = 4 * (size_t)R;
-    g.fix = b.actN; g.fix_bytes = row4 * (d + F);
-    const int qkv_tiles = hd == 128 ? H + 2 * Hkv : (H + 2 * Hkv + 1) / 2;
-    if ((e = launch_pgemm<PE_QKV>(m, g, qkv_tiles)) != hipSuccess) return e;
+    // (the last argument of a product: activations idle meanwhile, for the partial
+    // sums of a K split)
+    if ((e = launch_pgemm<PE_QKV>(m, g, PF_QKV, b.actN)) != hipSuccess) return e;
 
     PAttnArgs t{};
     t.q = b.q; t.ldq = H * hd;
@@ -1861,33 +1918,29 @@ hipError_t aio_launch_prefill_chunk(const aio_model& m, const PfBuffers& b, int 
     PGemmArgs o{};
     o.act = b.actA; o.lda = b.lda_a; o.R = R;
     o.w0 = L.wo; o.s0 = (const uint16_t*)L.so;
-    o.N = d; o.K = H * hd; o.out = b.x; o.ldo = d;
+    o.out = b.x; o.ldo = d;
     o.act_next = b.actN; o.lda_next = d;
     o.g_next = (const uint16_t*)L.ffn_norm; o.ss_out = b.ss; o.nss = nss;
-    o.fix = b.actB; o.fix_bytes = row4 * F;
-    if ((e = launch_pgemm<PE_RESID>(m, o, (d + kUnit - 1) / kUnit)) != hipSuccess) return e;
+    if ((e = launch_pgemm<PE_RESID>(m, o, PF_O, b.actB)) != hipSuccess) return e;
 
     PGemmArgs gu{};
     gu.act = b.actN; gu.lda = d; gu.R = R;
     gu.ss_in = b.ss; gu.nss = nss; gu.eps = c.rms_eps;
     gu.w0 = L.w_gate; gu.w1 = L.w_up;
     gu.s0 = (const uint16_t*)L.s_gate; gu.s1 = (const uint16_t*)L.s_up;
-    gu.N = F; gu.K = d;
-    gu.fix = b.q; gu.fix_bytes = row4 * (H * hd + std::max(d, H * hd));
     gu.act_out = b.actB; gu.lda_out = b.lda_b;
-    if ((e = launch_pgemm<PE_SWIGLU>(m, gu, (F + 63) / 64)) != hipSuccess) return e;
+    if ((e = launch_pgemm<PE_SWIGLU>(m, gu, PF_GU, b.q)) != hipSuccess) return e;
 
     PGemmArgs dn{};
     dn.act = b.actB; dn.lda = b.lda_b; dn.R = R;
     dn.w0 = L.w_down; dn.s0 = (const uint16_t*)L.s_down;
-    dn.N = d; dn.K = F; dn.out = b.x; dn.ldo = d;
-    dn.fix = b.q; dn.fix_bytes = row4 * H * hd;
+    dn.out = b.x; dn.ldo = d;
     if (!last) {
       dn.act_next = b.actA; dn.lda_next = b.lda_a;
       dn.g_next = (const uint16_t*)m.layers[(size_t)l + 1].attn_norm;
       dn.ss_out = b.ss; dn.nss = nss;
     }
-    if ((e = launch_pgemm<PE_RESID>(m, dn, (d + kUnit - 1) / kUnit)) != hipSuccess) return e;
+    if ((e = launch_pgemm<PE_RESID>(m, dn, PF_DOWN, b.q)) != hipSuccess) return e;
   }
   return hipSuccess;
 }

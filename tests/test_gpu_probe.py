@@ -25,7 +25,7 @@ CASES = {
     "n10": (dict(), 0, 10),
     "n23": (dict(), 0, 23),
     "n128": (dict(), 0, 128),
-    # the full 2K-token request of the routing rule, several 64-row tiles
+    # the full 2K-token request of the routing rule, in tiles of 64 and 32 rows
     "n2048": (dict(prompt_len=2048, n_steps=8), 0, 2048),
     # a prompt that continues a cache already holding 37 positions
     "after37": (dict(), 37, 90),
@@ -34,16 +34,15 @@ CASES = {
     # head_dim 128 with 4 query heads per kv head
     "hd128_gqa4": (dict(n_heads=4, n_kv_heads=1, head_dim=128), 0, 100),
     "int8": (dict(wfmt="int8"), 0, 23),
-    # d 1024, FFN 4096: at a short prompt every product (QKV and gate/up as
-    # well as O and down) has fewer tiles than two per CU and splits K over
-    # workgroups, the last slice adding the partial tiles in slice order
+    # d 1024, FFN 4096: 23 rows take the few-row products, all four with K
+    # split over workgroups; 70 rows take tiles, QKV, O and down split.  The
+    # last slice to arrive adds the partial sums in slice order
     "split_k": (dict(d_model=1024, ffn_dim=4096, n_heads=8, n_kv_heads=8, head_dim=128), 0, 23),
     "split_k_int8": (dict(d_model=1024, ffn_dim=4096, n_heads=8, n_kv_heads=8, head_dim=128,
                           wfmt="int8"), 0, 70),
-    # 1100 prompt rows (18 tiles of 64): 256-row weight tiles of 8 waves; K
-    # split in two for O and down, while QKV (216 workgroups) and gate/up
-    # (576) run unsplit in the XCD-renumbered order, whose last band holds 2
-    # of the 18 row tiles; attention gives each XCD one of the 8 heads
+    # 1100 prompt rows: QKV and gate/up in 18 row tiles of 64, unsplit in the
+    # XCD-renumbered order, whose last band holds 2 of them; O in tiles of 32
+    # rows, down split in two; attention gives each XCD one of the 8 heads
     "wide_tiles": (dict(d_model=1024, ffn_dim=4096, n_heads=8, n_kv_heads=8, head_dim=128,
                         prompt_len=1100), 0, 1100),
     # 16 query heads on 8 kv heads (G = 2), hd 64: attention gives each XCD
@@ -67,6 +66,12 @@ def test_prefill_matches_sequential_oracle(name):
         pair.gpu.sync()
         got = pair.logits[0].cpu().numpy().copy()
         kg = pair.gpu.kv_rows(before, before + n)
+        # again, and again: the slices of a split product arrive in any order
+        for _ in range(2):
+            pair.gpu.prefill(toks[before:], before, pair.logits)
+            pair.gpu.sync()
+            assert np.array_equal(got.view(np.uint32), pair.logits[0].cpu().numpy().view(np.uint32))
+            assert np.array_equal(kg, pair.gpu.kv_rows(before, before + n))
         free = pair.kv_host.copy()
         ref = ref_free = None
         need = np.zeros(cfg.n_layers)
@@ -105,7 +110,8 @@ def test_prefill_matches_sequential_oracle(name):
 
 
 def test_prefill_repeats_bit_for_bit():
-    """The same prefill twice: identical logits and cache rows (no atomics)."""
+    """The same prefill twice: identical logits and cache rows (the counters of
+    split products decide who adds the slices, not their order)."""
     cfg = TINY.with_(name="pf_repeat")
     pair = Pair(cfg, with_oracle=False)
     try:
