@@ -340,7 +340,7 @@ int aio_prefill(aio_model* m, const int32_t* tokens, int32_t n, int32_t pos, flo
  * of library-allocated memory.  It calls no hipMalloc, hipFree or other
  * allocating routine.  The prompt goes through in passes of at most
  * aio_prefill_noalloc_rows(cfg) rows (the array divided by the scratch of
- * one row: 4 (1 + d + H hd + max(d, H hd) + F) bytes, and at most 2048),
+ * one row: 4 (1 + 2 d + H hd + max(d, H hd) + F) + d / 16 bytes, at most 2048),
  * so any n works; results equal aio_prefill's up to rounding (bit-identical
  * where both take the prompt in one pass; a prompt of at most max_verify
  * tokens takes aio_prefill's verify route and needs none of the array).

@@ -67,6 +67,9 @@ constexpr int kVerifyMaxKs = 8;
 // tile pair; each has its slot of partial sums in skpart.
 constexpr int kVerifySkMaxC = 8;
 
+// Key blocks of 32 per split of the verify attention (one per wave).
+constexpr int kVattnBlocksPerSplit = 8;
+
 WsLayout aio_ws_layout(const aio_config& c);
 
 struct aio_model {

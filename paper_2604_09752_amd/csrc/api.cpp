@@ -84,8 +84,9 @@ WsLayout aio_ws_layout(const aio_config& c) {
   const size_t MV = (size_t)c.max_verify, d = (size_t)c.d_model, F = (size_t)c.ffn_dim;
   const size_t Hd = (size_t)c.n_heads * (size_t)c.head_dim;
   L.splits = choose_splits(c);
-  // verify attention: at least 4 key blocks of 32 per split, at most 64 splits
-  L.vsplits = (int)std::min<size_t>(64, std::max<size_t>(1, ((size_t)c.max_ctx + 127) / 128));
+  // verify attention: splits of kVattnBlocksPerSplit blocks of 32 keys, at most 64
+  constexpr size_t kSplitKeys = 32 * kVattnBlocksPerSplit;
+  L.vsplits = (int)std::min<size_t>(64, ((size_t)c.max_ctx + kSplitKeys - 1) / kSplitKeys);
   const size_t SP = (size_t)std::max(L.splits, L.vsplits);
   size_t ka = d > Hd ? d : Hd;
   if (F > ka) ka = F;
@@ -106,9 +107,10 @@ WsLayout aio_ws_layout(const aio_config& c) {
   L.skpart = off;
   off = align256(off + L.sk_tiles * kVerifySkMaxC * AIO_MAX_VERIFY_ROWS * 64 * 4);
   L.skcnt = off; off = align256(off + L.sk_tiles * 4);
-  // prefill K split (products with fewer tiles than two per CU): room for
-  // 512 partial tiles of 128 x 64 fp32 and 1024 tile counters
-  L.pfix_bytes = (size_t)512 * 128 * 64 * 4;
+  // prefill K split: room for the partial sums of the slices where the idle
+  // activations of a short chunk hold less (16 MB: 128 Big, 256 Wide or 1024 Short
+  // tiles), and 1024 tile counters
+  L.pfix_bytes = (size_t)16 << 20;
   L.pfix = off; off = align256(off + L.pfix_bytes);
   L.pcnt_n = 1024;
   L.pcnt = off; off = align256(off + L.pcnt_n * 4);
@@ -647,7 +649,7 @@ static hipError_t enqueue_status_copy(const aio_model* m, unsigned* word) {
 // ---------------------------------------------------- the probe's front end
 
 // Rows of one prefill chunk when the library sizes the scratch: the whole
-// prompt up to this many rows, in multiples of the GEMM's 64-row tiles.
+// prompt up to this many rows, in steps of 64.
 constexpr int kPrefillChunk = 2048;
 
 // Checks shared by the prefill entry points.
@@ -683,12 +685,13 @@ static hipError_t enqueue_prefill(aio_model* m, const PfBuffers& b, const int32_
 }
 
 // A prompt of at most max_verify tokens goes through the verify forward
-// (skinny products over the weights once): at the 1B, 10 tokens take 1.5
-// against 3.7 ms in prompt-length products, whose tiles are 64 rows.
+// (skinny products over the weights once, whose activations are split once by
+// their producer).  Against the few-row products of prefill, us: 7B 2 tokens 3024 /
+// 3616, 10 tokens 3384 / 3701; 1B 1139 / 1194, 1347 / 1277 (the only loss).
 static bool prefill_as_verify(const aio_model* m, int32_t n) { return n <= m->cfg.max_verify; }
 
-// A single token is one decode step (the persistent kernel: 0.80 against
-// 1.25 ms for the 1B in the verify forward).
+// A single token is one decode step (the persistent kernel: 0.8 against 1.1 ms
+// and more for the 1B in the verify forward).
 static hipError_t enqueue_prefill_as_verify(aio_model* m, const int32_t* tokens, int32_t n,
                                             int32_t pos, float* logits_dev) {
   if (n == 1) {

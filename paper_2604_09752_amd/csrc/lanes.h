@@ -1,5 +1,5 @@
-// Lane exchanges and division helpers of the verify and prefill kernels (the
-// step kernel does not use them).
+// Lane exchanges, division and device-coherent access of the verify and prefill
+// kernels (the step kernel does not use them).
 #pragma once
 
 #include "common.h"
@@ -43,3 +43,29 @@ AIO_DEV uint2 lds_read_tr16(const void* p) {
       (__attribute__((address_space(3))) i16x4*)p);
   return __builtin_bit_cast(uint2, v);
 }
+
+// Device-coherent access for sums that workgroups hand to one another (K slices,
+// attention splits): written through to memory and read past the (per-XCD) L2, so
+// the hand-over needs no fence that writes back or drops a whole L2 (with fences, it
+// cost about 40 us per product).  The arrival counters are vector atomics at device
+// scope.
+AIO_DEV void st_agent(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+AIO_DEV float ld_agent(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+AIO_DEV int atomic_add_agent(int* p, int v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+AIO_DEV int atomic_load_agent(const int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+AIO_DEV void atomic_store_agent(int* p, int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Wait for this wave's LDS operations; also a compiler barrier, so no LDS access
+// moves across it.  Lanes of one wave exchange data through LDS without a workgroup
+// barrier (the waves of a workgroup run different numbers of iterations).
+AIO_DEV void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }

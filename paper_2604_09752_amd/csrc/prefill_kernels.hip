@@ -39,8 +39,6 @@ AIO_DEV f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-AIO_DEV bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
-
 // Terms of the activation split.
 constexpr int kNT = 3;
 
@@ -62,31 +60,6 @@ AIO_DEV void split3t(uint32_t a, uint32_t (&t)[kNT]) {
 AIO_DEV uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
 }
-
-// Device-coherent access for the K slices of a split product: the partials
-// are written through to memory and read past the (per-XCD) L2, and the
-// slice counters are vector atomics at device scope.
-AIO_DEV void st_agent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV float ld_agent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV int atomic_add_agent(int* p, int v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV int atomic_load_agent(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV void atomic_store_agent(int* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Wait for this wave's LDS operations; also a compiler barrier, so no LDS
-// access moves across it.  Lanes of one wave exchange data through LDS
-// without a workgroup barrier (the waves of a workgroup run different
-// numbers of iterations).
-AIO_DEV void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // ------------------------------------------------------------- RMSNorm rows
 
@@ -438,16 +411,16 @@ AIO_DEV void scale4(const uint16_t* s, float (&f)[4]) {
   f[3] = fp16_to_f32((uint16_t)(u.y >> 16));
 }
 
-// Epilogue of a wave: its 64 weight rows (the 32-row blocks slo and shi, both
-// whole or both past the end) by its PB blocks of 16 prompt rows from row
+// Epilogue of a wave: its 64 weight rows (the 32-row block slo and the one after
+// it, both whole or both past the end) by its PB blocks of 16 prompt rows from row
 // rw0.  Lane (c16, g) holds, for prompt row rw0 + 16 p + c16, rows 16 m + 4 g
 // .. + 3 of the 64 in y[p][m].  inv: the norm factors of the wave's prompt
 // rows (QKV and SWIGLU).  Everything it reads is requested before the first
 // store (a load after a store that may alias it would wait its own round
 // trip: 16 of them in turn in a residual tile).
 template <int WFMT, int EPI, int PB>
-AIO_DEV void pgemm_epi(const PGemmArgs& a, const BlockSrc& slo, const BlockSrc& shi, int rw0,
-                       int c16, int g, const float* inv, const f32x4 (&y)[PB][kMB]) {
+AIO_DEV void pgemm_epi(const PGemmArgs& a, const BlockSrc& slo, int rw0, int c16, int g,
+                       const float* inv, const f32x4 (&y)[PB][kMB]) {
   if (!slo.valid) return;
   if constexpr (EPI == PE_RESID) {
     float4 xv[PB][kMB];
@@ -877,8 +850,7 @@ __global__ __launch_bounds__(Tl::GT, 2) void k_pgemm(PGemmArgs a) {
 
   const int blk = 2 * wn;  // the wave's first block of 32 weight rows in the tile
   const BlockSrc slo = block_src<EPI>(a, Tl::UPT * bx + (blk >> 2), blk & 3);
-  const BlockSrc shi = block_src<EPI>(a, Tl::UPT * bx + (blk >> 2), (blk & 3) + 1);
-  pgemm_epi<WFMT, EPI, PB>(a, slo, shi, r0 + wr * PB * 16, c16, g,
+  pgemm_epi<WFMT, EPI, PB>(a, slo, r0 + wr * PB * 16, c16, g,
                            EPI == PE_RESID ? nullptr : inv_rows + wr * PB * 16, hi);
 }
 
@@ -1173,18 +1145,18 @@ __global__ __launch_bounds__(kAW * AIO_WAVE, 2) void k_pattn(PAttnArgs a) {
 // ------------------------------------------- products of a few prompt rows
 
 // Products of at most kSkRows prompt rows.  The tiles of k_pgemm leave such a
-// product to 128 or 176 workgroups, and a CU streams no more than about 30
-// bytes per ns, so its weights should come in equal shares through all of
-// them: a workgroup owns np row pairs (k_spair) or 64 rows and a K slice
-// (k_sresid) and passes its weights through LDS in stages of 256 k.  Wave w
+// product to few workgroups (the 1B's 128 or 176), and a CU streams no more than
+// about 30 bytes per ns of weights from memory, so they should come in equal shares
+// through all of them: a workgroup owns np row pairs (k_spair) or 64 rows and a K
+// slice (k_sresid) and passes its weights through LDS in stages of 256 k.  Wave w
 // multiplies 32-k block w of every stage by all prompt rows: lane rl of a half
-// wave reads prompt row rl's 16 activations of the block from memory and
-// splits them, and the three terms are three products into 32x32 tiles, hi
-// (first terms) and lo.  The waves' tiles meet in LDS.  What bounds it is the
-// bytes through each CU, some 45 per ns with the activations (every workgroup
-// reads those of its K slice).  23 rows of the 1B, in us, Short tiles of k_pgemm
-// before and now: QKV 19.5 -> 12.6, O 15.7 -> 10.4, gate/up 20.0 -> 18.0, down
-// 21.5 -> 13.7.
+// wave reads prompt row rl's 16 activations of the block from memory and splits
+// them, and the three terms are three products into 32x32 tiles, hi (first terms)
+// and lo.  The waves' tiles meet in LDS.  What bounds it is the bytes through each
+// CU, weights and activations together some 45 per ns (every workgroup reads the
+// activations of its K slice, which come from a cache).  23 rows of the 1B, in us,
+// Short tiles of k_pgemm before and now: QKV 19.5 -> 12.6, O 15.7 -> 10.4, gate/up
+// 20.0 -> 18.0, down 21.5 -> 13.7.
 constexpr int kSkRows = 32;
 
 struct SkArgs {
@@ -1590,10 +1562,10 @@ hipError_t launch_pnorm(const aio_model& m, const PfBuffers& b, int R, const uin
 // round of workgroups `round` plus, per 32 k of its K slice, `few` (at most
 // half the CUs busy) or `full`; `base` once; a K split `split` plus
 // `slice` per slice (scaled by the live share of the tile's prompt rows).
-// Fitted to the 1B's and the 7B's four products at 19 prompt lengths from 23
-// to 2048, every shape and split measured by kernel trace (the model is
+// Fitted to the 1B's and the 7B's four products (bf16) at 19 prompt lengths from
+// 23 to 2048, every shape and split measured by kernel trace (the model is
 // within 4 to 10 % of them, and the shape it picks within 1.8 % of the best
-// one on average, 13 % at worst):
+// one on average, 13 % at worst); int8 takes the same constants unfitted:
 //   Big    one workgroup per CU; the fewest bytes and LDS reads per product
 //          (2048 rows, 1B: QKV 86 against Wide's 105 us, gate/up 226 / 264)
 //   Wide   half the prompt rows: twice the workgroups where Big leaves CUs

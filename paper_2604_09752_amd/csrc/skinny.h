@@ -16,6 +16,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(1))) const u32x4 gl_u32x4;
 
+AIO_DEV bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
+
 // 16-byte loads through a global-address-space pointer.  Selected from a
 // table the pointer's address space is unknown, and a flat load also counts
 // against the LDS wait counter: every LDS wait would then wait for the
@@ -55,7 +57,6 @@ struct VStage {
   static constexpr int NLD = 64 * CPR / kGBlock;                     // loads per thread
   static constexpr int BPS = KC / 32;                                // 32-k blocks per stage
   static constexpr int BPW = BPS / kGWaves;                          // blocks per wave
-  static constexpr int BYTES = 64 * RS;
 };
 
 // Two bf16x8 MFMA fragments of one staged row for the wave's block of 32 k

@@ -70,9 +70,9 @@ namespace {
 // that the compiler cannot see through, so that it loads the few it needs
 // (scalar loads) instead of keeping all of them over the whole kernel, where
 // they were spilled to vector register lanes and read back one by one in every
-// phase (some 400 spilled scalars; now 8, and no scratch memory.  Tiny decoder
-// 67.5 -> 64.2 us per token, 1B at 2K 734 -> 712, 7B 2278 -> 2258, int8 1599 ->
-// 1575).
+// phase (some 400 spilled scalars; now 8 to 28 by instantiation, 8 in most, and no
+// scratch memory.  Tiny decoder 67.5 -> 64.2 us per token, 1B at 2K 734 -> 712, 7B
+// 2278 -> 2258, int8 1599 -> 1575).
 typedef __attribute__((address_space(4))) const MegaArgs CArgs;
 AIO_DEV CArgs& step_args() {
   uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
@@ -966,9 +966,10 @@ AIO_DEV void gemv_phase(int layer, int pos, int token, Bufs& W, float* lds,
   // loads in flight behind each buffer on every path.
   // O has one batch where its rows are few (2048 inputs and rows, or int8
   // 4096): then only that one is waited for and multiplied.  The other phases
-  // have this path in small models only (ONE: the tiny decoder 64.3 -> 60.1 us
-  // per token); in the larger ones it cost 1 to 2 % and is never taken, as did a
-  // test per batch in the last round.
+  // have this path only in models with at most 4096 down inputs (ONE: the tiny
+  // decoder 64.3 -> 60.1 us per token).  In the 1B and the 7B, which would never
+  // take it, it cost 1 to 2 %, as did a test per batch in the last round; models
+  // between them whose phases have one batch multiply a masked second one.
   if (kMaybeOne && nb <= 1) {
     compute<WFMT, KIND, VPL>(P, 0, W.b[0], h, red, T);
   } else {
@@ -1480,7 +1481,8 @@ __global__ __launch_bounds__(kT, 1) void k_step(MegaArgs) {
   // worth more (8 tokens of the 1B at 2K 5715 -> 5556 us, one at 128 669 -> 632, 4 of
   // the int8 7B at 2K 6299 -> 6143), with many the stream (7B bf16 9052 -> 9137):
   // late for int8 and for down projections of at most 8192 bf16 inputs (VD up
-  // to 2).
+  // to 2).  Measured on the tiny decoder, the 1B and the 7B: the line tells these
+  // apart, and stands in for the bytes of all five phases in other models.
   constexpr bool LATE = WFMT == AIO_WFMT_INT8 || VD < 3;
   constexpr bool ONE = VD == 1;  // at most 4096 down inputs
   CArgs& a = step_args();

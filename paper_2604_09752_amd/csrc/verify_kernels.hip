@@ -48,23 +48,6 @@ constexpr int kMaxRows = AIO_MAX_VERIFY_ROWS;
 // order on both sides (256: one attention split, a key block per wave).
 constexpr int kOrderKeys = 256;
 
-// Device-coherent access for the slices of a split residual product: the
-// parts are written through to memory and read past the (per-XCD) L2, so
-// handing them over needs no fence that writes back or drops a whole L2
-// (with fences, the hand-over cost about 40 us per product).
-AIO_DEV int atomic_add_agent(int* p, int v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV void atomic_store_agent(int* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV void st_agent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-AIO_DEV float ld_agent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_STORE = 3 };
 
 // Exact three-term bf16 split of an fp32 value.
@@ -429,31 +412,23 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   };
   if (nst > 0) {
-    uint4 R0[St::NLD], R1[St::NLD], R2[St::NLD];
-    uint4 A0[BPW][2], A1[BPW][2], A2[BPW][2];
+    static_assert(kVNB == 2, "two register sets");
+    uint4 R0[St::NLD], R1[St::NLD];
+    uint4 A0[BPW][2], A1[BPW][2];
     gload_w(R0, 0);
     gload_a(A0, 0);
     gload_w(R1, 1);
     gload_a(A1, 1);
-    if (kVNB > 2) {
-      gload_w(R2, 2);
-      gload_a(A2, 2);
-    }
     int st = 0;
     for (; st + kVNB < nst; st += kVNB) {
       step(R0, A0, st);
       step(R1, A1, st + 1);
-      if (kVNB > 2) step(R2, A2, st + 2);
     }
     stage(R0);
     product(st, A0);
     if (st + 1 < nst) {
       stage(R1);
       product(st + 1, A1);
-    }
-    if (kVNB > 2 && st + 2 < nst) {
-      stage(R2);
-      product(st + 2, A2);
     }
   }
   __syncthreads();  // the stage buffer becomes the partial-tile buffer
@@ -970,7 +945,7 @@ struct VAttnArgs {
 // positions there is one split with a block per wave, and the fold's order is the
 // only one: results there do not depend on how longer contexts are split.
 constexpr int kVAW = 8;
-constexpr int kVattnBlocksPerSplit = kVAW;
+static_assert(kVattnBlocksPerSplit == kVAW, "a key block per wave");
 
 template <int HD>
 struct VAttnLds {
@@ -990,11 +965,6 @@ struct VAttnLds {
 AIO_DEV int vattn_key(int g, int j) { return 16 * (j >> 2) + 4 * g + (j & 3); }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-AIO_DEV bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
-
-// Wait for this wave's LDS operations (also a compiler barrier for LDS).
-AIO_DEV void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // Block kb's key fragments (A operand of tile tt: key row 16 tt + l % 16,
 // dims 32 c + 8 (l / 16) ..) and value chunks (16 bytes each, row-major);

@@ -18,12 +18,12 @@ CASES = {
     "hd128_gqa4": dict(n_heads=4, n_kv_heads=1, head_dim=128),
     "ragged": dict(d_model=320, ffn_dim=192, vocab=1000, n_heads=5, n_kv_heads=5),
     "int8": dict(wfmt="int8"),
-    # caches beyond 8K positions take the attention shape with two row
-    # groups, and 128 splits per head leave most splits empty
+    # a cache with room for 8K positions, few of them filled: the workspace
+    # holds more splits than the attention takes
     "long_cache": dict(max_ctx=8256),
     "long_cache_hd128": dict(n_heads=4, n_kv_heads=1, head_dim=128, max_ctx=8256),
     # O (K = 1024) and down (K = 4096) products split over K, their slices
-    # added in order by the next RMSNorm
+    # added in order by the last one to finish
     "split_k": dict(n_heads=16, n_kv_heads=4, ffn_dim=4096),
     # d 576: three 256-k stages per tile pair, the last one ragged; the
     # gate/up product deals out (tile pair, stage) units two per workgroup,
