@@ -44,8 +44,9 @@ constexpr int kMaxRows = AIO_MAX_VERIFY_ROWS;
 // cache rows of a 7B verify of 4 rows at position 17 up to 1.1e-3 apart (each as
 // far from a 64-bit evaluation), 7e-4 at 40, 2.5e-4 at 400 and 2048.  So gate/up
 // runs in the order of k_vgemm_sk up to here, some 4 us per layer of a 7B slower
-// than k_vpair, which takes it beyond; every other kernel of a verify has the same
-// order on both sides (256: one attention split, a key block per wave).
+// than k_vpair, which takes it beyond; QKV keeps its workgroups inside blocks of 32
+// pairs, and a single attention split folds its waves one by one (256: one split, a
+// key block per wave).  The other kernels have one order at any length.
 constexpr int kOrderKeys = 256;
 
 enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_STORE = 3 };
@@ -512,20 +513,18 @@ __global__ __launch_bounds__(kGBlock) void k_vgemm(VGemmArgs a) {
   }
 }
 
-// The QKV product and, behind all but a short cache, gate/up: outputs in pairs of
-// weight rows (QKV: rows ii and ii + hd / 2 of a head section, SWIGLU: the same row
-// of gate and up).  Workgroup b owns the np pairs from np b.
-//   SWIGLU: as many as spread the product evenly over the CUs, up to 64, so every
-// CU streams the same bytes in one workgroup.  Measured (7B: 9 rows at 2048, 1B: 3
-// rows at 1531), in us, against k_vgemm_sk: 7B bf16 (43 pairs) 38.2 -> 34.0, int8
-// 27.0 -> 23.3, 1B (22 pairs) 15.3 -> 11.1.  Other np (22 to 64) were within 3 %
-// or slower.
-//   QKV: a power of two up to 32, the least that covers the product in one round,
-// so that a workgroup lies in one block of 32 pairs and takes the K stages in the
-// order that belongs to that block: the sums are the same whatever np.  1B (8
-// pairs) 10.8 -> 7.7 us against 32 pairs on 64 CUs.  The 7B's 192 workgroups of 32
-// pairs stream at the rate HBM gives (24 pairs on 256 CUs: bf16 22.3 -> 23.2,
-// int8 16.6 -> 16.2).
+// The QKV product and, behind all but a short cache (kOrderKeys), gate/up: outputs
+// in pairs of weight rows (QKV: rows ii and ii + hd / 2 of a head section, SWIGLU:
+// the same row of gate and up).  Workgroup b owns the np pairs from np b: as many
+// as spread the product evenly over the CUs, up to 64, so every CU streams the same
+// bytes in one workgroup.  Measured (7B: 9 rows at 2048, 1B: 3 rows at 1531), in us:
+// gate/up against k_vgemm_sk 7B bf16 (43 pairs) 38.2 -> 34.0, int8 27.0 -> 23.3, 1B
+// (22 pairs) 15.3 -> 11.1; QKV of the 1B (8 pairs; 32 before, on 64 CUs) 10.8 ->
+// 7.7.  Other np (22 to 64) were within 3 % or slower.
+//   QKV starts its K stages by the block of 32 pairs that a workgroup begins in (7B
+// bf16, 24 pairs: 20.1 us; by its own index 22.5).  Behind a short cache it takes a
+// power of two of pairs, at most 32, and so lies in one block: the sums are the same
+// whatever np (32 pairs in place of 24 on the 7B: bf16 23.0 us, int8 16.4 for 15.6).
 //
 // As in k_vgemm, the weights pass through LDS in stages of 256 k, with NS
 // stages in flight in registers, and wave w multiplies 32-k block w of every
@@ -942,8 +941,7 @@ struct VAttnArgs {
 // the kernel's critical path, about 2 us each at 2K context.  With the
 // weights of the fold computed per wave and a merge of one round trip: 7B, 9
 // rows at 2048, 17.5 -> 15.1 us, 1B, 3 rows at 1531, 13.2 -> 10.7.  Up to 256
-// positions there is one split with a block per wave, and the fold's order is the
-// only one: results there do not depend on how longer contexts are split.
+// positions there is one split with a block per wave.
 constexpr int kVAW = 8;
 static_assert(kVattnBlocksPerSplit == kVAW, "a key block per wave");
 
@@ -991,13 +989,13 @@ AIO_DEV void vattn_load(const uint16_t* kbase, const uint16_t* vbase, int kb, in
 // Merge of head h's S <= 64 splits for the M rows (by the split that finished
 // last; the others' states are in memory, read past the caches).  The splits'
 // (max, sum) pairs of a row, one per lane (of 8 lanes up to eight splits, else
-// of a wave), become their weights 2^(m - max m) and the row's sum; every output
-// element adds its splits' outputs with them, in split order, and divides by the
-// sum (a single split's weight is 1, its output exact).  The outputs of the
+// of a wave), become their weights 2^(m - max m) / sum; every output element
+// adds its splits' outputs with them, in split order (a single split's is divided
+// by its sum).  The outputs of the
 // first eight splits are requested with the pairs, so up to eight splits take
 // one round trip.
 template <int HD>
-AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64], float* sums) {
+AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64]) {
   constexpr int NT = kVAW * AIO_WAVE, NI = (kMaxRows * HD + NT - 1) / NT;
   const int M = a.M, S = a.S, tid = threadIdx.x, lane = tid & (AIO_WAVE - 1), wid = tid / AIO_WAVE;
   const bool few = S <= 8;
@@ -1025,8 +1023,7 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64], float* sum
     const float mx = group_max8_dpp(m);
     const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
     const float l = group_sum_dpp<8>((tid & 7) < S ? w * lv[0] : 0.f);
-    if (tid < 8 * M) wts[tid / 8][tid & 7] = w;
-    if (tid < 8 * M && (tid & 7) == 0) sums[tid / 8] = l;
+    if (tid < 8 * M) wts[tid / 8][tid & 7] = S == 1 ? l : (l > 0.f ? w / l : 0.f);
   } else {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -1035,8 +1032,7 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64], float* sum
       const float mx = wave_max(m);
       const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mx);
       const float l = wave_sum(lane < S ? w * lv[q] : 0.f);
-      if (r < M) wts[r][lane] = w;
-      if (r < M && lane == 0) sums[r] = l;
+      if (r < M) wts[r][lane] = l > 0.f ? w / l : 0.f;
     }
   }
   __syncthreads();
@@ -1045,9 +1041,14 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64], float* sum
     const int e = tid + i * NT, r = e / HD, dim = e % HD;
     if (e >= M * HD) break;
     float o = 0.f;
+    if (S == 1) {
+      const float l = wts[r][0];
+      o = l > 0.f ? ov[i][0] / l : 0.f;
+    } else {
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (j < S) o += ov[i][j] * wts[r][j];
+      for (int j = 0; j < 8; ++j)
+        if (j < S) o += ov[i][j] * wts[r][j];
+    }
     for (int s0 = 8; s0 < S; s0 += 8) {
       float x[8];
 #pragma unroll
@@ -1056,8 +1057,7 @@ AIO_DEV void vattn_merge(const VAttnArgs& a, int h, float (*wts)[64], float* sum
       for (int j = 0; j < 8; ++j)
         if (s0 + j < S) o += x[j] * wts[r][s0 + j];
     }
-    const float l = sums[r];
-    store_split(a.act, a.lda, M, r, h * HD + dim, l > 0.f ? o / l : 0.f);
+    store_split(a.act, a.lda, M, r, h * HD + dim, o);
   }
 }
 
@@ -1264,51 +1264,66 @@ __global__ __launch_bounds__(kVAW * AIO_WAVE, 1) void k_vattn_mma(VAttnArgs a) {
   __syncthreads();
 
   // The split's state of its M rows, written through to memory: (max, sum) in
-  // log2 units and the unnormalized output, the waves' folded in wave order, each
-  // step weighting the state so far by c1 and the wave's by c2 (2^ their maxima
-  // minus the new maximum).  Thread 8 r + w computes step w of row r.
+  // log2 units and the unnormalized output.  Thread 8 r + w gives wave w's weight
+  // in row r: 2^(m - max m), with which the waves' outputs are added in wave order;
+  // or, for a single split, the two weights of step w of folding them one by one
+  // (the state so far by c1, the wave's by c2: 2^ their maxima minus the new
+  // maximum), the order that results behind a short cache keep to (for 9 rows of
+  // the 7B at 2048 it took 15.7 us, the sum 15.3).
   static_assert(kVAW == 8, "a group of 8 lanes holds a row's waves");
   __shared__ float wts[kMaxRows][64];
+  const bool chain = a.S == 1;
   if (tid < 8 * kMaxRows) {
     const int r = tid / 8, w = tid & 7;
-    float before = -INFINITY, after = -INFINITY, mw = -INFINITY;
+    const float mw = r < M ? mm[w * kMaxRows + r] : -INFINITY;
+    if (chain) {
+      float before = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kVAW; ++j) {
-      const float mj = r < M ? mm[j * kMaxRows + r] : -INFINITY;
-      if (j < w) before = fmaxf(before, mj);
-      if (j <= w) after = fmaxf(after, mj);
-      if (j == w) mw = mj;
+      for (int j = 0; j < kVAW - 1; ++j)
+        if (j < w && r < M) before = fmaxf(before, mm[j * kMaxRows + r]);
+      const float after = fmaxf(before, mw);
+      wts[r][2 * w] = before == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(before - after);
+      wts[r][2 * w + 1] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - after);
+      if (w == kVAW - 1 && r < M) st_agent(a.part_ml + ((size_t)r * a.H + h) * 2, after);
+    } else {
+      const float ms = group_max8_dpp(mw);
+      const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - ms);
+      const float ls = group_sum_dpp<8>(r < M ? wt * ll[w * kMaxRows + r] : 0.f);
+      wts[r][w] = wt;
+      if (w == 0 && r < M) {
+        float* ml = a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2;
+        st_agent(ml, ms);
+        st_agent(ml + 1, ls);
+      }
     }
-    wts[r][2 * w] = before == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(before - after);
-    wts[r][2 * w + 1] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - after);
-    if (w == kVAW - 1 && r < M) st_agent(a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2, after);
   }
   __syncthreads();
   for (int e = tid; e < M * HD; e += NT) {
     const int r = e / HD, dim = e % HD;
     float os = 0.f;
-#pragma unroll
-    for (int w = 0; w < kVAW; ++w)
-      os = fmaf(os, wts[r][2 * w], om[(w * kMaxRows + r) * Lds::OROW + dim] * wts[r][2 * w + 1]);
-    st_agent(a.part_o + (((size_t)r * a.H + h) * a.S + s) * HD + dim, os);
-    if (dim == 0) {
+    if (chain) {
       float ls = 0.f;
 #pragma unroll
-      for (int w = 0; w < kVAW; ++w)
+      for (int w = 0; w < kVAW; ++w) {
+        os = fmaf(os, wts[r][2 * w], om[(w * kMaxRows + r) * Lds::OROW + dim] * wts[r][2 * w + 1]);
         ls = fmaf(ls, wts[r][2 * w], ll[w * kMaxRows + r] * wts[r][2 * w + 1]);
-      st_agent(a.part_ml + (((size_t)r * a.H + h) * a.S + s) * 2 + 1, ls);
+      }
+      if (dim == 0) st_agent(a.part_ml + ((size_t)r * a.H + h) * 2 + 1, ls);
+    } else {
+#pragma unroll
+      for (int w = 0; w < kVAW; ++w) os += wts[r][w] * om[(w * kMaxRows + r) * Lds::OROW + dim];
     }
+    st_agent(a.part_o + (((size_t)r * a.H + h) * a.S + s) * HD + dim, os);
   }
   // count the split; the last of head h's splits to arrive merges them
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  __shared__ float sums[kMaxRows];
   __shared__ int last_s;
   if (tid == 0) last_s = atomic_add_agent(a.cnt + h, 1) == a.S - 1;
   __syncthreads();
   if (!last_s) return;
   if (tid == 0) atomic_store_agent(a.cnt + h, 0);  // ready for the next layer
-  vattn_merge<HD>(a, h, wts, sums);
+  vattn_merge<HD>(a, h, wts);
 }
 
 // Launch with `blocks` tile pairs.  A residual-add product with fewer tile
@@ -1361,11 +1376,11 @@ hipError_t launch_vpair_t(const aio_model& m, const VGemmArgs& a) {
   return hipGetLastError();
 }
 
-// Launch of a product of `pairs` row pairs (k_vpair).  SWIGLU: in as few rounds of
-// one workgroup per CU as workgroups of at most 64 pairs allow, each round full.
-// QKV: the least power of two of pairs that takes one round, at most 32.  The load
-// slots of a workgroup (16 rows of bf16, 32 of int8) round its pairs up; few of
-// them leave registers for more stages in flight.
+// Launch of a product of `pairs` row pairs (k_vpair), in as few rounds of one
+// workgroup per CU as workgroups of at most 64 pairs allow, each round full; QKV
+// behind a short cache takes the least power of two of pairs that makes one round,
+// at most 32.  The load slots of a workgroup (16 rows of bf16, 32 of int8) round
+// its pairs up; few of them leave registers for more stages in flight.
 template <int EPI>
 hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   VGemmArgs a = g;
@@ -1374,7 +1389,7 @@ hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   a.eps = m.cfg.rms_eps;
   a.ss_in = m.at<float>(m.lay.vss);
   a.pairs = pairs;
-  if (EPI == EPI_QKV) {
+  if (EPI == EPI_QKV && g.pos + g.M <= kOrderKeys) {
     a.np = 1;
     while (a.np < 32 && a.np * m.num_cus < pairs) a.np *= 2;
   } else {
@@ -1389,22 +1404,15 @@ hipError_t launch_vpair(const aio_model& m, const VGemmArgs& g, int pairs) {
   if (m.cfg.wfmt == AIO_WFMT_INT8) {
     if (a.np <= 16) return launch_vpair_t<I8, EPI, 1, 1, 4>(m, a);
     if (a.np <= 32) return launch_vpair_t<I8, EPI, 1, 2, 2>(m, a);
-    if constexpr (EPI == EPI_SWIGLU) {
-      if (a.np <= 48) return launch_vpair_t<I8, EPI, 2, 3, 2>(m, a);
-      return launch_vpair_t<I8, EPI, 2, 4, 2>(m, a);
-    }
-    return hipErrorInvalidValue;
+    if (a.np <= 48) return launch_vpair_t<I8, EPI, 2, 3, 2>(m, a);
+    return launch_vpair_t<I8, EPI, 2, 4, 2>(m, a);
   }
   if (a.np <= 8) return launch_vpair_t<BF, EPI, 1, 1, 4>(m, a);
   if (a.np <= 16) return launch_vpair_t<BF, EPI, 1, 2, 4>(m, a);
-  if constexpr (EPI == EPI_SWIGLU)
-    if (a.np <= 24) return launch_vpair_t<BF, EPI, 1, 3, 2>(m, a);
+  if (a.np <= 24) return launch_vpair_t<BF, EPI, 1, 3, 2>(m, a);
   if (a.np <= 32) return launch_vpair_t<BF, EPI, 1, 4, 2>(m, a);
-  if constexpr (EPI == EPI_SWIGLU) {
-    if (a.np <= 48) return launch_vpair_t<BF, EPI, 2, 6, 2>(m, a);
-    return launch_vpair_t<BF, EPI, 2, 8, 2>(m, a);
-  }
-  return hipErrorInvalidValue;
+  if (a.np <= 48) return launch_vpair_t<BF, EPI, 2, 6, 2>(m, a);
+  return launch_vpair_t<BF, EPI, 2, 8, 2>(m, a);
 }
 
 // Stream-K launch of the gate/up product of `tiles` tile pairs: one workgroup per

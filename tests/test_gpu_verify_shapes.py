@@ -1,7 +1,7 @@
 """The verify products' work splits and the attention's splits at their edges
-(needs an MI355X with 256 CUs).  Behind up to 256 visible positions gate/up runs
-as k_vgemm_sk, beyond as k_vpair with np = pairs / 256 row pairs per workgroup,
-rounded up; QKV is k_vpair with the next power of two, at most 32.  Each case is
+(needs an MI355X with 256 CUs).  QKV is k_vpair with np = pairs / 256 row
+pairs per workgroup, rounded up, and behind up to 256 visible positions the next
+power of two, at most 32; gate/up is k_vgemm_sk there and k_vpair beyond.  Each case is
 held to the bounds of the verify's oracle comparison: fp32 sums in another order,
 and one bf16 rounding per cache entry."""
 import pytest
@@ -31,10 +31,13 @@ CASES = {
     "int8_np17": dict(ONE, ffn_dim=4160, wfmt="int8"),
     "int8_np33": dict(ONE, ffn_dim=8256, wfmt="int8"),
     "int8_np49": dict(ONE, ffn_dim=12352, wfmt="int8"),
-    # QKV of 12288 pairs: 384 workgroups of 32 (half a head each), three ragged
-    # K stages
+    # QKV of 12288 pairs, three ragged K stages: behind a short cache 384 workgroups
+    # of 32 (half a head each), then 256 of 48 (which start inside a head and span
+    # q, k and v)
     "qkv32": dict(WIDE_QKV, d_model=576),
     "qkv32_int8": dict(WIDE_QKV, d_model=576, wfmt="int8"),
+    "qkv48": dict(WIDE_QKV, d_model=576, prompt_len=256),
+    "qkv48_int8": dict(WIDE_QKV, d_model=576, prompt_len=256, wfmt="int8"),
     # gate/up ranges: 10 over two tile pairs of 16 stages, so that up to five meet
     # in one; 129 of two whole pairs; 256 of 2 or 3 units, ragged stages
     "sk_shared": dict(SHORT, d_model=4096, ffn_dim=64),
