@@ -1115,7 +1115,7 @@ AIO_DEV void attend(const KV4& d, int n, const float (&q)[G][8], float (&o)[G][8
 // fused multiply-adds here and in attn_merge are fixed: behind a few keys a
 // rounding that falls the other way moves a 7B's logits by up to 1e-3.  (One
 // maximum over all groups and the exchanges in any order: 8 tokens of the 1B at 2K
-// 5507 -> 5460 us, 4 of the 7B 9055 -> 9047, int8 6244 -> 6208.)
+// 5491 -> 5469 us, 4 of the 7B 9026 -> 9032, int8 6213 -> 6197.)
 template <int LPK>
 constexpr int fold_dims() { return LPK == 16 ? 2 : 1; }
 template <int LPK>
@@ -1151,8 +1151,10 @@ AIO_DEV void fold_pair(float (&o)[G][8], float (&m)[G], float (&l)[G], int lane)
     partners<BIT>(m[gg], m[gg], up, m1, m2);
     partners<BIT>(l[gg], l[gg], up, l1, l2);
     const float mx = fmaxf(m1, m2);
-    const float c1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mx);
-    const float c2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mx);
+    // (the weight of the larger maximum is 1)
+    const float e = __builtin_amdgcn_exp2f(-fabsf(m1 - m2));
+    const float c1 = m1 >= m2 ? (m1 == -INFINITY ? 0.f : 1.f) : e;
+    const float c2 = m2 >= m1 ? (m2 == -INFINITY ? 0.f : 1.f) : e;
     l[gg] = fmaf(l1, c1, l2 * c2);
 #pragma unroll
     for (int i = 0; i < HALF; ++i) {
@@ -1272,7 +1274,9 @@ AIO_DEV void attn_merge(CArgs& a, int g, float* lds, unsigned ver) {
     for (int i = 0; i < 3 * MS; ++i) v[i] = ld_dev(base + off[i]);
     await4(a, base, off, need, v, ver);
     // splits in order, each with the running maximum up to it; the maxima come
-    // first, so that the weights do not wait for one another
+    // first, so that the weights do not wait for one another.  Of a step's two
+    // weights (of the sums so far and of the split) the one with the larger maximum
+    // is 1.
     float mx[MS + 1];
     mx[0] = Mt;
 #pragma unroll
@@ -1280,13 +1284,12 @@ AIO_DEV void attn_merge(CArgs& a, int g, float* lds, unsigned ver) {
       mx[i + 1] = fmaxf(mx[i], need[3 * i] ? untagf(v[3 * i + 1]) : -INFINITY);
 #pragma unroll
     for (int i = 0; i < MS; ++i) {
-      const float ms = untagf(v[3 * i + 1]);
-      const bool live = need[3 * i] && ms != -INFINITY;
-      const float c0 = live ? __builtin_amdgcn_exp2f(mx[i] - mx[i + 1]) : 1.f;
-      const float c1 = live ? __builtin_amdgcn_exp2f(ms - mx[i + 1]) : 0.f;
-      const float ov = live ? untagf(v[3 * i]) : 0.f, lv = live ? untagf(v[3 * i + 2]) : 0.f;
-      Ot = fmaf(Ot, c0, c1 * ov);
-      Lt = fmaf(Lt, c0, c1 * lv);
+      const float ms = need[3 * i] ? untagf(v[3 * i + 1]) : -INFINITY;
+      const bool up = ms > mx[i];
+      const float e = __builtin_amdgcn_exp2f(-fabsf(ms - mx[i]));
+      const float c0 = up ? e : 1.f, c1 = up ? 1.f : (ms == -INFINITY ? 0.f : e);
+      Ot = fmaf(Ot, c0, c1 * untagf(v[3 * i]));
+      Lt = fmaf(Lt, c0, c1 * untagf(v[3 * i + 2]));
     }
     Mt = mx[MS];
   }
