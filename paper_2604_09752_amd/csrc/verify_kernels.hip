@@ -42,7 +42,8 @@ constexpr int kMaxRows = AIO_MAX_VERIFY_ROWS;
 // rows attend mostly to one another, so a K or V element whose fp32 value rounds
 // the other way moves everything after it: two orders of the gate/up sums put the
 // cache rows of a 7B verify of 4 rows at position 17 up to 1.1e-3 apart (each as
-// far from a 64-bit evaluation), 7e-4 at 40, 2.5e-4 at 400 and 2048.  So gate/up
+// far from a 64-bit evaluation), 7e-4 at 40, some 2e-4 at 260 and less beyond (at
+// the median: over 960 inputs at 260 to 14000 positions 4.5e-4 at most).  So gate/up
 // runs in the order of k_vgemm_sk up to here, some 4 us per layer of a 7B slower
 // than k_vpair, which takes it beyond; QKV keeps its workgroups inside blocks of 32
 // pairs, and a single attention split folds its waves one by one (256: one split, a
